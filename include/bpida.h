@@ -9,7 +9,7 @@
  * (CreateRootSet), the block-parallel f-limited DFS (BPDFS: one subtree per
  * workgroup, the DFS stack in LDS, one wavefront expanding per round either
  * 16 nodes x 4 moves, Alg. 1's thread-to-action map, or 64 nodes, one per
- * lane with its four moves, the batched default) and the per-limit reduction
+ * lane, the batched default) and the per-limit reduction
  * of node counts and next limits.
  *
  * Conventions shared by every entry point:
@@ -254,17 +254,20 @@ int bpida_server_stop(void);
  *                        for 16-node rounds, 1024 for 64-node rounds (64-node
  *                        rounds need at least 512 on 4x4 and 1024 on 5x5, 256
  *                        on 3x3; 640, 672 and 768 only for batched 64-node
- *                        rounds with one-wave workgroups, where they let 24,
- *                        20 and 20 waves share a compute unit instead of 16;
- *                        at 672 the 4x4 stack interleaves each entry's state
- *                        and meta word, one instruction less per child; other
- *                        combinations are BPIDA_EINVAL at solve time); deeper
+ *                        rounds with one-wave workgroups, where they let 25,
+ *                        23 and 20 waves share a compute unit instead of 16;
+ *                        other combinations are BPIDA_EINVAL at solve time).
+ *                        An entry is 10 bytes; batched 64-node rounds keep
+ *                        3x3 and 4x4 stacks as 12-byte entries, four fifths
+ *                        as many in the same LDS, each a node with all the
+ *                        moves it has left.  Deeper
  *                        entries spill to HBM (plain) or to the work queue
  *                        (batched).  A smaller stack spills more: with 512
  *                        entries, batches of thousands of 4x4 instances can
  *                        overflow the default work queue (BPIDA_ENOMEM)
- *   "nodes_per_round"    batched mode: 64 (default) pops one node per lane and
- *                        each lane tries the four moves; 16 uses Alg. 1's map
+ *   "nodes_per_round"    batched mode: 64 (default) pops one entry per lane
+ *                        (3x3, 4x4: each lane makes one move; 5x5: all four);
+ *                        16 uses Alg. 1's map
  *                        (lane l expands node l/4 with move l%4).
  *   "wg_size"            batched mode and server: threads per workgroup of the
  *                        persistent kernel, 64 (default), 128 or 256: 1, 2 or

@@ -19,6 +19,7 @@
 
 #include "bpida_board.h"
 #include "bpida_internal.h"
+#include "bpida_ring.h"
 #include "bpida_round.h"
 
 namespace bpida {
@@ -83,10 +84,10 @@ __device__ __forceinline__ bool cas64(uint64_t* p, uint64_t expect, uint64_t wan
 }
 
 // Returns false if the ring stayed full for the whole bounded wait (the
-// entries were not queued).  `hi` is stored only for 5x5 chunks (wide), in
-// the slot's row of A.hi.
+// entries were not queued).  `kind` says what the entries are (kChunk*); `hi`
+// is stored only for 5x5 chunks, in the slot's row of A.hi.
 __device__ bool q_push(const BatchArgs& A, uint64_t tile, uint64_t hi, uint16_t meta, int count,
-                       int inst, bool wide) {
+                       int inst, int kind) {
   const int lane = lane_id();
   QueueCtl* q = A.q;
   const uint64_t mask = A.qmask;
@@ -118,12 +119,12 @@ __device__ bool q_push(const BatchArgs& A, uint64_t tile, uint64_t hi, uint16_t 
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   QChunk* c = A.slots + (pos & mask);
   c->tiles[lane] = tile;
-  if (wide) A.hi[(pos & mask) * kQChunk + lane] = hi;
+  if (kind == kChunkWide) A.hi[(pos & mask) * kQChunk + lane] = hi;
   c->meta[lane] = meta;
   if (lane == 0) {
     c->inst = inst;
     c->count = count;
-    c->wide = wide ? 1 : 0;
+    c->kind = kind;
   }
   WAVE_SYNC_MEM();  // every lane's stores precede lane 0's release
   if (lane == 0) __hip_atomic_store(&A.seq[pos & mask].seq, 4 * pos + 2, __ATOMIC_RELEASE, AGENT);
@@ -134,7 +135,7 @@ __device__ bool q_push(const BatchArgs& A, uint64_t tile, uint64_t hi, uint16_t 
 // ticket's chunk has arrived.  Returns true with the chunk, or false (the
 // ticket is kept for the next call, or dropped if its producer gave up).
 __device__ bool q_take(const BatchArgs& A, uint64_t& ticket, uint64_t& tile, uint64_t& hi,
-                       uint16_t& meta, int& count, int& inst) {
+                       uint16_t& meta, int& count, int& inst, int& kind) {
   const int lane = lane_id();
   QueueCtl* q = A.q;
   const uint64_t mask = A.qmask;
@@ -160,7 +161,8 @@ __device__ bool q_take(const BatchArgs& A, uint64_t& ticket, uint64_t& tile, uin
   count = wave_bcast(c->count);
   inst = wave_bcast(c->inst);
   // the high words only for a 5x5 chunk: a 4x4 chunk reads 6 lines, not 10
-  const int wide = wave_bcast(c->wide);
+  kind = wave_bcast(c->kind);
+  const bool wide = kind == kChunkWide;
   hi = wide ? A.hi[(ticket & mask) * kQChunk + lane] : 0ull;
   if (wide && lane == 0) __hip_atomic_fetch_add(&q->chunks_read_wide, (uint64_t)1, __ATOMIC_RELAXED, AGENT);
   WAVE_SYNC_MEM();  // all lanes have read the slot before it is handed back
@@ -226,7 +228,7 @@ __device__ bool seed_limit(const BatchArgs& A, int i, uint64_t* stage, uint16_t*
       const uint64_t th = lane < pc ? stage[64 + p0 + lane] : 0ull;
       const uint16_t m = lane < pc ? stage_m[p0 + lane] : (uint16_t)0;
       if (lane == 0) __hip_atomic_fetch_add(&S->outstanding, 1, __ATOMIC_RELAXED, AGENT);
-      if (!q_push(A, t, th, m, pc, i, wide)) {
+      if (!q_push(A, t, th, m, pc, i, wide ? kChunkWide : kChunkNodes)) {
         full = true;  // the remaining roots are dropped; the call reports BPIDA_ENOMEM
         if (lane == 0) {
           __hip_atomic_fetch_add(&S->outstanding, -1, __ATOMIC_RELAXED, AGENT);
@@ -572,47 +574,140 @@ struct WgCounters {
   uint64_t rounds = 0, pushes = 0, voluntary = 0;
 };
 
-// Searches one unit (the chunk already in LDS entries [0, cnt)) of an
-// instance of width W until its stack is empty: BPDFS rounds, with spills
-// to the queue when LDS would overflow and donations to waiting workgroups.
-// NPL = nodes popped per round: 16 (lane l expands node l/4 with move l%4,
-// Alg. 1's thread -> action map; width 4 only) or 64 (one node per lane,
-// four moves each).  Returns false if the time budget ran out (abandoned).
-template <int W, int CAP, int NPL, bool FS>
-__device__ bool run_unit(const BatchArgs& A, int inst, int limit, typename Board<W>::S* st,
-                         uint16_t* sm, int cnt, WgCounters& wc, uint32_t& tick, uint64_t deadline,
-                         uint64_t& expanded, int& goals, int& fmin) {
-  static_assert(NPL == 64 || W == 4, "16-node rounds are the 4x4 map");
-  static_assert(NPL == 64 ? CAP >= 256 : ((CAP & (CAP - 1)) == 0 && CAP >= 128), "stack size");
+// The LDS stack of one wave while it searches a unit: entries [0, top), the
+// oldest at 0.  NodeStack holds nodes to expand (16-node rounds: Alg. 1's
+// map, lane l expands node l/4 with move l%4, 4x4 only; 64-node rounds: one
+// node per lane, four moves each, 5x5), RingStack expanded 3x3 and 4x4 nodes
+// with the moves they have left (one move per lane and round, bpida_ring.h).
+template <int W, int CAP, int NPL>
+struct NodeStack {
+  static_assert(NPL == 64 ? W == 5 && CAP >= 256 : W == 4 && (CAP & (CAP - 1)) == 0 && CAP >= 128, "stack");
   using S = typename Board<W>::S;
-  const int lane = lane_id();
-  QueueCtl* q = A.q;
-  const bool wide = W == 5;
+  static constexpr int kCap = CAP, kNpl = NPL;
   // largest growth of one round: a node has at most 3 children (its parent's
   // cell is excluded).  Only a root of the split (depth 0) has no parent and
   // may have 4, and a root is expanded in the unit's first round, which
   // starts from one chunk (at most 64 entries) and so cannot overflow.
-  constexpr int kGrow = NPL == 16 ? 32 : 2 * 64;
-  // 64-node rounds on 3x3 and 4x4 stacks store without branches (under the
-  // keep mask)
-  constexpr bool kMasked = NPL == 64 && sizeof(S) == 8;
-  // the width-4 64-node round keeps its stack in its own layout (its own
-  // meta word; 12-byte interleaved entries at 672 entries); chunks carry
-  // the common meta word
-  constexpr bool kMeta4 = NPL == 64 && W == 4;
-  constexpr int kCap = CAP;
-  const LaneMap M = make_lane_map(lane);
-  const RoundConsts4 rk = make_round_consts4();
+  static constexpr int kGrow = NPL == 16 ? 32 : 2 * 64;
+  static constexpr int kKind = W == 5 ? kChunkWide : kChunkNodes;
+  struct Entry {
+    S s;
+    uint16_t m;
+  };
+  S* st;
+  uint16_t* sm;
+  LaneMap M;
+  int limit;
+
+  __device__ __forceinline__ NodeStack(uint64_t* lds, int lim)
+      : st((S*)lds), sm((uint16_t*)((S*)lds + CAP)), M(make_lane_map(lane_id())), limit(lim) {}
+  __device__ __forceinline__ Entry get(uint32_t i) const { return {st[i], sm[i]}; }
+  __device__ __forceinline__ void put(uint32_t i, Entry e) {
+    st[i] = e.s;
+    sm[i] = e.m;
+  }
+  __device__ __forceinline__ bool push(const BatchArgs& A, Entry e, int count, int inst) const {
+    return q_push(A, (uint64_t)e.s, W == 5 ? (uint64_t)((unsigned __int128)e.s >> 64) : 0ull, e.m, count, inst, kKind);
+  }
+  __device__ __forceinline__ uint32_t round(uint32_t top, int kp, int& goals, int& fmin) {
+    if constexpr (NPL == 16) return bp_round<CAP>(st, sm, top, kp, limit, M, goals, fmin);
+    else return bp_round64w<W, CAP, false>(st, sm, top, kp, goals);
+  }
+  __device__ __forceinline__ uint32_t full_round(uint32_t top, uint64_t& gm) {
+    return bp_round64w<W, CAP, true>(st, sm, top, 64, gm);
+  }
+};
+
+template <int W, int CAP>
+struct RingStack {
+  static constexpr int kCap = CAP, kNpl = 64;
+  static constexpr int kGrow = 64;  // an entry and its child replace an entry
+  static constexpr uint32_t kTable = kRingEntry * CAP;
+  struct Entry {
+    uint32_t r, c, m;
+  };
+  Entry* st;
+  RingConsts k;
+
+  __device__ __forceinline__ RingStack(uint64_t* lds)
+      : st((Entry*)lds), k(make_ring_consts<W>((char*)lds, kTable)) {}
+  __device__ __forceinline__ Entry get(uint32_t i) const { return st[i]; }
+  __device__ __forceinline__ void put(uint32_t i, Entry e) { st[i] = e; }
+  __device__ __forceinline__ bool push(const BatchArgs& A, Entry e, int count, int inst) const {
+    return q_push(A, (uint64_t)e.r | ((uint64_t)e.c << 32), 0ull, (uint16_t)ring_pack(e.m), count, inst, kChunkRing);
+  }
+  __device__ __forceinline__ uint32_t round(uint32_t top, int kp, int& goals, int&) {
+    uint64_t gm = 0;
+    top = ring_round<W, kTable, false>(top, kp, gm, k);
+    goals += __popcll(gm);
+    return top;
+  }
+  __device__ __forceinline__ uint32_t full_round(uint32_t top, uint64_t& gm) {
+    return ring_round<W, kTable, true>(top, 64, gm, k);
+  }
+
+  // Loads a chunk: entries that are under way as they are; nodes are expanded
+  // here (counted, tested for the goal, and stored if they keep a move).
+  __device__ __forceinline__ uint32_t load(uint64_t t, uint16_t meta, int cnt, int kind, uint64_t& expanded, int& goals) {
+    const uint32_t lane = (uint32_t)lane_id();
+    uint32_t top = (uint32_t)cnt;
+    if (kind == kChunkRing) {
+      if (lane < top) put(lane, {(uint32_t)t, (uint32_t)(t >> 32), ring_unpack(meta)});
+    } else {
+      uint32_t r, c, b;
+      ring_planes<W>(t, meta & 15u, &r, &c, &b);
+      const uint32_t fb = (meta >> 5) & 7u;
+      const uint32_t undo = fb == 0 ? kRingU : fb == 1 ? kRingL : fb == 2 ? kRingR : fb == 3 ? kRingD : 0u;
+      const uint32_t base = (b << 3) | ((uint32_t)(meta >> 9) * kRingSlack1);
+      const uint32_t near = ring_nearer(r, c, ring_compare<W>(b));
+      const uint32_t m = ring_meta(base, near, ring_legal<W>(b), undo);
+      expanded += (uint64_t)cnt;
+      goals += __popcll(__builtin_amdgcn_ballot_w64(lane < top && t == (uint64_t)Board<W>::goal()));
+      const uint64_t km = __builtin_amdgcn_ballot_w64(lane < top && m > kRingBase);
+      const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(km >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)km, 0u));
+      if (lane < top && m > kRingBase) put(at, {r, c, m});
+      top = (uint32_t)__popcll(km);
+    }
+    WAVE_SYNC();
+    return top;
+  }
+};
+
+// Moves stack entries [src, src + n) down to [dst, dst + n), dst < src, 64 at
+// a time in ascending order: every entry is read before anything is written
+// over it.
+template <class ST>
+__device__ __forceinline__ void stack_down(ST& S, uint32_t dst, uint32_t src, uint32_t n) {
+  for (uint32_t i = 0; i < n; i += 64u) {
+    const uint32_t k = i + (uint32_t)lane_id();
+    if (k < n) S.put(dst + k, S.get(src + k));
+  }
+  WAVE_SYNC();
+}
+
+// Searches one unit (the entries [0, top) of stack S) of an instance until
+// its stack is empty: BPDFS rounds, with spills to the queue when LDS would
+// overflow and donations to waiting workgroups.  Returns false if the time
+// budget ran out (abandoned).
+template <class ST, bool FS>
+__device__ bool run_unit(const BatchArgs& A, int inst, int limit, ST& S, uint32_t top, WgCounters& wc, uint32_t& tick,
+                         uint64_t deadline, uint64_t& expanded, int& goals, int& fmin) {
+  using Entry = typename ST::Entry;
+  constexpr int kCap = ST::kCap, kNpl = ST::kNpl, kGrow = ST::kGrow;
+  const int lane = lane_id();
+  QueueCtl* q = A.q;
   // Donating from a shallow stack hands over pieces too small to pay for the
   // transfer; a threshold the stack seldom reaches stops donation and leaves
   // subtrees on one workgroup.  Default: four rounds' worth of pops, at most
   // half the stack.
-  const int dmin = A.donate_min > 0 ? A.donate_min : min(4 * NPL, CAP / 2);
-  // The LDS stack holds entries [0, top), the oldest at 0.  Entries taken
-  // from the bottom (spills, donations) make the rest move down, so a
-  // position never wraps and a round addresses the stack without a mask.
-  uint32_t top = (uint32_t)cnt;
-  if (FS && wave_bcast(lane == 0 ? ld_relaxed(&A.is[inst].stop) : 0)) top = 0;
+  const int dmin = A.donate_min > 0 ? A.donate_min : min(4 * kNpl, kCap / 2);
+  // Entries taken from the bottom (spills, donations) make the rest move
+  // down, so a position never wraps and a round addresses the stack without
+  // a mask.
+  if (FS) {
+    if (goals > 0 && lane == 0) __hip_atomic_store(&A.is[inst].stop, 1, __ATOMIC_RELAXED, AGENT);
+    if (goals > 0 || wave_bcast(lane == 0 ? ld_relaxed(&A.is[inst].stop) : 0)) top = 0;
+  }
   // The deadline, donation and first-solution polls come every
   // min(64, donate_every) rounds, a period that divides each of theirs; the
   // rounds in between test only whether the next round needs a spill.
@@ -643,38 +738,17 @@ __device__ bool run_unit(const BatchArgs& A, int inst, int limit, typename Board
           const int w = min(avail, A.donate_window) & ~1;
           const int h = w >> 1;
           // (positions up to 127: inside the stack's storage, read for every lane)
-          S tg, tk;
-          uint16_t mg, mk;
-          if constexpr (kMeta4) {
-            tg = (S)e4_tile<CAP>((uint64_t*)st, 2 * lane);
-            tk = (S)e4_tile<CAP>((uint64_t*)st, 2 * lane + 1);
-            mg = (uint16_t)e4_meta<CAP>((uint64_t*)st, 2 * lane);
-            mk = (uint16_t)e4_meta<CAP>((uint64_t*)st, 2 * lane + 1);
-          } else {
-            tg = st[2 * lane];
-            tk = st[2 * lane + 1];
-            mg = sm[2 * lane];
-            mk = sm[2 * lane + 1];
-          }
+          const Entry give = S.get(2 * lane), keep = S.get(2 * lane + 1);
           WAVE_SYNC();
           if (lane == 0) __hip_atomic_fetch_add(&A.is[inst].outstanding, 1, __ATOMIC_RELAXED, AGENT);
-          if (q_push(A, (uint64_t)tg, wide ? (uint64_t)((unsigned __int128)tg >> 64) : 0ull,
-                     kMeta4 ? (uint16_t)meta4_out(mg) : mg, h, inst, wide)) {
+          if (S.push(A, give, h, inst)) {
             wc.pushes += 1;
             wc.voluntary += 1;
             // the kept half becomes the bottom, the entries above the window
             // close up behind it
-            if constexpr (kMeta4) {
-              if (lane < h) e4_put<CAP>((uint64_t*)st, lane, (uint64_t)tk, mk);
-              WAVE_SYNC();
-              move_down4<CAP>((uint64_t*)st, (uint32_t)h, (uint32_t)w, top - (uint32_t)w);
-            } else {
-              if (lane < h) {
-                st[lane] = tk;
-                sm[lane] = mk;
-              }
-              move_down(st, sm, (uint32_t)h, (uint32_t)w, top - (uint32_t)w);
-            }
+            if (lane < h) S.put(lane, keep);
+            WAVE_SYNC();
+            stack_down(S, (uint32_t)h, (uint32_t)w, top - (uint32_t)w);
             top -= (uint32_t)h;
             avail -= h;
           } else if (lane == 0) {
@@ -687,30 +761,23 @@ __device__ bool run_unit(const BatchArgs& A, int inst, int limit, typename Board
       // LDS could overflow: move the oldest entries to the queue, 64 at a
       // time, until the largest round fits.
       do {
-        const S t = kMeta4 ? (S)e4_tile<CAP>((uint64_t*)st, lane) : st[lane];
-        const uint16_t m = kMeta4 ? (uint16_t)e4_meta<CAP>((uint64_t*)st, lane) : sm[lane];
+        const Entry e = S.get(lane);
         WAVE_SYNC();
         if (lane == 0) __hip_atomic_fetch_add(&A.is[inst].outstanding, 1, __ATOMIC_RELAXED, AGENT);
-        if (q_push(A, (uint64_t)t, wide ? (uint64_t)((unsigned __int128)t >> 64) : 0ull,
-                   kMeta4 ? (uint16_t)meta4_out(m) : m, 64, inst, wide)) {
+        if (S.push(A, e, 64, inst)) {
           wc.pushes += 1;
         } else if (lane == 0) {
           __hip_atomic_fetch_add(&A.is[inst].outstanding, -1, __ATOMIC_RELAXED, AGENT);
           __hip_atomic_store(&A.is[inst].lost, 1, __ATOMIC_RELAXED, AGENT);
           atomicOr(&q->err, 2);  // entries dropped: the call reports BPIDA_ENOMEM
         }
-        if constexpr (kMeta4) move_down4<CAP>((uint64_t*)st, 0u, 64u, top - 64u);
-        else move_down(st, sm, 0u, 64u, top - 64u);
+        stack_down(S, 0u, 64u, top - 64u);
         top -= 64u;
         avail -= 64;
       } while (avail + kGrow > kCap);
     }
-    const int kp = min(avail, NPL);
-    if constexpr (NPL == 16) {
-      top = bp_round<CAP>((uint64_t*)st, sm, top, kp, limit, M, goals, fmin);
-    } else {
-      top = bp_round64w<W, CAP, kMasked, false>(st, sm, top, kp, goals, rk);
-    }
+    const int kp = min(avail, kNpl);
+    top = S.round(top, kp, goals, fmin);
     // the spill above keeps every round inside the stack; a round that ended
     // past it would have overwritten entries (reported, never silent)
     if (top > (uint32_t)kCap) atomicOr(&q->err, 32);  // every lane: a uniform branch
@@ -727,9 +794,9 @@ __device__ bool run_unit(const BatchArgs& A, int inst, int limit, typename Board
       if (poll && (tick & 63u) == 0 && wave_bcast(lane == 0 ? ld_relaxed(&A.is[inst].stop) : 0))
         break;
     }
-    if constexpr (NPL == 64) {
+    if constexpr (kNpl == 64) {
       // Full rounds with nothing else to test: while the stack holds 64
-      // entries and has room for their children (the condition under which
+      // entries and has room for what they leave (the condition under which
       // the round above needs no spill) and no poll is due, 64-node rounds
       // run back to back; their counts are added once at the end.  The
       // first-solution search also leaves after a round that expanded a goal
@@ -741,7 +808,7 @@ __device__ bool run_unit(const BatchArgs& A, int inst, int limit, typename Board
       for (;;) {
         if (r >= n) break;
         if (top - 64u > (uint32_t)(kCap - kGrow - 64)) break;
-        top = bp_round64w<W, CAP, kMasked, true>(st, sm, top, 64, gm, rk);
+        top = S.full_round(top, gm);
         ++r;
         if constexpr (FS) {
           if (gm != 0) break;
@@ -763,27 +830,28 @@ __device__ bool run_unit(const BatchArgs& A, int inst, int limit, typename Board
   // and every limit below the optimum prunes one: below the optimum, a path
   // of approaching moves from a slack-0 node cannot reach the goal, so it
   // ends at a node whose remaining moves all go away and are pruned
-  if (NPL == 64) fmin = limit + 2;
+  if (kNpl == 64) fmin = limit + 2;
   return true;
 }
 
 // The persistent kernel.  A workgroup holds WPG independent waves (Sec. 5's
 // block = one warp, WPG times over): each wave has its own stack and takes
-// its own work, and no wave ever waits for another.  LDS per wave: CAP
-// entries of u64 tiles + u16 meta for widths 3 and 4 (10 bytes an entry;
-// 12 for width 4 in the interleaved layout, which then sizes the stack for
-// every width), CAP/2 entries of 128-bit tiles + u16 meta for width 5; the
-// width is read per chunk from the instance.
+// its own work, and no wave ever waits for another.  LDS per wave: 10 * CAP
+// bytes, i.e. CAP nodes of a 16-node round, 5/6 CAP entries of the 3x3 and
+// 4x4 64-node round, or CAP/2 nodes of 5x5; the width is read per chunk from
+// the instance.
 //
-// Waves per SIMD a one-wave workgroup's 64-node stack allows (LDS: 160 KB
-// per compute unit): 24 per compute unit at 640 entries, 20 at 672
-// (interleaved) and 768, 16 at 1024.  The launch bound keeps the vector
-// registers within that occupancy (at most 80 per lane at 6 waves per SIMD,
-// 96 at 5), capped at 6.
+// Waves per SIMD a one-wave workgroup's stack allows (LDS: 160 KB per compute
+// unit).  The launch bound keeps the vector registers within that occupancy,
+// capped at 8.
 template <int CAP, int NPL>
 constexpr int batch_waves_per_simd() {
-  constexpr int w = NPL != 64 ? 1 : (int)(163840u / stack4_bytes<CAP>()) / 4;
-  return w > 6 ? 6 : w < 1 ? 1 : w;
+  constexpr int w = NPL != 64 ? 1 : (int)(163840u / (10u * CAP)) / 4;
+  return w > 8 ? 8 : w < 1 ? 1 : w;
+}
+template <int CAP>
+constexpr int ring_cap() {
+  return (CAP * 10 - (int)kRingTable) / 12 / 16 * 16;
 }
 
 template <int CAP, int NPL, int WPG, bool FS>
@@ -792,13 +860,10 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
   static_assert(NPL == 16 || NPL == 64, "nodes per round");
   static_assert(NPL == 16 || CAP >= 256, "stack too small for 64-node rounds");
   static_assert(WPG == 1 || WPG == 2 || WPG == 4, "waves per workgroup");
-  // u64 words of one wave's stack: 10 bytes an entry, or 12 with the
-  // interleaved width-4 layout of 64-node rounds
-  constexpr int kWords = (int)((NPL == 64 ? stack4_bytes<CAP>() : 10u * CAP) / 8u);
+  constexpr int kWords = 10 * CAP / 8;  // u64 words of one wave's stack
   __shared__ __attribute__((aligned(16))) uint64_t lds[WPG * kWords];
-  uint64_t* st = lds + (WPG == 1 ? 0 : (int)(threadIdx.x >> 6) * kWords);  // widths 3, 4: CAP tiles
-  uint16_t* sm = (uint16_t*)(st + CAP);        // CAP (or CAP/2) meta words
-  unsigned __int128* st5 = (unsigned __int128*)st;  // width 5: CAP/2 tiles
+  uint64_t* st = lds + (WPG == 1 ? 0 : (int)(threadIdx.x >> 6) * kWords);
+  uint16_t* sm = (uint16_t*)(st + CAP);  // staging of the seeds' meta words
   const int lane = lane_id();
   QueueCtl* q = A.q;
 
@@ -838,8 +903,8 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
   for (;;) {
     uint64_t t, th;
     uint16_t m;
-    int cnt, inst;
-    if (!q_take(A, ticket, t, th, m, cnt, inst)) {
+    int cnt, inst, kind;
+    if (!q_take(A, ticket, t, th, m, cnt, inst, kind)) {
       if (ld_wave(&q->remaining) <= 0) break;
       if (!A.server && (ld_wave(&q->err) & kErrFatal)) break;
       const uint64_t now = wall_clock64();
@@ -883,39 +948,33 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
     uint64_t expanded = 0;
     int goals = 0, fmin = INT_MAX;
     bool ok = true;
-    if (width == 4) {
-      if (lane < cnt) {
-        // the 64-node round's stack has its own layout
-        if constexpr (NPL == 64) {
-          e4_put<CAP>(st, lane, t, meta4_in(m));
-        } else {
-          st[lane] = t;
-          sm[lane] = m;
-        }
+    if (width == 5) {
+      // (smaller stacks take no 5x5 batch: the host refuses it)
+      if constexpr (CAP / 2 >= 512) {
+        NodeStack<5, CAP / 2, 64> S(st, limit);
+        if (lane < cnt) S.put(lane, {(unsigned __int128)t | ((unsigned __int128)th << 64), m});
+        WAVE_SYNC();
+        ok = run_unit<NodeStack<5, CAP / 2, 64>, FS>(A, inst, limit, S, (uint32_t)cnt, wc, tick, deadline, expanded,
+                                                     goals, fmin);
       }
-      WAVE_SYNC();
-      ok = run_unit<4, CAP, NPL, FS>(A, inst, limit, st, sm, cnt, wc, tick, deadline,
-                                             expanded, goals, fmin);
     } else if (width == 3) {
       if constexpr (CAP >= 256) {
-        if (lane < cnt) {
-          st[lane] = t;
-          sm[lane] = m;
-        }
-        WAVE_SYNC();
-        ok = run_unit<3, CAP, 64, FS>(A, inst, limit, st, sm, cnt, wc, tick, deadline,
-                                              expanded, goals, fmin);
+        RingStack<3, ring_cap<CAP>()> S(st);
+        const uint32_t top = S.load(t, m, cnt, kind, expanded, goals);
+        ok = run_unit<RingStack<3, ring_cap<CAP>()>, FS>(A, inst, limit, S, top, wc, tick, deadline, expanded, goals,
+                                                         fmin);
       }
+    } else if constexpr (NPL == 64) {
+      RingStack<4, ring_cap<CAP>()> S(st);
+      const uint32_t top = S.load(t, m, cnt, kind, expanded, goals);
+      ok = run_unit<RingStack<4, ring_cap<CAP>()>, FS>(A, inst, limit, S, top, wc, tick, deadline, expanded, goals,
+                                                       fmin);
     } else {
-      if constexpr (CAP / 2 >= 256) {
-        if (lane < cnt) {
-          st5[lane] = (unsigned __int128)t | ((unsigned __int128)th << 64);
-          sm[lane] = m;
-        }
-        WAVE_SYNC();
-        ok = run_unit<5, CAP / 2, 64, FS>(A, inst, limit, st5, sm, cnt, wc, tick,
-                                                  deadline, expanded, goals, fmin);
-      }
+      NodeStack<4, CAP, NPL> S(st, limit);
+      if (lane < cnt) S.put(lane, {t, m});
+      WAVE_SYNC();
+      ok = run_unit<NodeStack<4, CAP, NPL>, FS>(A, inst, limit, S, (uint32_t)cnt, wc, tick, deadline, expanded, goals,
+                                                fmin);
     }
     if (!ok) break;
     const uint64_t now = wall_clock64();

@@ -252,47 +252,20 @@ constexpr bool check_meta4() {
 }
 static_assert(check_meta4(), "width-4 stack meta does not round-trip");
 
-// Width-4 stacks of 64-node rounds come in two layouts.  Split (most sizes):
-// CAP 8-byte states, then CAP 2-byte meta words, 10 bytes an entry.
-// Interleaved (672 entries): entry i holds its state at bytes
-// 12i .. 12i + 7 (two dwords) and its meta word at 12i + 8, so that one
-// address serves both (one instruction less per child and per node, 20 %
-// more LDS per entry, i.e. fewer waves per compute unit at a given size).
-// st is the stack's base.
-template <int CAP>
-constexpr bool stack4_interleaved() {
-  return CAP == 672;
-}
-template <int CAP>
-constexpr uint32_t stack4_bytes() {
-  return (stack4_interleaved<CAP>() ? 12u : 10u) * (uint32_t)CAP;
-}
-constexpr uint32_t kEntry4 = 12;
+// A width-4 stack: CAP 8-byte states, then CAP 2-byte meta words.  st is its
+// base.
 template <int CAP>
 __device__ __forceinline__ uint64_t e4_tile(const uint64_t* st, uint32_t i) {
-  if constexpr (stack4_interleaved<CAP>()) {
-    const uint32_t* p = (const uint32_t*)((const char*)st + kEntry4 * i);
-    return (uint64_t)p[0] | ((uint64_t)p[1] << 32);
-  } else {
-    return st[i];
-  }
+  return st[i];
 }
 template <int CAP>
 __device__ __forceinline__ uint32_t e4_meta(const uint64_t* st, uint32_t i) {
-  if constexpr (stack4_interleaved<CAP>()) return *(const uint16_t*)((const char*)st + kEntry4 * i + 8);
-  else return ((const uint16_t*)(st + CAP))[i];
+  return ((const uint16_t*)(st + CAP))[i];
 }
 template <int CAP>
 __device__ __forceinline__ void e4_put(uint64_t* st, uint32_t i, uint64_t t, uint32_t m) {
-  if constexpr (stack4_interleaved<CAP>()) {
-    uint32_t* p = (uint32_t*)((char*)st + kEntry4 * i);
-    p[0] = (uint32_t)t;
-    p[1] = (uint32_t)(t >> 32);
-    *(uint16_t*)(p + 2) = (uint16_t)m;
-  } else {
-    st[i] = t;
-    ((uint16_t*)(st + CAP))[i] = (uint16_t)m;
-  }
+  st[i] = t;
+  ((uint16_t*)(st + CAP))[i] = (uint16_t)m;
 }
 
 // Moves width-4 stack entries [src, src + n) down to [dst, dst + n), dst <
@@ -303,20 +276,9 @@ __device__ __forceinline__ void move_down4(uint64_t* st, uint32_t dst, uint32_t 
   const uint32_t lane = (uint32_t)lane_id();
   for (uint32_t i = 0; i < n; i += 64u) {
     const uint32_t k = i + lane;
-    if (k < n) {
-      const uint64_t t = e4_tile<CAP>(st, src + k);
-      const uint32_t m = e4_meta<CAP>(st, src + k);
-      e4_put<CAP>(st, dst + k, t, m);
-    }
+    if (k < n) e4_put<CAP>(st, dst + k, e4_tile<CAP>(st, src + k), e4_meta<CAP>(st, src + k));
   }
   WAVE_SYNC();
-}
-
-// r * 12 + c in one instruction (r below 2^24).
-__device__ __forceinline__ uint32_t mad12(uint32_t r, uint32_t c) {
-  uint32_t d;
-  asm("v_mad_u32_u24 %0, %1, 12, %2" : "=v"(d) : "v"(r), "s"(c));
-  return d;
 }
 
 // Move A of the width-4 round takes tile t away from its goal cell (tile t's
@@ -495,36 +457,24 @@ __device__ __forceinline__ void bp_move4(uint64_t* st, uint32_t& out, const uint
   // compiler would put a skip jump around stores in a divergent branch, so
   // the asm sets EXEC to the mask, stores and restores EXEC itself.
   uint64_t saved;
-  if constexpr (stack4_interleaved<CAP>()) {
-    const uint32_t as = lds_addr(st) + mad12(r, out * kEntry4);
-    asm volatile(
-        "s_and_saveexec_b64 %0, %1\n\t"
-        "ds_write2_b32 %2, %3, %4 offset1:1\n\t"
-        "ds_write_b16 %2, %5 offset:8\n\t"
-        "s_mov_b64 exec, %0"
-        : "=&s"(saved)
-        : "s"(km), "v"(as), "v"((uint32_t)cs), "v"((uint32_t)(cs >> 32)), "v"(cm)
-        : "memory", "scc");
-  } else {
-    // (the meta array follows the CAP states)
-    const uint32_t pst = (r + out) << 3;
-    const uint32_t as = lds_addr(st) + pst;
-    const uint32_t am = lds_addr(st) + (pst >> 2);
-    asm volatile(
-        "s_and_saveexec_b64 %0, %1\n\t"
-        "ds_write_b64 %2, %3\n\t"
-        "ds_write_b16 %4, %5 offset:%6\n\t"
-        "s_mov_b64 exec, %0"
-        : "=&s"(saved)
-        : "s"(km), "v"(as), "v"(cs), "v"(am), "v"(cm), "i"(CAP * 8)
-        : "memory", "scc");
-  }
+  // (the meta array follows the CAP states)
+  const uint32_t pst = (r + out) << 3;
+  const uint32_t as = lds_addr(st) + pst;
+  const uint32_t am = lds_addr(st) + (pst >> 2);
+  asm volatile(
+      "s_and_saveexec_b64 %0, %1\n\t"
+      "ds_write_b64 %2, %3\n\t"
+      "ds_write_b16 %4, %5 offset:%6\n\t"
+      "s_mov_b64 exec, %0"
+      : "=&s"(saved)
+      : "s"(km), "v"(as), "v"(cs), "v"(am), "v"(cm), "i"(CAP * 8)
+      : "memory", "scc");
   out += (uint32_t)__popcll(km);
 }
 
 // One BPDFS round of the width-4 board with one popped node per lane: pops
-// kp = min(64, top) nodes from a stack of entries [0, top) (either layout
-// above, meta words in the width-4 layout), tests them for the goal and pushes
+// kp = min(64, top) nodes from a stack of entries [0, top) (meta words in the
+// width-4 layout), tests them for the goal and pushes
 // every legal, non-undoing child with f <= limit.  The caller guarantees
 // that the children fit, top + 2*kp <= CAP; FULL: kp = 64 and `goals` is a
 // 64-bit mask that collects the lanes that expanded a goal, else a count.
@@ -538,16 +488,9 @@ __device__ __forceinline__ uint32_t bp_round64_4(uint64_t* st, uint32_t top, int
   const uint32_t base = top - (uint32_t)kp;
   uint64_t s;
   uint32_t m;
-  if constexpr (stack4_interleaved<CAP>()) {
-    const uint32_t pe = opaque(mad12((uint32_t)lane, base * kEntry4));
-    const uint32_t* pp = (const uint32_t*)((const char*)st + pe);
-    s = (uint64_t)pp[0] | ((uint64_t)pp[1] << 32);
-    m = *(const uint16_t*)(pp + 2);
-  } else {
-    const uint32_t pst = opaque((base + (uint32_t)lane) << 3);
-    s = *(const uint64_t*)((const char*)st + pst);
-    m = *(const uint16_t*)((const char*)(st + CAP) + (pst >> 2));
-  }
+  const uint32_t pst = opaque((base + (uint32_t)lane) << 3);
+  s = *(const uint64_t*)((const char*)st + pst);
+  m = *(const uint16_t*)((const char*)(st + CAP) + (pst >> 2));
   const uint64_t actm = FULL || kp >= 64 ? ~0ull : ((1ull << kp) - 1ull);
   const uint64_t gm = __builtin_amdgcn_uicmpl(s, rk.goal, 32);
   if constexpr (FULL) goals |= gm;
@@ -575,8 +518,8 @@ __device__ __forceinline__ uint32_t bp_round64_4(uint64_t* st, uint32_t top, int
   return out;
 }
 
-// Per-node values shared by the four moves of a 64-node round (widths 3
-// and 5).
+// Per-node values shared by the four moves of a 64-node round
+// (width 5).
 struct NodeCtx {
   uint32_t b;      // blank cell
   uint32_t shb;    // BITS * b
@@ -587,7 +530,7 @@ struct NodeCtx {
 };
 
 // One move for every lane of a 64-node round (see bp_round64w).
-template <int W, int CAP, int A, bool MASKED>
+template <int W, int CAP, int A>
 __device__ __forceinline__ void bp_move_w(typename Board<W>::S* st, uint16_t* sm, uint32_t& out,
                                           const typename Board<W>::S s, const NodeCtx& c) {
   using B = Board<W>;
@@ -603,27 +546,16 @@ __device__ __forceinline__ void bp_move_w(typename Board<W>::S* st, uint16_t* sm
   const uint32_t up = B::template up<A>(x, c.rowi, c.coli);  // 1: t moves away from its goal cell
   const uint32_t kb = opaque((c.lmx >> (A + 4 * up)) & 1u);
   const uint64_t km = __builtin_amdgcn_uicmp(kb, 0u, 33);  // lanes with kb != 0
-  // MASKED (64-bit states): every lane builds its child (a vector
-  // instruction costs the same for any number of active lanes) and only the
-  // lanes that keep it store, under the mask; no branch.  Otherwise (5x5)
-  // the child is built in a branch that the compiler skips when no lane
-  // keeps the move.
-  if (MASKED || kb != 0u) {
+  // the child is built in a branch that the compiler skips when no lane keeps
+  // the move
+  if (kb != 0u) {
     // successor: t moves from n to b, i.e. the packed word changes by
     // t * (base^b - base^n) = +/- (K * t) << (BITS * min(b, n))
-    S cs;
-    if constexpr (A >= 2 && sizeof(S) == 8) {
-      // the subtraction as the addition of -K t sign-extended to 64 bits:
-      // one 64-bit add instead of a subtract with borrow
-      const uint32_t nkt = mul_i24(-(int)K, tile);
-      cs = s + (((0xFFFFFFFFull << 32) | nkt) << (c.shb & 63u));
-    } else {
-      uint32_t kt;
-      if constexpr (K < (1u << 24)) kt = mul_u24(K, tile);
-      else kt = K * tile;  // 5x5 rows: K = 2^25 - 1
-      const S d = (S)kt << ((A < 2 ? shu : c.shb) & (8u * sizeof(S) - 1u));
-      cs = A < 2 ? s + d : s - d;
-    }
+    uint32_t kt;
+    if constexpr (K < (1u << 24)) kt = mul_u24(K, tile);
+    else kt = K * tile;  // 5x5 rows: K = 2^25 - 1
+    const S d = (S)kt << ((A < 2 ? shu : c.shb) & (8u * sizeof(S) - 1u));
+    const S cs = A < 2 ? s + d : s - d;
     // stack meta: n | (3 - A) << 5 | (slack - 2 up) << 8
     const uint32_t cm = mad_i24(up, -512, c.mbase) + (uint32_t)(delta + ((3 - A) << 5));
     const uint32_t r = __builtin_amdgcn_mbcnt_hi((uint32_t)(km >> 32),
@@ -632,32 +564,13 @@ __device__ __forceinline__ void bp_move_w(typename Board<W>::S* st, uint16_t* sm
     // leaves room for the largest round)
     constexpr uint32_t LS = sizeof(S) == 8 ? 3 : 4;
     const uint32_t pst = (r + out) << LS;
-    if constexpr (MASKED) {
-      // the two stores under the keep mask, with no branch around them (the
-      // meta array follows the CAP tiles: sm == st + CAP).  The compiler
-      // would put a skip jump around stores in a divergent branch; this asm
-      // sets EXEC to the mask, stores and restores EXEC itself.
-      const uint32_t as = lds_addr(st) + pst;
-      const uint32_t am = lds_addr(st) + (pst >> (LS - 1));
-      uint64_t saved;
-      asm volatile(
-          "s_and_saveexec_b64 %0, %1\n\t"
-          "ds_write_b64 %2, %3\n\t"
-          "ds_write_b16 %4, %5 offset:%6\n\t"
-          "s_mov_b64 exec, %0"
-          : "=&s"(saved)
-          : "s"(km), "v"(as), "v"(cs), "v"(am), "v"(cm), "i"(CAP * (int)sizeof(S))
-          : "memory", "scc");
-    } else {
-      *(S*)((char*)st + pst) = cs;
-      *(uint16_t*)((char*)sm + (pst >> (LS - 1))) = (uint16_t)cm;
-    }
+    *(S*)((char*)st + pst) = cs;
+    *(uint16_t*)((char*)sm + (pst >> (LS - 1))) = (uint16_t)cm;
   }
   out += (uint32_t)__popcll(km);
 }
 
-// One BPDFS round with one popped node per lane, for boards of width 3 and
-// 5 (width 4 has its own round above, with its own stack meta layout): pops
+// One BPDFS round with one popped node per lane, for 5x5 boards: pops
 // kp = min(64, top) nodes from a stack of entries [0, top), tests them for
 // the goal and pushes every legal, non-undoing child with f <= limit.  The
 // caller guarantees that the children fit, top + 2*kp <= CAP (three
@@ -668,51 +581,43 @@ __device__ __forceinline__ void bp_move_w(typename Board<W>::S* st, uint16_t* sm
 // of pruned children: every slack on the stack is even (f keeps the parity
 // of h0, and so does the limit), so a child is pruned only from slack 0,
 // moving a tile away from its goal, and its f is the limit + 2.
-template <int W, int CAP, bool MASKED, bool FULL, typename G>
+template <int W, int CAP, bool FULL, typename G>
 __device__ __forceinline__ uint32_t bp_round64w(typename Board<W>::S* st, uint16_t* sm, uint32_t top, int kp,
-                                           G& goals, const RoundConsts4& rk) {
-  if constexpr (W == 4) {
-    return bp_round64_4<CAP, FULL>(st, top, kp, goals, rk);
-  } else {
-    using B = Board<W>;
-    using S = typename B::S;
-    const int lane = lane_id();
-    const uint32_t base = top - (uint32_t)kp;
-    constexpr uint32_t LS = sizeof(S) == 8 ? 3 : 4;
-    const uint32_t pst = opaque((base + (uint32_t)lane) << LS);
-    const S s = *(const S*)((const char*)st + pst);
-    const uint32_t m = *(const uint16_t*)((const char*)sm + (pst >> (LS - 1)));
-    const uint64_t actm = FULL || kp >= 64 ? ~0ull : ((1ull << kp) - 1ull);
-    uint64_t gm;
-    if constexpr (sizeof(S) == 8) gm = __builtin_amdgcn_uicmpl((uint64_t)s, (uint64_t)B::goal(), 32);
-    else gm = __builtin_amdgcn_ballot_w64(s == B::goal());
-    // goals: a count (int), or (FULL) the union of the rounds' goal masks
-    if constexpr (FULL) goals |= gm;
-    else goals += __popcll(gm & actm);
-    NodeCtx c;
-    c.b = m & 31u;
-    const uint32_t fb = (m >> 5) & 7u;
-    c.shb = opaque(B::BITS * c.b);
-    uint32_t lm;
-    if constexpr (W * W <= 16) lm = (uint32_t)(legal_table<W>() >> (4u * c.b)) & ~(1u << fb) & 15u;
-    else lm = B::legal(c.b) & ~(1u << fb);
-    c.coli = B::col_part(c.b);
-    c.rowi = B::row_part(c.b);
-    // moves that survive: any legal one if its tile approaches its goal, and
-    // only with slack >= 2 if it moves away (bits 0..3 and 4..7 of lm * 17);
-    // lanes past kp keep nothing
-    const bool roomy = m >= (2u << 8);
-    if constexpr (FULL) c.lmx = mul_u24(lm, roomy ? 17u : 1u);
-    else c.lmx = mul_u24(lm, sel_lanes(actm, roomy ? 17u : 1u));
-    c.mbase = (m & 0xFF00u) | c.b;
-    uint32_t out = base;
-    bp_move_w<W, CAP, 0, MASKED>(st, sm, out, s, c);
-    bp_move_w<W, CAP, 1, MASKED>(st, sm, out, s, c);
-    bp_move_w<W, CAP, 2, MASKED>(st, sm, out, s, c);
-    bp_move_w<W, CAP, 3, MASKED>(st, sm, out, s, c);
-    WAVE_SYNC();
-    return out;
-  }
+                                                G& goals) {
+  using B = Board<W>;
+  using S = typename B::S;
+  const int lane = lane_id();
+  const uint32_t base = top - (uint32_t)kp;
+  constexpr uint32_t LS = sizeof(S) == 8 ? 3 : 4;
+  const uint32_t pst = opaque((base + (uint32_t)lane) << LS);
+  const S s = *(const S*)((const char*)st + pst);
+  const uint32_t m = *(const uint16_t*)((const char*)sm + (pst >> (LS - 1)));
+  const uint64_t actm = FULL || kp >= 64 ? ~0ull : ((1ull << kp) - 1ull);
+  const uint64_t gm = __builtin_amdgcn_ballot_w64(s == B::goal());
+  // goals: a count (int), or (FULL) the union of the rounds' goal masks
+  if constexpr (FULL) goals |= gm;
+  else goals += __popcll(gm & actm);
+  NodeCtx c;
+  c.b = m & 31u;
+  const uint32_t fb = (m >> 5) & 7u;
+  c.shb = opaque(B::BITS * c.b);
+  const uint32_t lm = B::legal(c.b) & ~(1u << fb);
+  c.coli = B::col_part(c.b);
+  c.rowi = B::row_part(c.b);
+  // moves that survive: any legal one if its tile approaches its goal, and
+  // only with slack >= 2 if it moves away (bits 0..3 and 4..7 of lm * 17);
+  // lanes past kp keep nothing
+  const bool roomy = m >= (2u << 8);
+  if constexpr (FULL) c.lmx = mul_u24(lm, roomy ? 17u : 1u);
+  else c.lmx = mul_u24(lm, sel_lanes(actm, roomy ? 17u : 1u));
+  c.mbase = (m & 0xFF00u) | c.b;
+  uint32_t out = base;
+  bp_move_w<W, CAP, 0>(st, sm, out, s, c);
+  bp_move_w<W, CAP, 1>(st, sm, out, s, c);
+  bp_move_w<W, CAP, 2>(st, sm, out, s, c);
+  bp_move_w<W, CAP, 3>(st, sm, out, s, c);
+  WAVE_SYNC();
+  return out;
 }
 
 }  // namespace bpida

@@ -192,8 +192,14 @@ struct alignas(128) QChunk {
   uint16_t meta[kQChunk];
   int32_t inst;
   int32_t count;
-  int32_t wide;  // 1: a 5x5 chunk, whose high words are in BatchArgs::hi
+  int32_t kind;  // kChunk*
 };
+
+// What a chunk's entries are.
+constexpr int kChunkNodes = 0;  // nodes to expand: packed board, stack_meta word
+constexpr int kChunkWide = 1;   // the same on 5x5, high words in BatchArgs::hi
+constexpr int kChunkRing = 2;   // expanded 3x3 or 4x4 nodes with moves left: the two
+                                // planes (rows in the low word), ring_pack'ed meta
 
 // Per-slot control words of the queue ring, for the next ticket t to use the
 // slot: seq == 4t free for producer t, 4t + 1 claimed by it, 4t + 2 holds

@@ -324,8 +324,7 @@ __global__ __launch_bounds__(64) void search64_kernel(const Node* __restrict__ r
                                                       int32_t* __restrict__ stop,
                                                       uint32_t* __restrict__ load) {
   static_assert((CAP & (CAP - 1)) == 0 && CAP >= 512, "stack size for 64-node rounds");
-  // the width-4 round's stack (its layout for this size)
-  __shared__ __attribute__((aligned(16))) uint64_t lds[stack4_bytes<CAP>() / 8];
+  __shared__ __attribute__((aligned(16))) uint64_t lds[10 * CAP / 8];
   uint64_t* st = lds;
   constexpr uint32_t kCap = CAP;
   // largest growth of one round: at most 3 children a node (a unit starts
