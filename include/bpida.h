@@ -296,9 +296,11 @@ int bpida_server_stop(void);
  *   "max_workgroups"     cap on the persistent search grid (0 = occupancy)
  *   "max_threshold"      stop with BPIDA_ELIMIT before a limit above this
  *                        (-1 = none, default)
- *   "donate_every"       batched mode: rounds between a workgroup's checks
- *                        for waiting workgroups to donate to (a power of
- *                        two in 4..1024, default 128)
+ *   "donate_every"       batched mode: a quarter of the rounds between a
+ *                        workgroup's looks for waiting workgroups to donate
+ *                        to while every workgroup searches; when some wait,
+ *                        the searching ones look more often, in proportion
+ *                        (a power of two in 4..1024, default 128)
  *   "start_threshold"    first f-limit to search: -1 (default) = h0; else the
  *                        smallest h0 + 2j >= the value.  Columns of skipped
  *                        limits stay 0.  out_len is then the first searched
@@ -327,7 +329,8 @@ int bpida_server_stop(void);
  *                        alternately.  Overflow spills always move 64.
  *   "donate_min"         batched mode: smallest LDS stack (entries) that
  *                        donates (2..2048; -1 = four rounds' worth of pops,
- *                        at most half the stack: 256 for 64-node rounds, the
+ *                        at most half the stack: 256 for 64-node rounds, half
+ *                        of that while more workgroups wait than search: the
  *                        default).  Too small a value ships pieces of work
  *                        that cost more to move than they hold; one the stack
  *                        seldom reaches stops donation altogether.

@@ -16,6 +16,7 @@
 // solutions: the limit has been searched to completion), and otherwise
 // advances the limit by 2 and seeds the instance's subtree roots again.
 #include <limits.h>
+#include <stddef.h>
 
 #include "bpida_board.h"
 #include "bpida_internal.h"
@@ -83,20 +84,40 @@ __device__ __forceinline__ bool cas64(uint64_t* p, uint64_t expect, uint64_t wan
                                               AGENT);
 }
 
+// Payload and bookkeeping that pass between waves go through relaxed
+// agent-scope accesses (which read and write past the caches that other
+// compute units do not see) in an order kept by waiting for the earlier ones:
+// a release would write back this XCD's whole L2 and an acquire drop its
+// lines, on every hand-over.
+__device__ __forceinline__ void performed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+template <class T>
+__device__ __forceinline__ void st_relaxed(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, AGENT);
+}
+template <class T>
+__device__ __forceinline__ T ld_agent(const T* p) {
+  return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, AGENT);
+}
+
+// One chunk in a wave's registers: lane k holds entry k; the rest is uniform.
+struct Unit {
+  uint64_t tile = 0, hi = 0;  // hi: 5x5 only
+  uint16_t meta = 0;
+  int count = 0, inst = 0, kind = 0, limit = 0, width = 0;
+};
+
 // Returns false if the ring stayed full for the whole bounded wait (the
-// entries were not queued).  `kind` says what the entries are (kChunk*); `hi`
-// is stored only for 5x5 chunks, in the slot's row of A.hi.
-__device__ bool q_push(const BatchArgs& A, uint64_t tile, uint64_t hi, uint16_t meta, int count,
-                       int inst, int kind) {
+// entries were not queued).  `hi` goes to the slot's row of A.hi.
+__device__ bool q_push(const BatchArgs& A, const Unit& u, RunStats& wc) {
   const int lane = lane_id();
   QueueCtl* q = A.q;
   const uint64_t mask = A.qmask;
-  uint64_t pos = 0;
+  uint64_t pos = 0, depth = 0;
   int ok = 0;
   if (lane == 0) {
     pos = __hip_atomic_fetch_add(&q->tail, (uint64_t)1, __ATOMIC_RELAXED, AGENT);
     const uint64_t h = ld_relaxed(&q->head);
-    if (pos + 1 > h) __hip_atomic_fetch_max(&q->qmax, pos + 1 - h, __ATOMIC_RELAXED, AGENT);
+    if (pos + 1 > h) depth = pos + 1 - h;
     SlotCtl* sc = A.seq + (pos & mask);
     for (int k = 0; k < A.push_spin; ++k) {
       const uint64_t v = ld_relaxed(&sc->seq);
@@ -113,38 +134,42 @@ __device__ bool q_push(const BatchArgs& A, uint64_t tile, uint64_t hi, uint16_t 
     }
   }
   ok = wave_bcast(ok);
+  wc.qmax = max(wc.qmax, bcast64(depth));
   if (!ok) return false;
   pos = bcast64(pos);
-  // the slot's previous consumer released it; order the new payload after
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   QChunk* c = A.slots + (pos & mask);
-  c->tiles[lane] = tile;
-  if (kind == kChunkWide) A.hi[(pos & mask) * kQChunk + lane] = hi;
-  c->meta[lane] = meta;
+  st_relaxed(&c->tiles[lane], u.tile);
+  if (u.kind == kChunkWide) st_relaxed(&A.hi[(pos & mask) * kQChunk + lane], u.hi);
+  st_relaxed(&c->meta[lane], u.meta);
   if (lane == 0) {
-    c->inst = inst;
-    c->count = count;
-    c->kind = kind;
+    st_relaxed(&c->inst, (int32_t)u.inst);
+    st_relaxed(&c->info, (int32_t)(u.count | (u.kind << 8) | (u.width << 16)));
+    st_relaxed(&c->limit, (int32_t)u.limit);
   }
-  WAVE_SYNC_MEM();  // every lane's stores precede lane 0's release
-  if (lane == 0) __hip_atomic_store(&A.seq[pos & mask].seq, 4 * pos + 2, __ATOMIC_RELEASE, AGENT);
+  performed();  // the payload, and the atomics on the instance before it, come first
+  if (lane == 0) st_relaxed(&A.seq[pos & mask].seq, 4 * pos + 2);
   return true;
 }
 
 // Takes a consumer ticket if `ticket` holds none, then checks whether that
-// ticket's chunk has arrived.  Returns true with the chunk, or false (the
-// ticket is kept for the next call, or dropped if its producer gave up).
-__device__ bool q_take(const BatchArgs& A, uint64_t& ticket, uint64_t& tile, uint64_t& hi,
-                       uint16_t& meta, int& count, int& inst, int& kind) {
+// ticket's chunk has arrived: 1 with the chunk; 0 not yet (the ticket is kept
+// for the next call, or dropped if its producer gave up); -1 the search is
+// over.
+__device__ int q_take(const BatchArgs& A, uint64_t& ticket, Unit& u, RunStats& wc) {
   const int lane = lane_id();
   QueueCtl* q = A.q;
   const uint64_t mask = A.qmask;
   int ready = 0;
   if (lane == 0) {
-    if (ticket == kNoTicket) ticket = __hip_atomic_fetch_add(&q->head, (uint64_t)1, __ATOMIC_RELAXED, AGENT);
+    const bool fresh = ticket == kNoTicket;
+    if (fresh) {
+      ticket = __hip_atomic_fetch_add(&q->head, (uint64_t)1, __ATOMIC_RELAXED, AGENT);
+      performed();  // a ticket that end_search did not see sees `remaining` below
+    }
     SlotCtl* sc = A.seq + (ticket & mask);
     const uint64_t v = ld_relaxed(&sc->seq);
-    ready = v == 4 * ticket + 2;
+    ready = v == 4 * ticket + 2 ? 1 : v == kSeqEnd ? -1 : 0;
+    if (!ready && fresh && ld_relaxed(&q->remaining) <= 0) ready = -1;
     if (!ready && v == 4 * ticket && ld_relaxed(&sc->abandoned) > ticket &&
         cas64(&sc->seq, 4 * ticket, 4 * (ticket + mask + 1))) {
       // a producer of this slot gave up at or after this ticket: hand the
@@ -153,47 +178,85 @@ __device__ bool q_take(const BatchArgs& A, uint64_t& ticket, uint64_t& tile, uin
     }
   }
   ticket = bcast64(ticket);
-  if (!wave_bcast(ready)) return false;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  ready = wave_bcast(ready);
+  if (ready <= 0) return ready;
+  asm volatile("" ::: "memory");  // the payload is read after the slot's state
   const QChunk* c = A.slots + (ticket & mask);
-  tile = c->tiles[lane];
-  meta = c->meta[lane];
-  count = wave_bcast(c->count);
-  inst = wave_bcast(c->inst);
+  u.tile = ld_agent(&c->tiles[lane]);
+  u.meta = ld_agent(&c->meta[lane]);
+  const int inst = ld_agent(&c->inst), info = ld_agent(&c->info), limit = ld_agent(&c->limit);
+  u.inst = wave_bcast(inst);
+  u.limit = wave_bcast(limit);
+  u.count = wave_bcast(info) & 255;
+  u.kind = (wave_bcast(info) >> 8) & 255;
+  u.width = wave_bcast(info) >> 16;
   // the high words only for a 5x5 chunk: a 4x4 chunk reads 6 lines, not 10
-  kind = wave_bcast(c->kind);
-  const bool wide = kind == kChunkWide;
-  hi = wide ? A.hi[(ticket & mask) * kQChunk + lane] : 0ull;
-  if (wide && lane == 0) __hip_atomic_fetch_add(&q->chunks_read_wide, (uint64_t)1, __ATOMIC_RELAXED, AGENT);
-  WAVE_SYNC_MEM();  // all lanes have read the slot before it is handed back
-  if (lane == 0)
-    __hip_atomic_store(&A.seq[ticket & mask].seq, 4 * (ticket + mask + 1), __ATOMIC_RELEASE, AGENT);
+  const bool wide = u.kind == kChunkWide;
+  u.hi = wide ? ld_agent(&A.hi[(ticket & mask) * kQChunk + lane]) : 0ull;
+  wc.chunks_read_wide += wide ? 1 : 0;
+  performed();  // all lanes have read the slot before it is handed back
+  if (lane == 0) st_relaxed(&A.seq[ticket & mask].seq, 4 * (ticket + mask + 1));
   ticket = kNoTicket;
-  return true;
+  return 1;
+}
+
+// Called by the wave that brought `remaining` to zero: no chunk is queued or
+// held any more (the caller has waited for that decrement).  Tells every wave
+// that waits on a ticket; one that takes its ticket after the fetch_add below
+// sees `remaining` itself.
+__device__ void end_search(const BatchArgs& A) {
+  const int lane = lane_id();
+  uint64_t h = 0, t = 0;
+  if (lane == 0) {
+    h = __hip_atomic_fetch_add(&A.q->head, (uint64_t)0, __ATOMIC_RELAXED, AGENT);
+    t = ld_relaxed(&A.q->tail);
+  }
+  h = bcast64(h);
+  t = bcast64(t);
+  if (h > t + A.qmask + 1) t = h - A.qmask - 1;
+  for (uint64_t k = t + (uint64_t)lane; k < h; k += 64) st_relaxed(&A.seq[k & A.qmask].seq, kSeqEnd);
 }
 
 // ---------------------------------------------------------------------------
 // Limit bookkeeping, executed by one wave.
 // ---------------------------------------------------------------------------
 
-// Pushes the roots of instance i with f <= limit as chunks, under a guard
-// unit so that the limit cannot complete while seeding.  Returns true if the
-// guard's release brought the instance's outstanding count to zero, i.e. the
-// caller must complete the limit itself.
+// Work of instance i that had been added to its outstanding units could not be
+// queued: takes the unit back and marks the instance's counts void.
+__device__ void drop_unit(const BatchArgs& A, int i) {
+  if (lane_id() == 0) {
+    __hip_atomic_fetch_add(&A.is[i].outstanding, -1, __ATOMIC_RELAXED, AGENT);
+    st_relaxed(&A.is[i].lost, 1);
+    atomicOr(&A.q->err, 1);
+  }
+}
+
+// Hands the roots of instance i with f <= L out as chunks: the last one stays
+// with the caller (`mine`: it is searched next, or pushed), the others go to
+// the queue.  A guard unit keeps the limit from completing meanwhile; it
+// becomes mine's unit.  Returns true if there is no chunk and the guard's
+// release brought the instance's outstanding count to zero, i.e. the caller
+// must complete the limit itself.
 // `stage` (128 u64) and `stage_m` (64 u16) are LDS the caller does not use
 // while seeding (its LDS stack is empty whenever a limit is seeded).
-__device__ bool seed_limit(const BatchArgs& A, int i, uint64_t* stage, uint16_t* stage_m) {
+__device__ bool seed_limit(const BatchArgs& A, int i, int L, uint64_t* stage, uint16_t* stage_m, Unit& mine,
+                           RunStats& wc) {
   const int lane = lane_id();
   InstState* S = A.is + i;
-  const int L = S->limit;
-  const bool wide = S->width == 5;
-  if (lane == 0) __hip_atomic_store(&S->outstanding, 1, __ATOMIC_RELAXED, AGENT);
+  const int width = S->width;
+  const bool wide = width == 5;
+  if (lane == 0) st_relaxed(&S->outstanding, 1);
   const NodeW* roots = A.tree + S->root_off;
   // first-solution mode: a goal inside the split tree ends the search at
   // this limit without searching any subtree
   const int nroots = (A.first_solution && A.goal_g[i] <= L) ? 0 : S->nroots;
   int fm = INT_MAX;
   bool full = false;
+  mine.count = 0;
+  mine.inst = i;
+  mine.limit = L;
+  mine.width = width;
+  mine.kind = wide ? kChunkWide : kChunkNodes;
   for (int base = 0; base < nroots && !full; base += 64) {
     const int r = base + lane;
     NodeW R;
@@ -223,29 +286,26 @@ __device__ bool seed_limit(const BatchArgs& A, int i, uint64_t* stage, uint16_t*
     // per workgroup, so the whole grid has work from the start
     const int sc = A.seed_chunk > 0 ? A.seed_chunk : kQChunk;
     for (int p0 = 0; p0 < cnt && !full; p0 += sc) {
-      const int pc = min(sc, cnt - p0);
-      const uint64_t t = lane < pc ? stage[p0 + lane] : 0ull;
-      const uint64_t th = lane < pc ? stage[64 + p0 + lane] : 0ull;
-      const uint16_t m = lane < pc ? stage_m[p0 + lane] : (uint16_t)0;
-      if (lane == 0) __hip_atomic_fetch_add(&S->outstanding, 1, __ATOMIC_RELAXED, AGENT);
-      if (!q_push(A, t, th, m, pc, i, wide ? kChunkWide : kChunkNodes)) {
-        full = true;  // the remaining roots are dropped; the call reports BPIDA_ENOMEM
-        if (lane == 0) {
-          __hip_atomic_fetch_add(&S->outstanding, -1, __ATOMIC_RELAXED, AGENT);
-          __hip_atomic_store(&S->lost, 1, __ATOMIC_RELAXED, AGENT);
-          atomicOr(&A.q->err, 1);
-        }
+      if (mine.count) {
+        if (lane == 0) __hip_atomic_fetch_add(&S->outstanding, 1, __ATOMIC_RELAXED, AGENT);
+        full = !q_push(A, mine, wc);
       }
+      mine.count = min(sc, cnt - p0);
+      const bool on = lane < mine.count;
+      mine.tile = on ? stage[p0 + lane] : 0ull;
+      mine.hi = on ? stage[64 + p0 + lane] : 0ull;
+      mine.meta = on ? stage_m[p0 + lane] : (uint16_t)0;
     }
     WAVE_SYNC();
   }
+  if (full) drop_unit(A, i);  // the remaining roots are dropped; the call reports BPIDA_ENOMEM
   fm = wave_min(fm);
+  if (lane == 0 && fm != INT_MAX) __hip_atomic_fetch_min(&S->fmin, fm, __ATOMIC_RELAXED, AGENT);
+  wc.roots_read += (uint64_t)nroots;
+  if (mine.count) return false;
+  performed();
   int last = 0;
-  if (lane == 0) {
-    if (nroots) __hip_atomic_fetch_add(&A.q->roots_read, (uint64_t)nroots, __ATOMIC_RELAXED, AGENT);
-    if (fm != INT_MAX) __hip_atomic_fetch_min(&S->fmin, fm, __ATOMIC_RELAXED, AGENT);
-    last = __hip_atomic_fetch_add(&S->outstanding, -1, __ATOMIC_ACQ_REL, AGENT) == 1;
-  }
+  if (lane == 0) last = __hip_atomic_fetch_add(&S->outstanding, -1, __ATOMIC_RELAXED, AGENT) == 1;
   return wave_bcast(last) != 0;
 }
 
@@ -257,9 +317,10 @@ __device__ void emit_result(const BatchArgs& A, int i, int status) {
   WAVE_SYNC_MEM();  // the slot's output row, written by lane 0, is visible
   const uint64_t t = V.ticket[i];
   ServerRes* r = V.res + (t & V.ring_mask);
-  r->nodes[lane] = A.out_nodes[(size_t)i * 64 + lane];
+  // (columns of earlier limits may come from other waves)
+  r->nodes[lane] = ld_agent(&A.out_nodes[(size_t)i * 64 + lane]);
   if (lane == 0) {
-    r->len = A.out_len[i];
+    r->len = ld_agent(&A.out_len[i]);
     r->status = status;
   }
   WAVE_SYNC_MEM();
@@ -270,37 +331,44 @@ __device__ void emit_result(const BatchArgs& A, int i, int status) {
   }
 }
 
-// Completes the current limit of instance i (its outstanding count is zero
-// and this wave observed it), then advances it.  Loops while a new limit
-// has no queued work.
-__device__ void complete_limit(const BatchArgs& A, int i, uint64_t* stage, uint16_t* stage_m) {
+// Completes limit L of instance i (its outstanding count is zero and this
+// wave observed it), then advances it.  Loops while a new limit has no work;
+// the new limit's last chunk is left in `mine` (count 0: the instance is
+// done).
+__device__ void complete_limit(const BatchArgs& A, int i, int L, uint64_t* stage, uint16_t* stage_m, Unit& mine,
+                           RunStats& wc) {
   const int lane = lane_id();
   InstState* S = A.is + i;
+  mine.count = 0;
+  // the server's split trees and histograms are written while the kernel runs
+  if (A.server) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   for (;;) {
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    const int L = S->limit;
-    const int col = S->col;
+    const int col = ld_relaxed(&S->col), goals = ld_relaxed(&S->goals), lost = ld_relaxed(&S->lost);
+    const uint64_t searched = ld_relaxed(&S->nodes);
+    const int fsearch = ld_relaxed(&S->fmin);
+    const int goal_g = A.goal_g[i];
     // interior nodes of the split tree (depth < D) expanded at this limit
     const uint32_t* h = A.hist + (size_t)i * kHistBins;
-    uint64_t interior = 0;
+    uint32_t interior = 0;
     int fm = INT_MAX;
-    for (int f = lane; f < kHistBins; f += 64) {
-      const uint32_t c = h[f];
-      if (f <= L) interior += c;
-      else if (c) fm = min(fm, f);
+    uint32_t c[kHistBins / 64];
+    for (int k = 0; k < kHistBins / 64; ++k) c[k] = h[64 * k + lane];
+    for (int k = 0; k < kHistBins / 64; ++k) {
+      const int f = 64 * k + lane;
+      if (f <= L) interior += c[k];
+      else if (c[k]) fm = min(fm, f);
     }
     for (int o = 32; o > 0; o >>= 1) interior += __shfl_xor(interior, o, 64);
     fm = wave_min(fm);
     int state = 0;  // 0: advance, 1: solved, <0: error code
+    int left = 1;
     if (lane == 0) {
-      const uint64_t total = ld_relaxed(&S->nodes) + interior;
-      A.out_nodes[(size_t)i * 64 + col] = total;
-      const int goals = ld_relaxed(&S->goals);
-      const int fnext = min(fm, ld_relaxed(&S->fmin));
-      if (ld_relaxed(&S->lost)) {
+      st_relaxed(&A.out_nodes[(size_t)i * 64 + col], searched + interior);
+      const int fnext = min(fm, fsearch);
+      if (lost) {
         state = -4;  // BPIDA_ENOMEM: work of this limit was dropped, its counts are void
-      } else if (goals > 0 || A.goal_g[i] <= L) {
-        A.out_len[i] = L;
+      } else if (goals > 0 || goal_g <= L) {
+        st_relaxed(&A.out_len[i], L);
         state = 1;
       } else if (fnext != L + 2) {
         state = -6;  // BPIDA_EINTERNAL
@@ -310,23 +378,25 @@ __device__ void complete_limit(const BatchArgs& A, int i, uint64_t* stage, uint1
         state = -3;  // BPIDA_ELIMIT
       }
       if (state != 0) {
-        __hip_atomic_store(&S->done, state, __ATOMIC_RELAXED, AGENT);
-        if (!A.server) __hip_atomic_fetch_add(&A.q->remaining, -1, __ATOMIC_RELEASE, AGENT);
+        st_relaxed(&S->done, state);
+        if (!A.server) left = __hip_atomic_fetch_add(&A.q->remaining, -1, __ATOMIC_RELAXED, AGENT) - 1;
       } else {
-        S->limit = L + 2;
-        S->col = col + 1;
-        __hip_atomic_store(&S->nodes, (uint64_t)0, __ATOMIC_RELAXED, AGENT);
-        __hip_atomic_store(&S->fmin, INT_MAX, __ATOMIC_RELAXED, AGENT);
-        __hip_atomic_store(&S->goals, 0, __ATOMIC_RELAXED, AGENT);
+        st_relaxed(&S->limit, L + 2);
+        st_relaxed(&S->col, col + 1);
+        st_relaxed(&S->nodes, (uint64_t)0);
+        st_relaxed(&S->fmin, INT_MAX);
+        st_relaxed(&S->goals, 0);
       }
     }
     state = wave_bcast(state);
     if (state != 0) {
+      performed();
       if (A.server) emit_result(A, i, state);
+      else if (wave_bcast(left) == 0) end_search(A);
       return;
     }
-    WAVE_SYNC_MEM();
-    if (!seed_limit(A, i, stage, stage_m)) return;
+    L += 2;
+    if (!seed_limit(A, i, L, stage, stage_m, mine, wc)) return;
   }
 }
 
@@ -443,6 +513,27 @@ __device__ int64_t wave_split4(const Inst& I, int depth, const int32_t* walks, N
   return lvl;
 }
 
+// Seeds a request's first limit with every chunk in the queue: the admitter
+// searches nothing itself.
+__device__ void admit_limit(const BatchArgs& A, int i, int L, uint64_t* st, uint16_t* sm) {
+  Unit mine;
+  RunStats wc = {};  // (the admitter's own counts are not reported)
+  if (seed_limit(A, i, L, st, sm, mine, wc)) complete_limit(A, i, L, st, sm, mine, wc);
+  while (mine.count && !q_push(A, mine, wc)) {
+    // lost: this was the instance's last unit unless other chunks are out
+    int last = 0;
+    if (lane_id() == 0) {
+      st_relaxed(&A.is[i].lost, 1);
+      atomicOr(&A.q->err, 1);
+      performed();
+      last = __hip_atomic_fetch_add(&A.is[i].outstanding, -1, __ATOMIC_RELAXED, AGENT) == 1;
+    }
+    L = mine.limit;
+    mine.count = 0;
+    if (wave_bcast(last)) complete_limit(A, i, L, st, sm, mine, wc);
+  }
+}
+
 // Admits requests until the host asks to stop and nothing is in flight.
 __device__ void admitter_loop(const BatchArgs& A, uint64_t* st, uint16_t* sm, uint64_t deadline) {
   const int lane = lane_id();
@@ -473,7 +564,9 @@ __device__ void admitter_loop(const BatchArgs& A, uint64_t* st, uint16_t* sm, ui
         int inflight = 0;
         if (lane == 0) inflight = __hip_atomic_load(V.in_flight, __ATOMIC_ACQUIRE, AGENT);
         if (wave_bcast(inflight) == 0) {
-          if (lane == 0) __hip_atomic_store(&q->remaining, 0, __ATOMIC_RELEASE, AGENT);
+          if (lane == 0) st_relaxed(&q->remaining, 0);
+          performed();
+          end_search(A);
           return;
         }
       }
@@ -544,34 +637,39 @@ __device__ void admitter_loop(const BatchArgs& A, uint64_t* st, uint16_t* sm, ui
     WAVE_SYNC_MEM();
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     if (S.done != 0) emit_result(A, slot, S.done);
-    else if (seed_limit(A, slot, st, sm)) complete_limit(A, slot, st, sm);
+    else admit_limit(A, slot, S.limit, st, sm);
     ++head;
   }
 }
 
-// Adds this workgroup's counts for the unit of instance i it held and
-// releases the unit; completes the limit if it was the last unit.
-__device__ void release_unit(const BatchArgs& A, int i, uint64_t expanded, int goals, int fmin,
-                             uint64_t* stage, uint16_t* stage_m) {
+// Adds this wave's counts for the unit of instance i it held at limit L and
+// releases the unit; completes the limit if it was the last unit, which may
+// leave the next limit's chunk in `mine`.
+__device__ void release_unit(const BatchArgs& A, int i, int L, uint64_t expanded, int goals, int fmin,
+                             uint64_t* stage, uint16_t* stage_m, Unit& mine,
+                           RunStats& wc) {
   const int lane = lane_id();
   InstState* S = A.is + i;
+  mine.count = 0;
   fmin = wave_min(fmin);
-  int last = 0;
   if (lane == 0) {
     if (expanded) __hip_atomic_fetch_add(&S->nodes, expanded, __ATOMIC_RELAXED, AGENT);
     if (goals) __hip_atomic_fetch_add(&S->goals, goals, __ATOMIC_RELAXED, AGENT);
     if (fmin != INT_MAX) __hip_atomic_fetch_min(&S->fmin, fmin, __ATOMIC_RELAXED, AGENT);
-    last = __hip_atomic_fetch_add(&S->outstanding, -1, __ATOMIC_ACQ_REL, AGENT) == 1;
   }
-  if (wave_bcast(last)) complete_limit(A, i, stage, stage_m);
+  performed();  // the counts are in before the unit is gone
+  int last = 0;
+  if (lane == 0) last = __hip_atomic_fetch_add(&S->outstanding, -1, __ATOMIC_RELAXED, AGENT) == 1;
+  if (wave_bcast(last)) complete_limit(A, i, L, stage, stage_m, mine, wc);
 }
 
 // ---------------------------------------------------------------------------
 // The persistent kernel.
 // ---------------------------------------------------------------------------
-// Per-workgroup run counters.
-struct WgCounters {
-  uint64_t rounds = 0, pushes = 0, voluntary = 0;
+// A wave's clock in rounds, over all its units.
+struct RoundClock {
+  uint32_t tick = 0;       // rounds started
+  uint32_t next_look = 0;  // the tick of the next look for waiting waves
 };
 
 // The LDS stack of one wave while it searches a unit: entries [0, top), the
@@ -589,7 +687,6 @@ struct NodeStack {
   // may have 4, and a root is expanded in the unit's first round, which
   // starts from one chunk (at most 64 entries) and so cannot overflow.
   static constexpr int kGrow = NPL == 16 ? 32 : 2 * 64;
-  static constexpr int kKind = W == 5 ? kChunkWide : kChunkNodes;
   struct Entry {
     S s;
     uint16_t m;
@@ -606,8 +703,14 @@ struct NodeStack {
     st[i] = e.s;
     sm[i] = e.m;
   }
-  __device__ __forceinline__ bool push(const BatchArgs& A, Entry e, int count, int inst) const {
-    return q_push(A, (uint64_t)e.s, W == 5 ? (uint64_t)((unsigned __int128)e.s >> 64) : 0ull, e.m, count, inst, kKind);
+  // (u: the unit's instance and limit)
+  __device__ __forceinline__ bool push(const BatchArgs& A, Unit u, Entry e, int count, RunStats& wc) const {
+    u.tile = (uint64_t)e.s;
+    u.hi = W == 5 ? (uint64_t)((unsigned __int128)e.s >> 64) : 0ull;
+    u.meta = e.m;
+    u.kind = W == 5 ? kChunkWide : kChunkNodes;
+    u.count = count;
+    return q_push(A, u, wc);
   }
   __device__ __forceinline__ uint32_t round(uint32_t top, int kp, int& goals, int& fmin) {
     if constexpr (NPL == 16) return bp_round<CAP>(st, sm, top, kp, limit, M, goals, fmin);
@@ -633,8 +736,12 @@ struct RingStack {
       : st((Entry*)lds), k(make_ring_consts<W>((char*)lds, kTable)) {}
   __device__ __forceinline__ Entry get(uint32_t i) const { return st[i]; }
   __device__ __forceinline__ void put(uint32_t i, Entry e) { st[i] = e; }
-  __device__ __forceinline__ bool push(const BatchArgs& A, Entry e, int count, int inst) const {
-    return q_push(A, (uint64_t)e.r | ((uint64_t)e.c << 32), 0ull, (uint16_t)ring_pack(e.m), count, inst, kChunkRing);
+  __device__ __forceinline__ bool push(const BatchArgs& A, Unit u, Entry e, int count, RunStats& wc) const {
+    u.tile = (uint64_t)e.r | ((uint64_t)e.c << 32);
+    u.meta = (uint16_t)ring_pack(e.m);
+    u.kind = kChunkRing;
+    u.count = count;
+    return q_push(A, u, wc);
   }
   __device__ __forceinline__ uint32_t round(uint32_t top, int kp, int& goals, int&) {
     uint64_t gm = 0;
@@ -648,20 +755,22 @@ struct RingStack {
 
   // Loads a chunk: entries that are under way as they are; nodes are expanded
   // here (counted, tested for the goal, and stored if they keep a move).
-  __device__ __forceinline__ uint32_t load(uint64_t t, uint16_t meta, int cnt, int kind, uint64_t& expanded, int& goals) {
+  __device__ __forceinline__ uint32_t load(const Unit& u, uint64_t& expanded, int& goals) {
     const uint32_t lane = (uint32_t)lane_id();
-    uint32_t top = (uint32_t)cnt;
-    if (kind == kChunkRing) {
+    const uint64_t t = u.tile;
+    const uint32_t meta = u.meta;
+    uint32_t top = (uint32_t)u.count;
+    if (u.kind == kChunkRing) {
       if (lane < top) put(lane, {(uint32_t)t, (uint32_t)(t >> 32), ring_unpack(meta)});
     } else {
       uint32_t r, c, b;
       ring_planes<W>(t, meta & 15u, &r, &c, &b);
       const uint32_t fb = (meta >> 5) & 7u;
       const uint32_t undo = fb == 0 ? kRingU : fb == 1 ? kRingL : fb == 2 ? kRingR : fb == 3 ? kRingD : 0u;
-      const uint32_t base = (b << 3) | ((uint32_t)(meta >> 9) * kRingSlack1);
+      const uint32_t base = (b << 3) | ((meta >> 9) * kRingSlack1);
       const uint32_t near = ring_nearer(r, c, ring_compare<W>(b));
       const uint32_t m = ring_meta(base, near, ring_legal<W>(b), undo);
-      expanded += (uint64_t)cnt;
+      expanded += (uint64_t)top;
       goals += __popcll(__builtin_amdgcn_ballot_w64(lane < top && t == (uint64_t)Board<W>::goal()));
       const uint64_t km = __builtin_amdgcn_ballot_w64(lane < top && m > kRingBase);
       const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(km >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)km, 0u));
@@ -690,17 +799,18 @@ __device__ __forceinline__ void stack_down(ST& S, uint32_t dst, uint32_t src, ui
 // overflow and donations to waiting workgroups.  Returns false if the time
 // budget ran out (abandoned).
 template <class ST, bool FS>
-__device__ bool run_unit(const BatchArgs& A, int inst, int limit, ST& S, uint32_t top, WgCounters& wc, uint32_t& tick,
+__device__ bool run_unit(const BatchArgs& A, const Unit& u, ST& S, uint32_t top, RunStats& wc, RoundClock& clk,
                          uint64_t deadline, uint64_t& expanded, int& goals, int& fmin) {
   using Entry = typename ST::Entry;
   constexpr int kCap = ST::kCap, kNpl = ST::kNpl, kGrow = ST::kGrow;
-  const int lane = lane_id();
+  const int lane = lane_id(), inst = u.inst;
   QueueCtl* q = A.q;
-  // Donating from a shallow stack hands over pieces too small to pay for the
-  // transfer; a threshold the stack seldom reaches stops donation and leaves
-  // subtrees on one workgroup.  Default: four rounds' worth of pops, at most
-  // half the stack.
-  const int dmin = A.donate_min > 0 ? A.donate_min : min(4 * kNpl, kCap / 2);
+  constexpr uint32_t kLookMin = 32;  // rounds
+  const int waves = (int)(gridDim.x * (blockDim.x >> 6));
+  const float look_share = 4.0f * (float)(A.donate_mask + 1u) / (float)waves;
+  const int dhigh = A.donate_min > 0 ? A.donate_min : min(4 * kNpl, kCap / 2);
+  const int dlow = min(dhigh, A.donate_min > 0 ? A.donate_min : 2 * kNpl);
+  uint32_t tick = clk.tick;
   // Entries taken from the bottom (spills, donations) make the rest move
   // down, so a position never wraps and a round addresses the stack without
   // a mask.
@@ -708,40 +818,52 @@ __device__ bool run_unit(const BatchArgs& A, int inst, int limit, ST& S, uint32_
     if (goals > 0 && lane == 0) __hip_atomic_store(&A.is[inst].stop, 1, __ATOMIC_RELAXED, AGENT);
     if (goals > 0 || wave_bcast(lane == 0 ? ld_relaxed(&A.is[inst].stop) : 0)) top = 0;
   }
-  // The deadline, donation and first-solution polls come every
-  // min(64, donate_every) rounds, a period that divides each of theirs; the
-  // rounds in between test only whether the next round needs a spill.
-  const uint32_t poll_mask = min(A.donate_mask, 63u);
   while (top != 0) {
     int avail = (int)top;
     ++tick;
-    const bool poll = (tick & poll_mask) == 0;
-    if (poll) {
-      if ((tick & 1023u) == 0) {
-        // the time budget is spent, or work was dropped somewhere (every
-        // count is void and the call reports BPIDA_ENOMEM): stop instead of
-        // searching on
-        const bool late = wall_clock64() > deadline;
-        if (late || (!A.server && (ld_wave(&q->err) & kErrFatal))) {
-          if (late && lane == 0) atomicOr(&q->err, 8);
-          return false;
-        }
+    const bool poll = (tick & 63u) == 0;
+    if ((tick & 1023u) == 0) {
+      // the time budget is spent, or work was dropped somewhere (every
+      // count is void and the call reports BPIDA_ENOMEM): stop instead of
+      // searching on
+      const bool late = wall_clock64() > deadline;
+      if (late || (!A.server && (ld_wave(&q->err) & kErrFatal))) {
+        if (late && lane == 0) atomicOr(&q->err, 8);
+        return false;
       }
-      if (avail + kGrow <= kCap && avail >= dmin && (tick & A.donate_mask) == 0) {
-        // donation when workgroups wait on tickets no queued chunk covers:
-        // the oldest min(window, avail) entries (the shallowest, largest
-        // subtrees) are split alternately, so donor and receiver each keep
-        // about half
-        int want = 0;
-        if (lane == 0) want = (int64_t)(ld_relaxed(&q->head) - ld_relaxed(&q->tail)) > 0;
-        if (wave_bcast(want)) {
+    }
+    if ((int32_t)(tick - clk.next_look) >= 0 && avail + kGrow <= kCap) {
+      // Donation when workgroups wait on tickets no queued chunk covers: the
+      // oldest min(window, avail) entries (the shallowest, largest subtrees)
+      // are split alternately, so donor and receiver each keep about half.
+      //
+      // A look reads head and tail, which every push and take advances: all
+      // waves together can afford a few dozen looks a microsecond.  So the
+      // period is 4 * donate_every rounds while every wave searches (100 hard
+      // 4x4 states: 25.5 ms with 512 rounds, 28.7 ms with 128, 44 ms with
+      // 64), and shrinks with the share of waves that search, down to 32
+      // rounds when few do (one hard 4x4 state: 3.1 ms at a fixed 512, 1.4 ms).
+      // Donating from a shallow stack hands over pieces too small to pay for
+      // the transfer, and a threshold the stack seldom reaches leaves subtrees
+      // on one workgroup: four rounds' worth of pops, at most half the stack,
+      // but two while more waves wait than search (64 easy states: 1.37 ms
+      // with four throughout, 0.78 ms with two, 0.97 ms with one).
+      if (avail < dlow) {
+        clk.next_look = tick + kLookMin;
+      } else {
+        int64_t ht = 0;
+        if (lane == 0) ht = (int64_t)(ld_relaxed(&q->head) - ld_relaxed(&q->tail));
+        const int wait = min(max(wave_bcast((int)ht), 0), waves);
+        clk.next_look = tick + (uint32_t)max((int)kLookMin, (int)((float)(waves - wait) * look_share));
+        const int dmin = wait > waves - wait ? dlow : dhigh;
+        if (wait > 0 && avail >= dmin) {
           const int w = min(avail, A.donate_window) & ~1;
           const int h = w >> 1;
           // (positions up to 127: inside the stack's storage, read for every lane)
           const Entry give = S.get(2 * lane), keep = S.get(2 * lane + 1);
           WAVE_SYNC();
           if (lane == 0) __hip_atomic_fetch_add(&A.is[inst].outstanding, 1, __ATOMIC_RELAXED, AGENT);
-          if (S.push(A, give, h, inst)) {
+          if (S.push(A, u, give, h, wc)) {
             wc.pushes += 1;
             wc.voluntary += 1;
             // the kept half becomes the bottom, the entries above the window
@@ -764,7 +886,7 @@ __device__ bool run_unit(const BatchArgs& A, int inst, int limit, ST& S, uint32_
         const Entry e = S.get(lane);
         WAVE_SYNC();
         if (lane == 0) __hip_atomic_fetch_add(&A.is[inst].outstanding, 1, __ATOMIC_RELAXED, AGENT);
-        if (S.push(A, e, 64, inst)) {
+        if (S.push(A, u, e, 64, wc)) {
           wc.pushes += 1;
         } else if (lane == 0) {
           __hip_atomic_fetch_add(&A.is[inst].outstanding, -1, __ATOMIC_RELAXED, AGENT);
@@ -791,7 +913,7 @@ __device__ bool run_unit(const BatchArgs& A, int inst, int limit, ST& S, uint32_
         if (lane == 0) __hip_atomic_store(&A.is[inst].stop, 1, __ATOMIC_RELAXED, AGENT);
         break;
       }
-      if (poll && (tick & 63u) == 0 && wave_bcast(lane == 0 ? ld_relaxed(&A.is[inst].stop) : 0))
+      if (poll && wave_bcast(lane == 0 ? ld_relaxed(&A.is[inst].stop) : 0))
         break;
     }
     if constexpr (kNpl == 64) {
@@ -802,7 +924,7 @@ __device__ bool run_unit(const BatchArgs& A, int inst, int limit, ST& S, uint32_
       // first-solution search also leaves after a round that expanded a goal
       // (a test of the wave's goal mask, uniform), and stops its instance
       // outside the loop.
-      const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)(poll_mask - (tick & poll_mask)));
+      const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane(max(min((int)(63u - (tick & 63u)), (int)(clk.next_look - tick) - 1), 0));
       uint32_t r = 0;
       uint64_t gm = 0;  // lanes that expanded a goal (only "any" matters)
       for (;;) {
@@ -830,7 +952,8 @@ __device__ bool run_unit(const BatchArgs& A, int inst, int limit, ST& S, uint32_
   // and every limit below the optimum prunes one: below the optimum, a path
   // of approaching moves from a slack-0 node cannot reach the goal, so it
   // ends at a node whose remaining moves all go away and are pruned
-  if (kNpl == 64) fmin = limit + 2;
+  if (kNpl == 64) fmin = u.limit + 2;
+  clk.tick = tick;
   return true;
 }
 
@@ -872,127 +995,159 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
     if (lane == 0) role = atomicCAS(A.srv.admitter, 0, 1) == 0;
     if (wave_bcast(role)) {
       admitter_loop(A, st, sm, wall_clock64() + A.budget_ticks);
+      if (lane == 0) A.wave_stats[blockIdx.x * WPG + (WPG == 1 ? 0 : threadIdx.x >> 6)] = RunStats{};
       return;
     }
   }
 
+  Unit u;  // the chunk to search next (count 0: none)
+  RunStats wc = {};
+
   // Seed the first limit of every instance through a shared cursor: all
   // instances are seeded by workgroups that are running, whatever part of
-  // the grid is resident.
+  // the grid is resident.  A wave searches the last chunk it seeded itself.
+  // The cursor is read before it is advanced: thousands of waves that
+  // advance it past the end hold up the few that search.
   for (;;) {
-    int i = 0;
-    if (lane == 0) i = __hip_atomic_fetch_add(&q->seed_next, 1, __ATOMIC_RELAXED, AGENT);
+    int i = A.n;
+    if (lane == 0 && ld_relaxed(&q->seed_next) < A.n)
+      i = __hip_atomic_fetch_add(&q->seed_next, 1, __ATOMIC_RELAXED, AGENT);
     i = wave_bcast(i);
     if (i >= A.n) break;
     if (ld_wave(&q->err) & kErrFatal) break;  // work already lost: stop seeding
     if (A.is[i].done != 0) continue;
-    if (seed_limit(A, i, st, sm)) complete_limit(A, i, st, sm);
+    if (u.count && !q_push(A, u, wc)) drop_unit(A, u.inst);
+    const int L = A.is[i].limit;
+    if (seed_limit(A, i, L, st, sm, u, wc)) complete_limit(A, i, L, st, sm, u, wc);
   }
 
-  WgCounters wc;
-  uint64_t searched = 0, pops = 0;
-  uint64_t t_work = 0, t_queue = 0, t_idle = 0;
   uint64_t t_mark = wall_clock64();
   bool idle = false;
   uint64_t idle_since = 0, idle_act = 0;
-  uint32_t tick = 0;
-  int backoff = 1;
+  RoundClock clk;
+  uint32_t polls = 0;
   uint64_t ticket = kNoTicket;  // consumer ticket held while idle
   const uint64_t deadline = wall_clock64() + A.budget_ticks;
 
   for (;;) {
-    uint64_t t, th;
-    uint16_t m;
-    int cnt, inst, kind;
-    if (!q_take(A, ticket, t, th, m, cnt, inst, kind)) {
-      if (ld_wave(&q->remaining) <= 0) break;
-      if (!A.server && (ld_wave(&q->err) & kErrFatal)) break;
-      const uint64_t now = wall_clock64();
-      // queue activity seen by this idle workgroup (lane 0's view)
-      uint64_t act = 0;
-      if (lane == 0) act = ld_relaxed(&q->head) + ld_relaxed(&q->tail);
-      act = (uint64_t)(uint32_t)wave_bcast((int)(uint32_t)act);
-      if (!idle) {
-        idle = true;
-        idle_since = now;
-        idle_act = act;
-        backoff = 1;
-      } else if (act != idle_act) {
-        idle_since = now;  // the queue moved: work is being shared
-        idle_act = act;
-      } else if (now - idle_since > A.idle_ticks || now > deadline) {
-        // no queue activity for the whole watchdog period although
-        // instances remain, or the run's time budget is spent
-        if (lane == 0) atomicOr(&q->err, now > deadline ? 8 : 4);
-        break;
+    if (u.count == 0) {
+      const int got = q_take(A, ticket, u, wc);
+      if (got < 0) break;
+      if (got == 0) {
+        // Wait.  The ticket's own slot is all that is polled, with longer
+        // sleeps up to 2048 clocks; the shared words (end of the search,
+        // lost work, queue activity) are read every 32nd time only: thousands
+        // of waiting waves that read them on every poll held up the searching
+        // waves' looks at head and tail by some 25 us each.
+        if (!idle) {
+          idle = true;
+          polls = 0;
+          idle_since = 0;
+        }
+        if ((++polls & 31u) == 0) {
+          if (ld_wave(&q->remaining) <= 0) break;
+          if (!A.server && (ld_wave(&q->err) & kErrFatal)) break;
+          const uint64_t now = wall_clock64();
+          // queue activity seen by this idle workgroup (lane 0's view)
+          uint64_t act = 0;
+          if (lane == 0) act = ld_relaxed(&q->head) + ld_relaxed(&q->tail);
+          act = (uint64_t)(uint32_t)wave_bcast((int)(uint32_t)act);
+          if (idle_since == 0 || act != idle_act) {
+            idle_since = now;  // the queue moved: work is being shared
+            idle_act = act;
+          } else if (now - idle_since > A.idle_ticks || now > deadline) {
+            // no queue activity for the whole watchdog period although
+            // instances remain, or the run's time budget is spent
+            if (lane == 0) atomicOr(&q->err, now > deadline ? 8 : 4);
+            break;
+          }
+          wc.t_idle += now - t_mark;
+          t_mark = now;
+        }
+        if (polls < 8) __builtin_amdgcn_s_sleep(4);
+        else __builtin_amdgcn_s_sleep(32);
+        continue;
       }
-      // exponential backoff (1 .. 8 x 4096 clocks) keeps idle workgroups
-      // from flooding the queue's cache lines
-      for (int k = 0; k < backoff; ++k) __builtin_amdgcn_s_sleep(64);
-      backoff = min(backoff * 2, 8);
-      const uint64_t now2 = wall_clock64();
-      t_idle += now2 - t_mark;
-      t_mark = now2;
-      continue;
+      wc.pops += 1;
     }
     idle = false;
-    backoff = 1;
-    pops += 1;
     {
       const uint64_t now = wall_clock64();
-      t_queue += now - t_mark;
+      wc.t_queue += now - t_mark;
       t_mark = now;
     }
-    const int limit = A.is[inst].limit;
-    const int width = A.is[inst].width;
     uint64_t expanded = 0;
     int goals = 0, fmin = INT_MAX;
     bool ok = true;
-    if (width == 5) {
+    if (u.width == 5) {
       // (smaller stacks take no 5x5 batch: the host refuses it)
       if constexpr (CAP / 2 >= 512) {
-        NodeStack<5, CAP / 2, 64> S(st, limit);
-        if (lane < cnt) S.put(lane, {(unsigned __int128)t | ((unsigned __int128)th << 64), m});
+        NodeStack<5, CAP / 2, 64> S(st, u.limit);
+        if (lane < u.count) S.put(lane, {(unsigned __int128)u.tile | ((unsigned __int128)u.hi << 64), u.meta});
         WAVE_SYNC();
-        ok = run_unit<NodeStack<5, CAP / 2, 64>, FS>(A, inst, limit, S, (uint32_t)cnt, wc, tick, deadline, expanded,
+        ok = run_unit<NodeStack<5, CAP / 2, 64>, FS>(A, u, S, (uint32_t)u.count, wc, clk, deadline, expanded,
                                                      goals, fmin);
       }
-    } else if (width == 3) {
+    } else if (u.width == 3) {
       if constexpr (CAP >= 256) {
         RingStack<3, ring_cap<CAP>()> S(st);
-        const uint32_t top = S.load(t, m, cnt, kind, expanded, goals);
-        ok = run_unit<RingStack<3, ring_cap<CAP>()>, FS>(A, inst, limit, S, top, wc, tick, deadline, expanded, goals,
+        const uint32_t top = S.load(u, expanded, goals);
+        ok = run_unit<RingStack<3, ring_cap<CAP>()>, FS>(A, u, S, top, wc, clk, deadline, expanded, goals,
                                                          fmin);
       }
     } else if constexpr (NPL == 64) {
       RingStack<4, ring_cap<CAP>()> S(st);
-      const uint32_t top = S.load(t, m, cnt, kind, expanded, goals);
-      ok = run_unit<RingStack<4, ring_cap<CAP>()>, FS>(A, inst, limit, S, top, wc, tick, deadline, expanded, goals,
+      const uint32_t top = S.load(u, expanded, goals);
+      ok = run_unit<RingStack<4, ring_cap<CAP>()>, FS>(A, u, S, top, wc, clk, deadline, expanded, goals,
                                                        fmin);
     } else {
-      NodeStack<4, CAP, NPL> S(st, limit);
-      if (lane < cnt) S.put(lane, {t, m});
+      NodeStack<4, CAP, NPL> S(st, u.limit);
+      if (lane < u.count) S.put(lane, {u.tile, u.meta});
       WAVE_SYNC();
-      ok = run_unit<NodeStack<4, CAP, NPL>, FS>(A, inst, limit, S, (uint32_t)cnt, wc, tick, deadline, expanded, goals,
+      ok = run_unit<NodeStack<4, CAP, NPL>, FS>(A, u, S, (uint32_t)u.count, wc, clk, deadline, expanded, goals,
                                                 fmin);
     }
     if (!ok) break;
     const uint64_t now = wall_clock64();
-    t_work += now - t_mark;
+    wc.t_work += now - t_mark;
     t_mark = now;
-    release_unit(A, inst, expanded, goals, fmin, st, sm);
-    searched += expanded;
+    wc.searched += expanded;
+    release_unit(A, u.inst, u.limit, expanded, goals, fmin, st, sm, u, wc);
   }
-  if (lane == 0) {
-    atomicAdd((unsigned long long*)&q->rounds, (unsigned long long)wc.rounds);
-    atomicAdd((unsigned long long*)&q->searched, (unsigned long long)searched);
-    atomicAdd((unsigned long long*)&q->pushes, (unsigned long long)wc.pushes);
-    atomicAdd((unsigned long long*)&q->pops, (unsigned long long)pops);
-    atomicAdd((unsigned long long*)&q->t_work, (unsigned long long)t_work);
-    atomicAdd((unsigned long long*)&q->t_queue, (unsigned long long)t_queue);
-    atomicAdd((unsigned long long*)&q->t_idle, (unsigned long long)t_idle);
-    atomicAdd((unsigned long long*)&q->voluntary, (unsigned long long)wc.voluntary);
+  if (lane == 0) A.wave_stats[blockIdx.x * WPG + (WPG == 1 ? 0 : threadIdx.x >> 6)] = wc;
+}
+
+// One workgroup: the waves' counters into q->stats.
+constexpr int kStatsThreads = 1024;
+__global__ __launch_bounds__(kStatsThreads) void run_stats_kernel(const RunStats* __restrict__ w, int waves,
+                                                                  QueueCtl* __restrict__ q) {
+  __shared__ uint64_t part[kStatsThreads / 64][kRunStats];
+  constexpr int kMax = offsetof(RunStats, qmax) / 8;  // the one that is a maximum
+  uint64_t sum[kRunStats] = {};
+  for (int i = threadIdx.x; i < waves; i += kStatsThreads)
+    for (int k = 0; k < kRunStats; ++k) {
+      const uint64_t v = ((const uint64_t*)(w + i))[k];
+      sum[k] = k == kMax ? max(sum[k], v) : sum[k] + v;
+    }
+  for (int k = 0; k < kRunStats; ++k) {
+    for (int o = 32; o > 0; o >>= 1) {
+      const uint64_t v = __shfl_xor(sum[k], o, 64);
+      sum[k] = k == kMax ? max(sum[k], v) : sum[k] + v;
+    }
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][k] = sum[k];
   }
+  __syncthreads();
+  if (threadIdx.x < kRunStats) {
+    const int k = threadIdx.x;
+    uint64_t s = 0;
+    for (int j = 0; j < kStatsThreads / 64; ++j) s = k == kMax ? max(s, part[j][k]) : s + part[j][k];
+    ((uint64_t*)&q->stats)[k] = s;
+  }
+}
+
+hipError_t launch_run_stats(const RunStats* d_wave_stats, int waves, QueueCtl* d_q, hipStream_t s) {
+  hipLaunchKernelGGL(run_stats_kernel, dim3(1), dim3(kStatsThreads), 0, s, d_wave_stats, waves, d_q);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------

@@ -92,7 +92,7 @@ struct Workspace {
   bool arch_ok = false;
   uint64_t qcap = 0;  // queue slots of the last batched launch
   DevBuf inst, tree, tree_off, hist, goal_g, err, cursor, part, spill_t, spill_m, res, stop;
-  DevBuf qctl, qseq, qslots, qhi, istate, root_off, nroots, status;
+  DevBuf qctl, qseq, qslots, qhi, istate, root_off, nroots, status, wave_stats;
   // non-backtracking walk counts per width (3, 4, 5), start cell and length:
   // the device table (d_walks) and its host copy
   const int32_t* d_walks = nullptr;
@@ -408,6 +408,7 @@ struct BatchBufs {
   QChunk* qslots = nullptr;
   uint64_t* qhi = nullptr;  // 5x5 high words (any5 only)
   InstState* istate = nullptr;
+  RunStats* wave_stats = nullptr;
   int32_t* widths = nullptr;    // mixed widths only
   int64_t* byte_off = nullptr;  // mixed widths only
   int64_t* tree_offw = nullptr; // mixed widths only
@@ -491,6 +492,7 @@ size_t carve_batched(uintptr_t base, const BatchPlan& P, BatchBufs* B) {
   B->qslots = (QChunk*)take(sizeof(QChunk) * P.qcap);
   B->qhi = P.any5 ? (uint64_t*)take(sizeof(uint64_t) * kQChunk * P.qcap) : nullptr;
   B->istate = (InstState*)take(sizeof(InstState) * n);
+  B->wave_stats = (RunStats*)take(sizeof(RunStats) * (size_t)(P.grid * P.wpg));
   if (!P.toff.empty()) {
     B->widths = (int32_t*)take(sizeof(int32_t) * n);
     B->byte_off = (int64_t*)take(sizeof(int64_t) * n);
@@ -513,7 +515,8 @@ int alloc_batched(const BatchPlan& P, BatchBufs* B) {
       W.qseq.ensure(sizeof(SlotCtl) * P.qcap) != hipSuccess ||
       W.qslots.ensure(sizeof(QChunk) * P.qcap) != hipSuccess ||
       (P.any5 && W.qhi.ensure(sizeof(uint64_t) * kQChunk * P.qcap) != hipSuccess) ||
-      W.istate.ensure(sizeof(InstState) * n) != hipSuccess)
+      W.istate.ensure(sizeof(InstState) * n) != hipSuccess ||
+      W.wave_stats.ensure(sizeof(RunStats) * (size_t)(P.grid * P.wpg)) != hipSuccess)
     return g_no_alloc ? BPIDA_EINVAL : BPIDA_ENOMEM;
   if (!P.toff.empty() &&
       (W.widths.ensure(sizeof(int32_t) * n) != hipSuccess ||
@@ -532,6 +535,7 @@ int alloc_batched(const BatchPlan& P, BatchBufs* B) {
   B->qslots = W.qslots.as<QChunk>();
   B->qhi = P.any5 ? W.qhi.as<uint64_t>() : nullptr;
   B->istate = W.istate.as<InstState>();
+  B->wave_stats = W.wave_stats.as<RunStats>();
   if (!P.toff.empty()) {
     B->widths = W.widths.as<int32_t>();
     B->byte_off = W.byte_off.as<int64_t>();
@@ -587,6 +591,7 @@ int enqueue_batched_into(const uint8_t* d_states, int32_t* d_len, uint64_t* d_no
   A.goal_g = B.goal_g;
   A.out_len = d_len;
   A.out_nodes = d_nodes;
+  A.wave_stats = B.wave_stats;
   A.n = n;
   A.server = 0;
   A.max_limit = (int)(O.max_threshold >= 0 ? std::min<int64_t>(O.max_threshold, kMaxLimit) : kMaxLimit);
@@ -605,6 +610,8 @@ int enqueue_batched_into(const uint8_t* d_states, int32_t* d_len, uint64_t* d_no
   HIPCHK(launch_batch4(P.cap, P.npl, P.wpg, (int)P.grid, A, st));
   if (ev1) HIPCHK(hipEventRecord(ev1, st));
   HIPCHK(launch_batch_status(A.is, n, A.q, B.err, d_status, st));
+  // (counters are read by the synchronous calls only, which are the timed ones)
+  if (ev1) HIPCHK(launch_run_stats(B.wave_stats, (int)(P.grid * P.wpg), A.q, st));
   return BPIDA_OK;
 #undef HIPCHK
 }
@@ -658,22 +665,22 @@ int run_batched(const uint8_t* d_states, int n, int32_t* d_len, uint64_t* d_node
   HIPCHK(hipStreamSynchronize(st));
   float ms = 0.f;
   if (hipEventElapsedTime(&ms, W.ev0, W.ev1) == hipSuccess) stats[4] = (uint64_t)(ms * 1000.0f);
-  stats[0] = qc.rounds;
-  stats[1] = qc.searched;
-  stats[2] = qc.pushes * kQChunk;
+  stats[0] = qc.stats.rounds;
+  stats[1] = qc.stats.searched;
+  stats[2] = qc.stats.pushes * kQChunk;
   stats[3] = 1;
-  stats[6] = qc.pushes;
-  stats[7] = qc.pops;
-  stats[8] = qc.t_work / (uint64_t)std::max(1, W.wall_khz / 1000);  // microseconds
-  stats[9] = qc.t_queue / (uint64_t)std::max(1, W.wall_khz / 1000);
-  stats[10] = qc.t_idle / (uint64_t)std::max(1, W.wall_khz / 1000);
-  stats[11] = qc.voluntary;
-  stats[5] = qc.qmax;
+  stats[6] = qc.stats.pushes;
+  stats[7] = qc.stats.pops;
+  stats[8] = qc.stats.t_work / (uint64_t)std::max(1, W.wall_khz / 1000);  // microseconds
+  stats[9] = qc.stats.t_queue / (uint64_t)std::max(1, W.wall_khz / 1000);
+  stats[10] = qc.stats.t_idle / (uint64_t)std::max(1, W.wall_khz / 1000);
+  stats[11] = qc.stats.voluntary;
+  stats[5] = qc.stats.qmax;
   stats[12] = (uint64_t)grid;
   stats[13] = (uint64_t)(uint32_t)qc.err | ((uint64_t)(split_err != 0) << 8);
   stats[14] = W.qcap;
-  stats[16] = qc.roots_read;
-  stats[17] = qc.chunks_read_wide;
+  stats[16] = qc.stats.roots_read;
+  stats[17] = qc.stats.chunks_read_wide;
   memcpy(g_stats, stats, sizeof stats);
   int rc = BPIDA_OK;
   for (int i = 0; i < n && rc == BPIDA_OK; ++i)
@@ -947,7 +954,7 @@ struct Server {
   std::vector<uint8_t> collected;
   uint64_t tail = 0, min_uncollected = 0;
   DevBuf qctl, qseq, qslots, istate, tree, hist, goal_g, out_len, out_nodes, busy, ticket, admitter,
-      inflight;
+      inflight, wave_stats;
   int64_t grid = 0;
 };
 
@@ -1013,6 +1020,7 @@ extern "C" int bpida_server_start(int32_t width, int32_t max_inflight, int32_t r
         V.out_nodes.ensure(sizeof(uint64_t) * 64 * S) != hipSuccess ||
         V.busy.ensure(sizeof(int32_t) * S) != hipSuccess ||
         V.ticket.ensure(sizeof(uint64_t) * S) != hipSuccess ||
+        V.wave_stats.ensure(sizeof(RunStats) * (size_t)(grid * wpg)) != hipSuccess ||
         V.admitter.ensure(sizeof(int32_t)) != hipSuccess || V.inflight.ensure(sizeof(int32_t)) != hipSuccess)
       return BPIDA_ENOMEM;
     const unsigned fl = hipHostMallocCoherent | hipHostMallocMapped;
@@ -1050,6 +1058,7 @@ extern "C" int bpida_server_start(int32_t width, int32_t max_inflight, int32_t r
     A.goal_g = V.goal_g.as<int32_t>();
     A.out_len = V.out_len.as<int32_t>();
     A.out_nodes = V.out_nodes.as<uint64_t>();
+    A.wave_stats = V.wave_stats.as<RunStats>();
     A.n = 0;
     A.max_limit = (int)(O.max_threshold >= 0 ? std::min<int64_t>(O.max_threshold, kMaxLimit) : kMaxLimit);
     A.idle_ticks = ~0ull;  // waiting for requests is not a stall
@@ -1077,7 +1086,8 @@ extern "C" int bpida_server_start(int32_t width, int32_t max_inflight, int32_t r
     A.srv.backlog_max = O.admit_backlog < 0 ? (int64_t)(qcap / 2) : O.admit_backlog;
     if (launch_zero_words(V.qctl.p, sizeof(QueueCtl), V.stream) != hipSuccess ||
         launch_server_setup(A, V.stream) != hipSuccess ||
-        launch_batch4(cap, npl, wpg, (int)grid, A, V.stream) != hipSuccess) {
+        launch_batch4(cap, npl, wpg, (int)grid, A, V.stream) != hipSuccess ||
+        launch_run_stats(A.wave_stats, (int)(grid * wpg), A.q, V.stream) != hipSuccess) {
       (void)hipGetLastError();
       return BPIDA_EDEVICE;
     }
@@ -1139,13 +1149,13 @@ extern "C" int bpida_server_stop(void) {
     }
     V.running = false;
     uint64_t stats[kStats] = {0};
-    stats[0] = qc.rounds;
-    stats[1] = qc.searched;
-    stats[2] = qc.pushes * kQChunk;
+    stats[0] = qc.stats.rounds;
+    stats[1] = qc.stats.searched;
+    stats[2] = qc.stats.pushes * kQChunk;
     stats[3] = 1;
-    stats[6] = qc.pushes;
-    stats[7] = qc.pops;
-    stats[11] = qc.voluntary;
+    stats[6] = qc.stats.pushes;
+    stats[7] = qc.stats.pops;
+    stats[11] = qc.stats.voluntary;
     stats[12] = (uint64_t)V.grid;
     stats[13] = (uint64_t)(uint32_t)qc.err;
     memcpy(g_stats, stats, sizeof stats);

@@ -191,8 +191,8 @@ struct alignas(128) QChunk {
   uint64_t tiles[kQChunk];  // packed states, bits 0..63
   uint16_t meta[kQChunk];
   int32_t inst;
-  int32_t count;
-  int32_t kind;  // kChunk*
+  int32_t info;   // entries | kind (kChunk*) << 8 | board width << 16
+  int32_t limit;  // the f-limit being searched
 };
 
 // What a chunk's entries are.
@@ -203,8 +203,9 @@ constexpr int kChunkRing = 2;   // expanded 3x3 or 4x4 nodes with moves left: th
 
 // Per-slot control words of the queue ring, for the next ticket t to use the
 // slot: seq == 4t free for producer t, 4t + 1 claimed by it, 4t + 2 holds
-// ticket t's chunk; abandoned = 1 + the largest ticket whose producer gave up
+// ticket t's chunk, kSeqEnd: the search is over; abandoned = 1 + the largest ticket whose producer gave up
 // on this slot (ring full for its whole bounded wait), 0 if none.
+constexpr uint64_t kSeqEnd = ~0ull;  // every instance is done: the waiting wave leaves
 struct SlotCtl {
   uint64_t seq;
   uint64_t abandoned;
@@ -228,8 +229,21 @@ struct InstState {
                         // its counts are void (server mode answers BPIDA_ENOMEM)
 };
 
-// Queue control block and run counters.  The fields that many workgroups
-// touch concurrently sit on separate 128-byte lines.
+// Counters of one wave of the search kernel, stored when it leaves (adding
+// them up with atomics on one line took thousands of waves longer than a
+// small search), and their sums over the waves.
+struct RunStats {
+  uint64_t rounds, searched, pushes, pops;
+  uint64_t t_work, t_queue, t_idle;  // wall-clock ticks
+  uint64_t voluntary;                // donations made because workgroups idled
+  uint64_t qmax;                     // most chunks queued at once (seen at a push; a maximum)
+  uint64_t roots_read;               // split-tree roots read while seeding limits
+  uint64_t chunks_read_wide;         // 5x5 chunks taken (their high words read too)
+};
+constexpr int kRunStats = sizeof(RunStats) / 8;
+
+// Queue control block.  The fields that many workgroups touch concurrently
+// sit on separate 128-byte lines.
 struct QueueCtl {
   alignas(128) uint64_t head;
   alignas(128) uint64_t tail;
@@ -237,13 +251,7 @@ struct QueueCtl {
   alignas(128) int32_t seed_next;  // next instance whose first limit is to be seeded
   alignas(128) int32_t err;  // 1: queue full while seeding, 2: entries dropped,
                              // 4: idle watchdog, 8: deadline passed, 16: ring full
-  alignas(128) uint64_t rounds;
-  uint64_t searched, pushes, pops;
-  uint64_t t_work, t_queue, t_idle;  // wall-clock ticks summed over workgroups
-  uint64_t voluntary;                // donations made because workgroups idled
-  uint64_t qmax;                     // most chunks queued at once (seen at a push)
-  uint64_t roots_read;               // split-tree roots read while seeding limits
-  uint64_t chunks_read_wide;         // 5x5 chunks taken (their high words read too)
+  alignas(128) RunStats stats;  // summed over the waves after the search
 };
 
 // ---------------------------------------------------------------------------
@@ -299,11 +307,12 @@ struct BatchArgs {
   const int32_t* goal_g;
   int32_t* out_len;
   uint64_t* out_nodes;  // n x 64
+  RunStats* wave_stats; // per wave of the grid
   int32_t n;
   int32_t max_limit;
   uint64_t idle_ticks;   // an idle workgroup gives up after this many wall-clock ticks
   uint64_t budget_ticks; // every workgroup stops this many ticks after it starts
-  uint32_t donate_mask;  // donation checks run when (round & donate_mask) == 0
+  uint32_t donate_mask;  // donate_every - 1 (a quarter of the rounds between looks for waiting waves)
   int32_t donate_min;    // only stacks of at least this many entries donate (<= 0: 4 rounds of pops, <= ring / 2)
   int32_t donate_window; // a donation splits the oldest min(window, stack) entries (2 x chunk)
   int32_t first_solution; // nonzero: the final limit stops at its first goal
@@ -332,6 +341,8 @@ hipError_t launch_splitw(const InstW* d_inst, int n, int depth, const int64_t* d
 hipError_t launch_batch4(int lds_cap, int npl, int wpg, int grid, const BatchArgs& A, hipStream_t s);
 hipError_t launch_batch_status(const InstState* d_is, int n, const QueueCtl* d_q,
                                const int32_t* d_split_err, int32_t* d_status, hipStream_t s);
+// Sums `waves` records into q->stats.
+hipError_t launch_run_stats(const RunStats* d_wave_stats, int waves, QueueCtl* d_q, hipStream_t s);
 int batch4_max_blocks_per_cu(int lds_cap, int npl, int wpg);
 
 // Path reconstruction by exact-limit probes (bpida_path.hip).
