@@ -21,6 +21,7 @@
 #include "bpida_board.h"
 #include "bpida_internal.h"
 #include "bpida_ring.h"
+#include "bpida_ring5.h"
 #include "bpida_round.h"
 
 namespace bpida {
@@ -35,6 +36,17 @@ hipError_t walk_table_device(const int32_t** out) {
   const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(g_walk_table));
   *out = static_cast<const int32_t*>(p);
   return e;
+}
+
+// The search kernel's arguments, read where they lie.  The functions below
+// that run once a chunk or a limit take a fresh view of them: values that the
+// compiler may assume loaded already it keeps across the search loop, in
+// scalar registers that it then spills around every round.
+using Args = const __attribute__((address_space(4))) BatchArgs;
+__device__ __forceinline__ Args& fresh() {
+  Args* p = (Args*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm("" : "+s"(p));
+  return *p;
 }
 
 __device__ __forceinline__ uint64_t ld_relaxed(uint64_t* p) {
@@ -108,7 +120,8 @@ struct Unit {
 
 // Returns false if the ring stayed full for the whole bounded wait (the
 // entries were not queued).  `hi` goes to the slot's row of A.hi.
-__device__ bool q_push(const BatchArgs& A, const Unit& u, RunStats& wc) {
+__device__ __forceinline__ bool q_push(const Unit& u, RunStats& wc) {
+  Args& A = fresh();
   const int lane = lane_id();
   QueueCtl* q = A.q;
   const uint64_t mask = A.qmask;
@@ -116,8 +129,10 @@ __device__ bool q_push(const BatchArgs& A, const Unit& u, RunStats& wc) {
   int ok = 0;
   if (lane == 0) {
     pos = __hip_atomic_fetch_add(&q->tail, (uint64_t)1, __ATOMIC_RELAXED, AGENT);
-    const uint64_t h = ld_relaxed(&q->head);
-    if (pos + 1 > h) depth = pos + 1 - h;
+    if ((pos & 7) == 0) {  // (the line of `head` is busy with takes)
+      const uint64_t h = ld_relaxed(&q->head);
+      if (pos + 1 > h) depth = pos + 1 - h;
+    }
     SlotCtl* sc = A.seq + (pos & mask);
     for (int k = 0; k < A.push_spin; ++k) {
       const uint64_t v = ld_relaxed(&sc->seq);
@@ -139,7 +154,7 @@ __device__ bool q_push(const BatchArgs& A, const Unit& u, RunStats& wc) {
   pos = bcast64(pos);
   QChunk* c = A.slots + (pos & mask);
   st_relaxed(&c->tiles[lane], u.tile);
-  if (u.kind == kChunkWide) st_relaxed(&A.hi[(pos & mask) * kQChunk + lane], u.hi);
+  if (u.kind & kChunkWide) st_relaxed(&A.hi[(pos & mask) * kQChunk + lane], u.hi);
   st_relaxed(&c->meta[lane], u.meta);
   if (lane == 0) {
     st_relaxed(&c->inst, (int32_t)u.inst);
@@ -155,7 +170,8 @@ __device__ bool q_push(const BatchArgs& A, const Unit& u, RunStats& wc) {
 // ticket's chunk has arrived: 1 with the chunk; 0 not yet (the ticket is kept
 // for the next call, or dropped if its producer gave up); -1 the search is
 // over.
-__device__ int q_take(const BatchArgs& A, uint64_t& ticket, Unit& u, RunStats& wc) {
+__device__ __forceinline__ int q_take(uint64_t& ticket, Unit& u, RunStats& wc) {
+  Args& A = fresh();
   const int lane = lane_id();
   QueueCtl* q = A.q;
   const uint64_t mask = A.qmask;
@@ -191,7 +207,7 @@ __device__ int q_take(const BatchArgs& A, uint64_t& ticket, Unit& u, RunStats& w
   u.kind = (wave_bcast(info) >> 8) & 255;
   u.width = wave_bcast(info) >> 16;
   // the high words only for a 5x5 chunk: a 4x4 chunk reads 6 lines, not 10
-  const bool wide = u.kind == kChunkWide;
+  const bool wide = (u.kind & kChunkWide) != 0;
   u.hi = wide ? ld_agent(&A.hi[(ticket & mask) * kQChunk + lane]) : 0ull;
   wc.chunks_read_wide += wide ? 1 : 0;
   performed();  // all lanes have read the slot before it is handed back
@@ -204,7 +220,8 @@ __device__ int q_take(const BatchArgs& A, uint64_t& ticket, Unit& u, RunStats& w
 // held any more (the caller has waited for that decrement).  Tells every wave
 // that waits on a ticket; one that takes its ticket after the fetch_add below
 // sees `remaining` itself.
-__device__ void end_search(const BatchArgs& A) {
+__device__ __forceinline__ void end_search() {
+  Args& A = fresh();
   const int lane = lane_id();
   uint64_t h = 0, t = 0;
   if (lane == 0) {
@@ -223,7 +240,8 @@ __device__ void end_search(const BatchArgs& A) {
 
 // Work of instance i that had been added to its outstanding units could not be
 // queued: takes the unit back and marks the instance's counts void.
-__device__ void drop_unit(const BatchArgs& A, int i) {
+__device__ __forceinline__ void drop_unit(int i) {
+  Args& A = fresh();
   if (lane_id() == 0) {
     __hip_atomic_fetch_add(&A.is[i].outstanding, -1, __ATOMIC_RELAXED, AGENT);
     st_relaxed(&A.is[i].lost, 1);
@@ -239,8 +257,9 @@ __device__ void drop_unit(const BatchArgs& A, int i) {
 // must complete the limit itself.
 // `stage` (128 u64) and `stage_m` (64 u16) are LDS the caller does not use
 // while seeding (its LDS stack is empty whenever a limit is seeded).
-__device__ bool seed_limit(const BatchArgs& A, int i, int L, uint64_t* stage, uint16_t* stage_m, Unit& mine,
+__device__ __forceinline__ bool seed_limit(int i, int L, uint64_t* stage, uint16_t* stage_m, Unit& mine,
                            RunStats& wc) {
+  Args& A = fresh();
   const int lane = lane_id();
   InstState* S = A.is + i;
   const int width = S->width;
@@ -288,7 +307,7 @@ __device__ bool seed_limit(const BatchArgs& A, int i, int L, uint64_t* stage, ui
     for (int p0 = 0; p0 < cnt && !full; p0 += sc) {
       if (mine.count) {
         if (lane == 0) __hip_atomic_fetch_add(&S->outstanding, 1, __ATOMIC_RELAXED, AGENT);
-        full = !q_push(A, mine, wc);
+        full = !q_push(mine, wc);
       }
       mine.count = min(sc, cnt - p0);
       const bool on = lane < mine.count;
@@ -298,7 +317,7 @@ __device__ bool seed_limit(const BatchArgs& A, int i, int L, uint64_t* stage, ui
     }
     WAVE_SYNC();
   }
-  if (full) drop_unit(A, i);  // the remaining roots are dropped; the call reports BPIDA_ENOMEM
+  if (full) drop_unit(i);  // the remaining roots are dropped; the call reports BPIDA_ENOMEM
   fm = wave_min(fm);
   if (lane == 0 && fm != INT_MAX) __hip_atomic_fetch_min(&S->fmin, fm, __ATOMIC_RELAXED, AGENT);
   wc.roots_read += (uint64_t)nroots;
@@ -311,9 +330,10 @@ __device__ bool seed_limit(const BatchArgs& A, int i, int L, uint64_t* stage, ui
 
 // Server mode: copy slot i's answer into the pinned result ring, publish it,
 // and free the slot.  Executed by one wave after the slot's outputs are final.
-__device__ void emit_result(const BatchArgs& A, int i, int status) {
+__device__ __forceinline__ void emit_result(int i, int status) {
+  Args& A = fresh();
   const int lane = lane_id();
-  const ServerArgs& V = A.srv;
+  const auto& V = A.srv;
   WAVE_SYNC_MEM();  // the slot's output row, written by lane 0, is visible
   const uint64_t t = V.ticket[i];
   ServerRes* r = V.res + (t & V.ring_mask);
@@ -335,8 +355,9 @@ __device__ void emit_result(const BatchArgs& A, int i, int status) {
 // wave observed it), then advances it.  Loops while a new limit has no work;
 // the new limit's last chunk is left in `mine` (count 0: the instance is
 // done).
-__device__ void complete_limit(const BatchArgs& A, int i, int L, uint64_t* stage, uint16_t* stage_m, Unit& mine,
+__device__ __forceinline__ void complete_limit(int i, int L, uint64_t* stage, uint16_t* stage_m, Unit& mine,
                            RunStats& wc) {
+  Args& A = fresh();
   const int lane = lane_id();
   InstState* S = A.is + i;
   mine.count = 0;
@@ -391,12 +412,12 @@ __device__ void complete_limit(const BatchArgs& A, int i, int L, uint64_t* stage
     state = wave_bcast(state);
     if (state != 0) {
       performed();
-      if (A.server) emit_result(A, i, state);
-      else if (wave_bcast(left) == 0) end_search(A);
+      if (A.server) emit_result(i, state);
+      else if (wave_bcast(left) == 0) end_search();
       return;
     }
     L += 2;
-    if (!seed_limit(A, i, L, stage, stage_m, mine, wc)) return;
+    if (!seed_limit(i, L, stage, stage_m, mine, wc)) return;
   }
 }
 
@@ -405,7 +426,7 @@ __device__ void complete_limit(const BatchArgs& A, int i, int L, uint64_t* stage
 // ---------------------------------------------------------------------------
 
 // Validate and pack a state of 16 bytes (in pinned host memory) with one wave.
-__device__ Inst wave_ingest4(const uint8_t* src) {
+__device__ __forceinline__ Inst wave_ingest4(const uint8_t* src) {
   const int lane = lane_id();
   const uint32_t v = lane < 16 ? (uint32_t)src[lane] : 0u;
   // permutation: every value 0..15 exactly once
@@ -448,7 +469,7 @@ __device__ Inst wave_ingest4(const uint8_t* src) {
 // base[], interior nodes binned by f in hist_lds (256 entries of LDS).
 // Returns the first root's index inside base; the root count is
 // walks[blank][depth].
-__device__ int64_t wave_split4(const Inst& I, int depth, const int32_t* walks, NodeW* base,
+__device__ __forceinline__ int64_t wave_split4(const Inst& I, int depth, const int32_t* walks, NodeW* base,
                                uint32_t* hist_lds, uint32_t* hist_out, int32_t* goal_g_out) {
   const int lane = lane_id();
   for (int k = lane; k < kHistBins; k += 64) hist_lds[k] = 0;
@@ -515,11 +536,12 @@ __device__ int64_t wave_split4(const Inst& I, int depth, const int32_t* walks, N
 
 // Seeds a request's first limit with every chunk in the queue: the admitter
 // searches nothing itself.
-__device__ void admit_limit(const BatchArgs& A, int i, int L, uint64_t* st, uint16_t* sm) {
+__device__ __forceinline__ void admit_limit(int i, int L, uint64_t* st, uint16_t* sm) {
+  Args& A = fresh();
   Unit mine;
   RunStats wc = {};  // (the admitter's own counts are not reported)
-  if (seed_limit(A, i, L, st, sm, mine, wc)) complete_limit(A, i, L, st, sm, mine, wc);
-  while (mine.count && !q_push(A, mine, wc)) {
+  if (seed_limit(i, L, st, sm, mine, wc)) complete_limit(i, L, st, sm, mine, wc);
+  while (mine.count && !q_push(mine, wc)) {
     // lost: this was the instance's last unit unless other chunks are out
     int last = 0;
     if (lane_id() == 0) {
@@ -530,14 +552,15 @@ __device__ void admit_limit(const BatchArgs& A, int i, int L, uint64_t* st, uint
     }
     L = mine.limit;
     mine.count = 0;
-    if (wave_bcast(last)) complete_limit(A, i, L, st, sm, mine, wc);
+    if (wave_bcast(last)) complete_limit(i, L, st, sm, mine, wc);
   }
 }
 
 // Admits requests until the host asks to stop and nothing is in flight.
-__device__ void admitter_loop(const BatchArgs& A, uint64_t* st, uint16_t* sm, uint64_t deadline) {
+__device__ __forceinline__ void admitter_loop(uint64_t* st, uint16_t* sm, uint64_t deadline) {
+  Args& A = fresh();
   const int lane = lane_id();
-  const ServerArgs& V = A.srv;
+  const auto& V = A.srv;
   QueueCtl* q = A.q;
   uint32_t* hist_lds = (uint32_t*)st;  // the stack is unused by the admitter
   uint64_t head = 0;
@@ -566,7 +589,7 @@ __device__ void admitter_loop(const BatchArgs& A, uint64_t* st, uint16_t* sm, ui
         if (wave_bcast(inflight) == 0) {
           if (lane == 0) st_relaxed(&q->remaining, 0);
           performed();
-          end_search(A);
+          end_search();
           return;
         }
       }
@@ -636,8 +659,8 @@ __device__ void admitter_loop(const BatchArgs& A, uint64_t* st, uint16_t* sm, ui
     if (lane == 0) A.is[slot] = S;
     WAVE_SYNC_MEM();
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    if (S.done != 0) emit_result(A, slot, S.done);
-    else admit_limit(A, slot, S.limit, st, sm);
+    if (S.done != 0) emit_result(slot, S.done);
+    else admit_limit(slot, S.limit, st, sm);
     ++head;
   }
 }
@@ -645,9 +668,10 @@ __device__ void admitter_loop(const BatchArgs& A, uint64_t* st, uint16_t* sm, ui
 // Adds this wave's counts for the unit of instance i it held at limit L and
 // releases the unit; completes the limit if it was the last unit, which may
 // leave the next limit's chunk in `mine`.
-__device__ void release_unit(const BatchArgs& A, int i, int L, uint64_t expanded, int goals, int fmin,
+__device__ __forceinline__ void release_unit(int i, int L, uint64_t expanded, int goals, int fmin,
                              uint64_t* stage, uint16_t* stage_m, Unit& mine,
                            RunStats& wc) {
+  Args& A = fresh();
   const int lane = lane_id();
   InstState* S = A.is + i;
   mine.count = 0;
@@ -660,7 +684,7 @@ __device__ void release_unit(const BatchArgs& A, int i, int L, uint64_t expanded
   performed();  // the counts are in before the unit is gone
   int last = 0;
   if (lane == 0) last = __hip_atomic_fetch_add(&S->outstanding, -1, __ATOMIC_RELAXED, AGENT) == 1;
-  if (wave_bcast(last)) complete_limit(A, i, L, stage, stage_m, mine, wc);
+  if (wave_bcast(last)) complete_limit(i, L, stage, stage_m, mine, wc);
 }
 
 // ---------------------------------------------------------------------------
@@ -670,56 +694,62 @@ __device__ void release_unit(const BatchArgs& A, int i, int L, uint64_t expanded
 struct RoundClock {
   uint32_t tick = 0;       // rounds started
   uint32_t next_look = 0;  // the tick of the next look for waiting waves
+  bool fed = false;        // nobody waited at the last look
 };
 
 // The LDS stack of one wave while it searches a unit: entries [0, top), the
-// oldest at 0.  NodeStack holds nodes to expand (16-node rounds: Alg. 1's
-// map, lane l expands node l/4 with move l%4, 4x4 only; 64-node rounds: one
-// node per lane, four moves each, 5x5), RingStack expanded 3x3 and 4x4 nodes
-// with the moves they have left (one move per lane and round, bpida_ring.h).
-template <int W, int CAP, int NPL>
+// oldest at 0.  NodeStack holds 4x4 nodes to expand (16-node rounds: Alg. 1's
+// map, lane l expands node l/4 with move l%4), RingStack expanded nodes with
+// the moves they have left (one move per lane and round; bpida_ring.h, 5x5:
+// bpida_ring5.h).
+template <int CAP>
 struct NodeStack {
-  static_assert(NPL == 64 ? W == 5 && CAP >= 256 : W == 4 && (CAP & (CAP - 1)) == 0 && CAP >= 128, "stack");
-  using S = typename Board<W>::S;
-  static constexpr int kCap = CAP, kNpl = NPL;
+  static_assert((CAP & (CAP - 1)) == 0 && CAP >= 128, "stack");
+  static constexpr int kCap = CAP, kNpl = 16;
   // largest growth of one round: a node has at most 3 children (its parent's
   // cell is excluded).  Only a root of the split (depth 0) has no parent and
   // may have 4, and a root is expanded in the unit's first round, which
   // starts from one chunk (at most 64 entries) and so cannot overflow.
-  static constexpr int kGrow = NPL == 16 ? 32 : 2 * 64;
+  static constexpr int kGrow = 32;
   struct Entry {
-    S s;
+    uint64_t s;
     uint16_t m;
   };
-  S* st;
+  uint64_t* st;
   uint16_t* sm;
   LaneMap M;
   int limit;
 
   __device__ __forceinline__ NodeStack(uint64_t* lds, int lim)
-      : st((S*)lds), sm((uint16_t*)((S*)lds + CAP)), M(make_lane_map(lane_id())), limit(lim) {}
+      : st(lds), sm((uint16_t*)(lds + CAP)), M(make_lane_map(lane_id())), limit(lim) {}
   __device__ __forceinline__ Entry get(uint32_t i) const { return {st[i], sm[i]}; }
   __device__ __forceinline__ void put(uint32_t i, Entry e) {
     st[i] = e.s;
     sm[i] = e.m;
   }
   // (u: the unit's instance and limit)
-  __device__ __forceinline__ bool push(const BatchArgs& A, Unit u, Entry e, int count, RunStats& wc) const {
-    u.tile = (uint64_t)e.s;
-    u.hi = W == 5 ? (uint64_t)((unsigned __int128)e.s >> 64) : 0ull;
+  __device__ __forceinline__ bool push(Unit u, Entry e, int count, RunStats& wc) const {
+    u.tile = e.s;
     u.meta = e.m;
-    u.kind = W == 5 ? kChunkWide : kChunkNodes;
+    u.kind = kChunkNodes;
     u.count = count;
-    return q_push(A, u, wc);
+    return q_push(u, wc);
   }
   __device__ __forceinline__ uint32_t round(uint32_t top, int kp, int& goals, int& fmin) {
-    if constexpr (NPL == 16) return bp_round<CAP>(st, sm, top, kp, limit, M, goals, fmin);
-    else return bp_round64w<W, CAP, false>(st, sm, top, kp, goals);
+    return bp_round<CAP>(st, sm, top, kp, limit, M, goals, fmin);
   }
-  __device__ __forceinline__ uint32_t full_round(uint32_t top, uint64_t& gm) {
-    return bp_round64w<W, CAP, true>(st, sm, top, 64, gm);
+  __device__ __forceinline__ uint32_t load(const Unit& u, uint64_t&, int&) {
+    if (lane_id() < u.count) put((uint32_t)lane_id(), {u.tile, u.meta});
+    WAVE_SYNC();
+    return (uint32_t)u.count;
   }
 };
+
+// Bit of the moves that undo the move a node forbids (4: none).
+template <uint32_t U, uint32_t L, uint32_t R, uint32_t D>
+__device__ __forceinline__ uint32_t forbidden_bit(uint32_t fb) {
+  return fb == 0 ? U : fb == 1 ? L : fb == 2 ? R : fb == 3 ? D : 0u;
+}
 
 template <int W, int CAP>
 struct RingStack {
@@ -736,12 +766,12 @@ struct RingStack {
       : st((Entry*)lds), k(make_ring_consts<W>((char*)lds, kTable)) {}
   __device__ __forceinline__ Entry get(uint32_t i) const { return st[i]; }
   __device__ __forceinline__ void put(uint32_t i, Entry e) { st[i] = e; }
-  __device__ __forceinline__ bool push(const BatchArgs& A, Unit u, Entry e, int count, RunStats& wc) const {
+  __device__ __forceinline__ bool push(Unit u, Entry e, int count, RunStats& wc) const {
     u.tile = (uint64_t)e.r | ((uint64_t)e.c << 32);
     u.meta = (uint16_t)ring_pack(e.m);
     u.kind = kChunkRing;
     u.count = count;
-    return q_push(A, u, wc);
+    return q_push(u, wc);
   }
   __device__ __forceinline__ uint32_t round(uint32_t top, int kp, int& goals, int&) {
     uint64_t gm = 0;
@@ -765,8 +795,7 @@ struct RingStack {
     } else {
       uint32_t r, c, b;
       ring_planes<W>(t, meta & 15u, &r, &c, &b);
-      const uint32_t fb = (meta >> 5) & 7u;
-      const uint32_t undo = fb == 0 ? kRingU : fb == 1 ? kRingL : fb == 2 ? kRingR : fb == 3 ? kRingD : 0u;
+      const uint32_t undo = forbidden_bit<kRingU, kRingL, kRingR, kRingD>((meta >> 5) & 7u);
       const uint32_t base = (b << 3) | ((meta >> 9) * kRingSlack1);
       const uint32_t near = ring_nearer(r, c, ring_compare<W>(b));
       const uint32_t m = ring_meta(base, near, ring_legal<W>(b), undo);
@@ -775,6 +804,71 @@ struct RingStack {
       const uint64_t km = __builtin_amdgcn_ballot_w64(lane < top && m > kRingBase);
       const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(km >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)km, 0u));
       if (lane < top && m > kRingBase) put(at, {r, c, m});
+      top = (uint32_t)__popcll(km);
+    }
+    WAVE_SYNC();
+    return top;
+  }
+};
+
+template <int CAP>
+struct RingStack<5, CAP> {
+  static constexpr int kCap = CAP, kNpl = 64;
+  static constexpr int kGrow = 64;
+  static constexpr uint32_t kTable = (kR5Entry * CAP + 15u) & ~15u;
+  struct Entry {
+    R5Planes s;
+    uint32_t m;
+  };
+  static_assert(sizeof(Entry) == kR5Entry, "entry");
+  Entry* st;
+  R5Consts k;
+
+  __device__ __forceinline__ RingStack(uint64_t* lds) : st((Entry*)lds), k(make_r5_consts((char*)lds, kTable)) {}
+  __device__ __forceinline__ Entry get(uint32_t i) const { return st[i]; }
+  __device__ __forceinline__ void put(uint32_t i, Entry e) { st[i] = e; }
+  __device__ __forceinline__ bool push(Unit u, Entry e, int count, RunStats& wc) const {
+    const unsigned __int128 s = r5_board(e.s, (e.m >> 4) & 31u);
+    u.tile = (uint64_t)s;
+    u.hi = (uint64_t)(s >> 64);
+    u.meta = (uint16_t)r5_pack(e.m);
+    u.kind = kChunkRing | kChunkWide;
+    u.count = count;
+    return q_push(u, wc);
+  }
+  __device__ __forceinline__ uint32_t round(uint32_t top, int kp, int& goals, int&) {
+    uint64_t gm = 0;
+    top = r5_round<kTable, false>(top, kp, gm, k);
+    goals += __popcll(gm);
+    return top;
+  }
+  __device__ __forceinline__ uint32_t full_round(uint32_t top, uint64_t& gm) {
+    return r5_round<kTable, true>(top, 64, gm, k);
+  }
+  // As RingStack::load.
+  __device__ __forceinline__ uint32_t load(const Unit& u, uint64_t& expanded, int& goals) {
+    const uint32_t lane = (uint32_t)lane_id();
+    const unsigned __int128 t = (unsigned __int128)u.tile | ((unsigned __int128)u.hi << 64);
+    const uint32_t meta = u.meta;
+    const bool ring = (u.kind & kChunkRing) != 0;
+    uint32_t top = (uint32_t)u.count;
+    // the blank's board cell: in the meta word, as a ring cell if under way
+    const uint32_t c = meta & 31u, b = ring ? c - c / 6u : c;
+    const R5Planes s = r5_planes(t, b);
+    uint32_t m;
+    if (ring) {
+      m = r5_unpack(meta);
+      if (lane < top) put(lane, {s, m});
+    } else {
+      const uint32_t rb = r5_cell(b);
+      const uint32_t undo = forbidden_bit<kR5U, kR5L, kR5R, kR5D>((meta >> 5) & 7u);
+      const uint32_t base = (rb << 4) | ((meta >> 9) * kR5Slack1);
+      m = r5_meta(base, r5_nearer(s, r5_compare(rb, 0), r5_compare(rb, 1), r5_compare(rb, 2)), r5_legal(rb), undo);
+      expanded += (uint64_t)top;
+      goals += __popcll(__builtin_amdgcn_ballot_w64(lane < top && t == Board<5>::goal()));
+      const uint64_t km = __builtin_amdgcn_ballot_w64(lane < top && m > kR5Base);
+      const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(km >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)km, 0u));
+      if (lane < top && m > kR5Base) put(at, {s, m});
       top = (uint32_t)__popcll(km);
     }
     WAVE_SYNC();
@@ -799,8 +893,9 @@ __device__ __forceinline__ void stack_down(ST& S, uint32_t dst, uint32_t src, ui
 // overflow and donations to waiting workgroups.  Returns false if the time
 // budget ran out (abandoned).
 template <class ST, bool FS>
-__device__ bool run_unit(const BatchArgs& A, const Unit& u, ST& S, uint32_t top, RunStats& wc, RoundClock& clk,
+__device__ __forceinline__ bool run_unit(const Unit& u, ST& S, uint32_t top, RunStats& wc, RoundClock& clk,
                          uint64_t deadline, uint64_t& expanded, int& goals, int& fmin) {
+  Args& A = fresh();
   using Entry = typename ST::Entry;
   constexpr int kCap = ST::kCap, kNpl = ST::kNpl, kGrow = ST::kGrow;
   const int lane = lane_id(), inst = u.inst;
@@ -837,8 +932,10 @@ __device__ bool run_unit(const BatchArgs& A, const Unit& u, ST& S, uint32_t top,
       // oldest min(window, avail) entries (the shallowest, largest subtrees)
       // are split alternately, so donor and receiver each keep about half.
       //
-      // A look reads head and tail, which every push and take advances: all
-      // waves together can afford a few dozen looks a microsecond.  So the
+      // A look reads head and tail, which every push and take advances (or,
+      // after one that found nobody waiting, `fed`, which changes seldom: 256
+      // 5x5 states, which spill 17 chunks a microsecond, 63 -> 53 ms): all
+      // waves together can afford a few dozen of those a microsecond.  So the
       // period is 4 * donate_every rounds while every wave searches (100 hard
       // 4x4 states: 25.5 ms with 512 rounds, 28.7 ms with 128, 44 ms with
       // 64), and shrinks with the share of waves that search, down to 32
@@ -852,8 +949,12 @@ __device__ bool run_unit(const BatchArgs& A, const Unit& u, ST& S, uint32_t top,
         clk.next_look = tick + kLookMin;
       } else {
         int64_t ht = 0;
-        if (lane == 0) ht = (int64_t)(ld_relaxed(&q->head) - ld_relaxed(&q->tail));
+        if (lane == 0 && !(clk.fed && ld_relaxed(&q->fed))) {
+          ht = (int64_t)(ld_relaxed(&q->head) - ld_relaxed(&q->tail));
+          if (ht <= 0 && !clk.fed) st_relaxed(&q->fed, 1);
+        }
         const int wait = min(max(wave_bcast((int)ht), 0), waves);
+        clk.fed = wait == 0;
         clk.next_look = tick + (uint32_t)max((int)kLookMin, (int)((float)(waves - wait) * look_share));
         const int dmin = wait > waves - wait ? dlow : dhigh;
         if (wait > 0 && avail >= dmin) {
@@ -863,7 +964,7 @@ __device__ bool run_unit(const BatchArgs& A, const Unit& u, ST& S, uint32_t top,
           const Entry give = S.get(2 * lane), keep = S.get(2 * lane + 1);
           WAVE_SYNC();
           if (lane == 0) __hip_atomic_fetch_add(&A.is[inst].outstanding, 1, __ATOMIC_RELAXED, AGENT);
-          if (S.push(A, u, give, h, wc)) {
+          if (S.push(u, give, h, wc)) {
             wc.pushes += 1;
             wc.voluntary += 1;
             // the kept half becomes the bottom, the entries above the window
@@ -886,7 +987,7 @@ __device__ bool run_unit(const BatchArgs& A, const Unit& u, ST& S, uint32_t top,
         const Entry e = S.get(lane);
         WAVE_SYNC();
         if (lane == 0) __hip_atomic_fetch_add(&A.is[inst].outstanding, 1, __ATOMIC_RELAXED, AGENT);
-        if (S.push(A, u, e, 64, wc)) {
+        if (S.push(u, e, 64, wc)) {
           wc.pushes += 1;
         } else if (lane == 0) {
           __hip_atomic_fetch_add(&A.is[inst].outstanding, -1, __ATOMIC_RELAXED, AGENT);
@@ -898,7 +999,11 @@ __device__ bool run_unit(const BatchArgs& A, const Unit& u, ST& S, uint32_t top,
         avail -= 64;
       } while (avail + kGrow > kCap);
     }
-    const int kp = min(avail, kNpl);
+    // uniform as the compiler may not know it to be: a stack top it takes for a
+    // per-lane value moves the inner loop's bookkeeping to vector registers
+    // (13 more vector instructions a round, 15 % of a 4x4 search)
+    top = (uint32_t)wave_bcast((int)top);
+    const int kp = min((int)top, kNpl);
     top = S.round(top, kp, goals, fmin);
     // the spill above keeps every round inside the stack; a round that ended
     // past it would have overwritten entries (reported, never silent)
@@ -948,7 +1053,7 @@ __device__ bool run_unit(const BatchArgs& A, const Unit& u, ST& S, uint32_t top,
       }
     }
   }
-  // 64-node rounds: a pruned child always has f = limit + 2 (bp_round64w),
+  // 64-node rounds: a pruned child always has f = limit + 2,
   // and every limit below the optimum prunes one: below the optimum, a path
   // of approaching moves from a slack-0 node cannot reach the goal, so it
   // ends at a node whose remaining moves all go away and are pruned
@@ -960,9 +1065,9 @@ __device__ bool run_unit(const BatchArgs& A, const Unit& u, ST& S, uint32_t top,
 // The persistent kernel.  A workgroup holds WPG independent waves (Sec. 5's
 // block = one warp, WPG times over): each wave has its own stack and takes
 // its own work, and no wave ever waits for another.  LDS per wave: 10 * CAP
-// bytes, i.e. CAP nodes of a 16-node round, 5/6 CAP entries of the 3x3 and
-// 4x4 64-node round, or CAP/2 nodes of 5x5; the width is read per chunk from
-// the instance.
+// bytes, i.e. CAP nodes of a 16-node round, about 4/5 CAP entries of the 3x3
+// and 4x4 64-node round, or a third of CAP of the 5x5 one; a chunk carries its
+// width.
 //
 // Waves per SIMD a one-wave workgroup's stack allows (LDS: 160 KB per compute
 // unit).  The launch bound keeps the vector registers within that occupancy,
@@ -972,18 +1077,27 @@ constexpr int batch_waves_per_simd() {
   constexpr int w = NPL != 64 ? 1 : (int)(163840u / (10u * CAP)) / 4;
   return w > 8 ? 8 : w < 1 ? 1 : w;
 }
+constexpr int kCounterBytes = (sizeof(RunStats) + 15) / 16 * 16;
 template <int CAP>
 constexpr int ring_cap() {
-  return (CAP * 10 - (int)kRingTable) / 12 / 16 * 16;
+  return (CAP * 10 - (int)kRingTable - kCounterBytes) / 12 / 16 * 16;
+}
+template <int CAP>
+constexpr int ring5_cap() {
+  return (CAP * 10 - (int)kR5Table - kCounterBytes) / 28 / 16 * 16;
 }
 
 template <int CAP, int NPL, int WPG, bool FS>
-__global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void batch4_kernel(BatchArgs A) {
+__global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void batch4_kernel(BatchArgs) {
+  Args& A = fresh();
   static_assert(CAP % 16 == 0 && (NPL == 64 || (CAP & (CAP - 1)) == 0), "stack size");
   static_assert(NPL == 16 || NPL == 64, "nodes per round");
   static_assert(NPL == 16 || CAP >= 256, "stack too small for 64-node rounds");
   static_assert(WPG == 1 || WPG == 2 || WPG == 4, "waves per workgroup");
-  constexpr int kWords = 10 * CAP / 8;  // u64 words of one wave's stack
+  // u64 words of one wave's stack, and behind it the wave's counters: in
+  // registers they cost 22 scalar registers the search loop has better uses
+  // for (it spilled 40 to 190 vector registers around them)
+  constexpr int kWords = 10 * CAP / 8 + (NPL == 64 ? 0 : kCounterBytes / 8);
   __shared__ __attribute__((aligned(16))) uint64_t lds[WPG * kWords];
   uint64_t* st = lds + (WPG == 1 ? 0 : (int)(threadIdx.x >> 6) * kWords);
   uint16_t* sm = (uint16_t*)(st + CAP);  // staging of the seeds' meta words
@@ -994,14 +1108,16 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
     int role = 0;
     if (lane == 0) role = atomicCAS(A.srv.admitter, 0, 1) == 0;
     if (wave_bcast(role)) {
-      admitter_loop(A, st, sm, wall_clock64() + A.budget_ticks);
+      admitter_loop(st, sm, wall_clock64() + A.budget_ticks);
       if (lane == 0) A.wave_stats[blockIdx.x * WPG + (WPG == 1 ? 0 : threadIdx.x >> 6)] = RunStats{};
       return;
     }
   }
 
   Unit u;  // the chunk to search next (count 0: none)
-  RunStats wc = {};
+  // (every lane writes the same values to the same words)
+  RunStats& wc = *(RunStats*)(st + kWords - kCounterBytes / 8);
+  wc = RunStats{};
 
   // Seed the first limit of every instance through a shared cursor: all
   // instances are seeded by workgroups that are running, whatever part of
@@ -1016,9 +1132,9 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
     if (i >= A.n) break;
     if (ld_wave(&q->err) & kErrFatal) break;  // work already lost: stop seeding
     if (A.is[i].done != 0) continue;
-    if (u.count && !q_push(A, u, wc)) drop_unit(A, u.inst);
+    if (u.count && !q_push(u, wc)) drop_unit(u.inst);
     const int L = A.is[i].limit;
-    if (seed_limit(A, i, L, st, sm, u, wc)) complete_limit(A, i, L, st, sm, u, wc);
+    if (seed_limit(i, L, st, sm, u, wc)) complete_limit(i, L, st, sm, u, wc);
   }
 
   uint64_t t_mark = wall_clock64();
@@ -1031,7 +1147,7 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
 
   for (;;) {
     if (u.count == 0) {
-      const int got = q_take(A, ticket, u, wc);
+      const int got = q_take(ticket, u, wc);
       if (got < 0) break;
       if (got == 0) {
         // Wait.  The ticket's own slot is all that is polled, with longer
@@ -1044,7 +1160,9 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
           polls = 0;
           idle_since = 0;
         }
-        if ((++polls & 31u) == 0) {
+        ++polls;
+        if ((polls == 8 || (polls & 31u) == 0) && lane == 0 && ld_relaxed(&q->fed)) st_relaxed(&q->fed, 0);
+        if ((polls & 31u) == 0) {
           if (ld_wave(&q->remaining) <= 0) break;
           if (!A.server && (ld_wave(&q->err) & kErrFatal)) break;
           const uint64_t now = wall_clock64();
@@ -1082,37 +1200,33 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
     if (u.width == 5) {
       // (smaller stacks take no 5x5 batch: the host refuses it)
       if constexpr (CAP / 2 >= 512) {
-        NodeStack<5, CAP / 2, 64> S(st, u.limit);
-        if (lane < u.count) S.put(lane, {(unsigned __int128)u.tile | ((unsigned __int128)u.hi << 64), u.meta});
-        WAVE_SYNC();
-        ok = run_unit<NodeStack<5, CAP / 2, 64>, FS>(A, u, S, (uint32_t)u.count, wc, clk, deadline, expanded,
-                                                     goals, fmin);
+        RingStack<5, ring5_cap<CAP>()> S(st);
+        const uint32_t top = S.load(u, expanded, goals);
+        ok = run_unit<RingStack<5, ring5_cap<CAP>()>, FS>(u, S, top, wc, clk, deadline, expanded, goals, fmin);
       }
     } else if (u.width == 3) {
       if constexpr (CAP >= 256) {
         RingStack<3, ring_cap<CAP>()> S(st);
         const uint32_t top = S.load(u, expanded, goals);
-        ok = run_unit<RingStack<3, ring_cap<CAP>()>, FS>(A, u, S, top, wc, clk, deadline, expanded, goals,
+        ok = run_unit<RingStack<3, ring_cap<CAP>()>, FS>(u, S, top, wc, clk, deadline, expanded, goals,
                                                          fmin);
       }
     } else if constexpr (NPL == 64) {
       RingStack<4, ring_cap<CAP>()> S(st);
       const uint32_t top = S.load(u, expanded, goals);
-      ok = run_unit<RingStack<4, ring_cap<CAP>()>, FS>(A, u, S, top, wc, clk, deadline, expanded, goals,
+      ok = run_unit<RingStack<4, ring_cap<CAP>()>, FS>(u, S, top, wc, clk, deadline, expanded, goals,
                                                        fmin);
     } else {
-      NodeStack<4, CAP, NPL> S(st, u.limit);
-      if (lane < u.count) S.put(lane, {u.tile, u.meta});
-      WAVE_SYNC();
-      ok = run_unit<NodeStack<4, CAP, NPL>, FS>(A, u, S, (uint32_t)u.count, wc, clk, deadline, expanded, goals,
-                                                fmin);
+      NodeStack<CAP> S(st, u.limit);
+      const uint32_t top = S.load(u, expanded, goals);
+      ok = run_unit<NodeStack<CAP>, FS>(u, S, top, wc, clk, deadline, expanded, goals, fmin);
     }
     if (!ok) break;
     const uint64_t now = wall_clock64();
     wc.t_work += now - t_mark;
     t_mark = now;
     wc.searched += expanded;
-    release_unit(A, u.inst, u.limit, expanded, goals, fmin, st, sm, u, wc);
+    release_unit(u.inst, u.limit, expanded, goals, fmin, st, sm, u, wc);
   }
   if (lane == 0) A.wave_stats[blockIdx.x * WPG + (WPG == 1 ? 0 : threadIdx.x >> 6)] = wc;
 }

@@ -1,6 +1,7 @@
 // bpida_board.h -- sliding-tile boards of width 3, 4 and 5 for the batched
-// search: packed state type, goal, move legality, the Manhattan delta table
-// and the one-node-per-lane round of BPDFS (Alg. 1).
+// search: packed state type, goal, move legality, the Manhattan delta table,
+// and the 4x4 one-node-per-lane round of BPDFS (Alg. 1) that builds a node's
+// four children (plain mode).
 //
 // Packing: cell p holds its tile in bits [BITS*p, BITS*p + BITS): 4 bits per
 // tile in a u64 for 3x3 and 4x4, 5 bits per tile in a 128-bit word for 5x5.
@@ -168,14 +169,6 @@ __device__ __forceinline__ uint32_t mul_u24(uint32_t k, uint32_t t) {
 __device__ __forceinline__ uint32_t mul_i24(int k, uint32_t t) {
   uint32_t r;
   asm("v_mul_i32_i24 %0, %1, %2" : "=v"(r) : "v"(k), "v"(t));
-  return r;
-}
-
-// a * b + c on 24-bit signed a, b (one instruction; the compiler would
-// otherwise shift and subtract).
-__device__ __forceinline__ uint32_t mad_i24(uint32_t a, int b, uint32_t c) {
-  uint32_t r;
-  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b), "v"(c));
   return r;
 }
 
@@ -514,108 +507,6 @@ __device__ __forceinline__ uint32_t bp_round64_4(uint64_t* st, uint32_t top, int
   bp_move4<CAP, 1>(st, out, s, c, rk);
   bp_move4<CAP, 2>(st, out, s, c, rk);
   bp_move4<CAP, 3>(st, out, s, c, rk);
-  WAVE_SYNC();
-  return out;
-}
-
-// Per-node values shared by the four moves of a 64-node round
-// (width 5).
-struct NodeCtx {
-  uint32_t b;      // blank cell
-  uint32_t shb;    // BITS * b
-  uint32_t rowi;   // vertical moves: the blank's row (table index part)
-  uint32_t coli;   // horizontal moves: the blank's column
-  uint32_t lmx;    // bit (A + 4 up): move A survives the f test
-  uint32_t mbase;  // slack << 8 | blank
-};
-
-// One move for every lane of a 64-node round (see bp_round64w).
-template <int W, int CAP, int A>
-__device__ __forceinline__ void bp_move_w(typename Board<W>::S* st, uint16_t* sm, uint32_t& out,
-                                          const typename Board<W>::S s, const NodeCtx& c) {
-  using B = Board<W>;
-  using S = typename B::S;
-  constexpr int delta = A == 0 ? -W : A == 1 ? -1 : A == 2 ? 1 : W;
-  constexpr bool vert = A == 0 || A == 3;
-  constexpr uint32_t K = vert ? ((1u << (B::BITS * W)) - 1u) : B::MASK;
-  // shift to the neighbour's cell; it wraps (and the tile is unused) when
-  // the move is illegal, and needs no mask on a legal one
-  const uint32_t shu = c.shb + (uint32_t)(B::BITS * delta);
-  const uint32_t x = (uint32_t)(s >> (shu & (8u * sizeof(S) - 1u)));
-  const uint32_t tile = x & B::MASK;  // the neighbour's tile t
-  const uint32_t up = B::template up<A>(x, c.rowi, c.coli);  // 1: t moves away from its goal cell
-  const uint32_t kb = opaque((c.lmx >> (A + 4 * up)) & 1u);
-  const uint64_t km = __builtin_amdgcn_uicmp(kb, 0u, 33);  // lanes with kb != 0
-  // the child is built in a branch that the compiler skips when no lane keeps
-  // the move
-  if (kb != 0u) {
-    // successor: t moves from n to b, i.e. the packed word changes by
-    // t * (base^b - base^n) = +/- (K * t) << (BITS * min(b, n))
-    uint32_t kt;
-    if constexpr (K < (1u << 24)) kt = mul_u24(K, tile);
-    else kt = K * tile;  // 5x5 rows: K = 2^25 - 1
-    const S d = (S)kt << ((A < 2 ? shu : c.shb) & (8u * sizeof(S) - 1u));
-    const S cs = A < 2 ? s + d : s - d;
-    // stack meta: n | (3 - A) << 5 | (slack - 2 up) << 8
-    const uint32_t cm = mad_i24(up, -512, c.mbase) + (uint32_t)(delta + ((3 - A) << 5));
-    const uint32_t r = __builtin_amdgcn_mbcnt_hi((uint32_t)(km >> 32),
-                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)km, 0u));
-    // byte offsets into the stack: entry out + r (below CAP: the caller
-    // leaves room for the largest round)
-    constexpr uint32_t LS = sizeof(S) == 8 ? 3 : 4;
-    const uint32_t pst = (r + out) << LS;
-    *(S*)((char*)st + pst) = cs;
-    *(uint16_t*)((char*)sm + (pst >> (LS - 1))) = (uint16_t)cm;
-  }
-  out += (uint32_t)__popcll(km);
-}
-
-// One BPDFS round with one popped node per lane, for 5x5 boards: pops
-// kp = min(64, top) nodes from a stack of entries [0, top), tests them for
-// the goal and pushes every legal, non-undoing child with f <= limit.  The
-// caller guarantees that the children fit, top + 2*kp <= CAP (three
-// children a node at most; only a root, expanded in a unit's first round
-// from at most 64 entries, can have four; no position wraps); FULL: it also
-// guarantees kp = 64, so no lane is idle, and passes a 64-bit mask that
-// collects the lanes that expanded a goal.  The round does not track the f
-// of pruned children: every slack on the stack is even (f keeps the parity
-// of h0, and so does the limit), so a child is pruned only from slack 0,
-// moving a tile away from its goal, and its f is the limit + 2.
-template <int W, int CAP, bool FULL, typename G>
-__device__ __forceinline__ uint32_t bp_round64w(typename Board<W>::S* st, uint16_t* sm, uint32_t top, int kp,
-                                                G& goals) {
-  using B = Board<W>;
-  using S = typename B::S;
-  const int lane = lane_id();
-  const uint32_t base = top - (uint32_t)kp;
-  constexpr uint32_t LS = sizeof(S) == 8 ? 3 : 4;
-  const uint32_t pst = opaque((base + (uint32_t)lane) << LS);
-  const S s = *(const S*)((const char*)st + pst);
-  const uint32_t m = *(const uint16_t*)((const char*)sm + (pst >> (LS - 1)));
-  const uint64_t actm = FULL || kp >= 64 ? ~0ull : ((1ull << kp) - 1ull);
-  const uint64_t gm = __builtin_amdgcn_ballot_w64(s == B::goal());
-  // goals: a count (int), or (FULL) the union of the rounds' goal masks
-  if constexpr (FULL) goals |= gm;
-  else goals += __popcll(gm & actm);
-  NodeCtx c;
-  c.b = m & 31u;
-  const uint32_t fb = (m >> 5) & 7u;
-  c.shb = opaque(B::BITS * c.b);
-  const uint32_t lm = B::legal(c.b) & ~(1u << fb);
-  c.coli = B::col_part(c.b);
-  c.rowi = B::row_part(c.b);
-  // moves that survive: any legal one if its tile approaches its goal, and
-  // only with slack >= 2 if it moves away (bits 0..3 and 4..7 of lm * 17);
-  // lanes past kp keep nothing
-  const bool roomy = m >= (2u << 8);
-  if constexpr (FULL) c.lmx = mul_u24(lm, roomy ? 17u : 1u);
-  else c.lmx = mul_u24(lm, sel_lanes(actm, roomy ? 17u : 1u));
-  c.mbase = (m & 0xFF00u) | c.b;
-  uint32_t out = base;
-  bp_move_w<W, CAP, 0>(st, sm, out, s, c);
-  bp_move_w<W, CAP, 1>(st, sm, out, s, c);
-  bp_move_w<W, CAP, 2>(st, sm, out, s, c);
-  bp_move_w<W, CAP, 3>(st, sm, out, s, c);
   WAVE_SYNC();
   return out;
 }

@@ -195,11 +195,12 @@ struct alignas(128) QChunk {
   int32_t limit;  // the f-limit being searched
 };
 
-// What a chunk's entries are.
-constexpr int kChunkNodes = 0;  // nodes to expand: packed board, stack_meta word
-constexpr int kChunkWide = 1;   // the same on 5x5, high words in BatchArgs::hi
-constexpr int kChunkRing = 2;   // expanded 3x3 or 4x4 nodes with moves left: the two
-                                // planes (rows in the low word), ring_pack'ed meta
+// What a chunk's entries are: nodes to expand (packed board, stack_meta word)
+// or expanded nodes with moves left (3x3 and 4x4: the two planes, rows in the
+// low word; 5x5: the packed board; packed meta word).
+constexpr int kChunkWide = 1;   // 5x5: the entries' high words are in BatchArgs::hi
+constexpr int kChunkRing = 2;   // expanded nodes with moves left
+constexpr int kChunkNodes = 0;  // 3x3 or 4x4 nodes
 
 // Per-slot control words of the queue ring, for the next ticket t to use the
 // slot: seq == 4t free for producer t, 4t + 1 claimed by it, 4t + 2 holds
@@ -236,7 +237,7 @@ struct RunStats {
   uint64_t rounds, searched, pushes, pops;
   uint64_t t_work, t_queue, t_idle;  // wall-clock ticks
   uint64_t voluntary;                // donations made because workgroups idled
-  uint64_t qmax;                     // most chunks queued at once (seen at a push; a maximum)
+  uint64_t qmax;                     // most chunks queued at once (seen at every 8th push; a maximum)
   uint64_t roots_read;               // split-tree roots read while seeding limits
   uint64_t chunks_read_wide;         // 5x5 chunks taken (their high words read too)
 };
@@ -251,6 +252,7 @@ struct QueueCtl {
   alignas(128) int32_t seed_next;  // next instance whose first limit is to be seeded
   alignas(128) int32_t err;  // 1: queue full while seeding, 2: entries dropped,
                              // 4: idle watchdog, 8: deadline passed, 16: ring full
+  alignas(128) int32_t fed;  // a look at head and tail found no waiting wave; cleared by one that waits
   alignas(128) RunStats stats;  // summed over the waves after the search
 };
 

@@ -1,4 +1,4 @@
-"""The 64-node round on 3x3 and 4x4 stacks: entries with moves left.
+"""The batched 64-node rounds: stacks of entries with moves left.
 
 One f-limit far above the heuristic, so that slack runs deep and a root may
 keep all four moves: the count of that limit against a layer-by-layer path
@@ -19,7 +19,8 @@ pytestmark = pytest.mark.gpu
 # width, stack, split depth, moves from the goal, limit above the first one
 CASES = [(3, 256, 0, 4, 28), (3, 256, 5, 9, 24), (3, 512, 1, 12, 22), (3, 2048, 0, 1, 28),
          (4, 512, 0, 10, 16), (4, 512, 5, 6, 18), (4, 640, 1, 14, 14), (4, 672, 0, 3, 20),
-         (4, 768, 1, 9, 16), (4, 2048, 0, 10, 16)]
+         (4, 768, 1, 9, 16), (4, 2048, 0, 10, 16),
+         (5, 1024, 0, 12, 12), (5, 1024, 6, 24, 10), (5, 2048, 1, 30, 10)]
 
 
 @functools.lru_cache(maxsize=None)
