@@ -1131,7 +1131,12 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
     i = wave_bcast(i);
     if (i >= A.n) break;
     if (ld_wave(&q->err) & kErrFatal) break;  // work already lost: stop seeding
-    if (A.is[i].done != 0) continue;
+    if (A.is[i].done != 0) {  // nothing to search
+      int left = 1;
+      if (lane == 0) left = __hip_atomic_fetch_add(&q->remaining, -1, __ATOMIC_RELAXED, AGENT) - 1;
+      if (wave_bcast(left) == 0) end_search();
+      continue;
+    }
     if (u.count && !q_push(u, wc)) drop_unit(u.inst);
     const int L = A.is[i].limit;
     if (seed_limit(i, L, st, sm, u, wc)) complete_limit(i, L, st, sm, u, wc);
@@ -1265,73 +1270,54 @@ hipError_t launch_run_stats(const RunStats* d_wave_stats, int waves, QueueCtl* d
 }
 
 // ---------------------------------------------------------------------------
-// Set-up: per-instance state, queue sequence numbers and counters.
-// ---------------------------------------------------------------------------
-__global__ void batch_setup_kernel(BatchArgs A, const InstW* __restrict__ inst,
-                                   const int64_t* __restrict__ root_off,
-                                   const int32_t* __restrict__ nroots) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k <= (int64_t)A.qmask) {
-    A.seq[k].seq = 4 * (uint64_t)k;
-    A.seq[k].abandoned = 0;
-  }
-  if (k < A.n) {
-    InstState S;
-    S.limit = first_limit(inst[k].h0, A.start_limit);
-    S.col = (S.limit - inst[k].h0) / 2;
-    S.done = inst[k].status;  // 0 = to search
-    if (A.exact_limit) {
-      // one limit only: a limit below h0 or of the other parity has no path
-      // of exactly that length
-      S.limit = A.exact_limit[k];
-      S.col = 0;
-      if (S.done == 0 && (S.limit < inst[k].h0 || ((S.limit - inst[k].h0) & 1))) S.done = 2;
-    }
-    S.outstanding = 0;
-    S.nodes = 0;
-    S.fmin = INT_MAX;
-    S.goals = 0;
-    S.stop = 0;
-    S.lost = 0;
-    S.root_off = root_off[k];
-    S.nroots = nroots[k];
-    S.width = inst[k].width;
-    if (S.done == 0 && (S.limit > A.max_limit || S.col >= 64)) S.done = -3;  // BPIDA_ELIMIT
-    A.is[k] = S;
-    if (S.done == 0) atomicAdd(&A.q->remaining, 1);
-  }
-}
-
-// Per-instance status: 1 solved, < 0 a bpida_status.  A failed split or a
+// After the search: per-instance status, 1 solved, < 0 a bpida_status.  A
 // queue that overflowed (its dropped work invalidates every count) marks
 // every instance; a watchdog or deadline stop marks the unfinished ones.
+// ---------------------------------------------------------------------------
 __global__ void batch_status_kernel(const InstState* __restrict__ is, int n,
-                                    const QueueCtl* __restrict__ q,
-                                    const int32_t* __restrict__ split_err, int32_t* __restrict__ st) {
+                                    const QueueCtl* __restrict__ q, int32_t* __restrict__ st) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
   const int32_t done = is[k].done;
   int32_t v = done;
-  if (*split_err) v = -6;                    // BPIDA_EINTERNAL
-  else if (q->err & kErrFatal) v = -4;      // BPIDA_ENOMEM
+  if (q->err & kErrFatal) v = -4;           // BPIDA_ENOMEM
   else if (q->err & 32) v = -6;             // LDS stack overrun: BPIDA_EINTERNAL
   else if (done == 0) v = -6;               // stopped by the watchdog or the deadline
   st[k] = v;
 }
 
 // ---------------------------------------------------------------------------
-// Ingest and root split of the batched path, any width.
+// Before the search, in one launch: ingest, root split and state of every
+// instance, its output row, the queue's slots and control block.
 // ---------------------------------------------------------------------------
 
-// One thread per instance: validate (a permutation of 0..w*w-1 whose parity
-// matches the blank's distance from cell 0), pack, Manhattan h0.  States are
-// w*w bytes at byte_off[i] (or i*w*w); widths[i] (or `width`) per instance.
-__global__ void ingestw_kernel(const uint8_t* __restrict__ states, const int64_t* __restrict__ byte_off,
-                               const int32_t* __restrict__ widths, int width, int n,
-                               InstW* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int w = widths ? widths[i] : width;
+// Validates (a permutation of 0..w*w-1 whose parity matches the blank's
+// distance from cell 0), packs and measures the state at s with one wave:
+// lane p takes cell p.
+__device__ __forceinline__ InstW wave_ingest(const uint8_t* __restrict__ s, int w) {
+  const int lane = lane_id();
+  const int nn = w * w, bits = w == 5 ? 5 : 4;
+  const bool on = lane < nn;
+  const uint32_t v = on ? (uint32_t)s[lane] : 0xFFu;
+  const bool fits = on && v < (uint32_t)nn;
+  uint32_t seen = fits ? 1u << v : 0u, inv = 0;
+  for (int p = 0; p < 25; ++p) inv += (p > lane && p < nn && (uint32_t)__builtin_amdgcn_readlane((int)v, p) < v) ? 1u : 0u;
+  if (!on) inv = 0;
+  int h = 0;
+  if (fits && v != 0) {
+    const int dr = lane / w - (int)v / w, dc = lane % w - (int)v % w;
+    h = (dr < 0 ? -dr : dr) + (dc < 0 ? -dc : dc);
+  }
+  const unsigned __int128 word = on ? (unsigned __int128)(v & 31u) << (bits * lane) : 0;
+  uint64_t lo = (uint64_t)word, hi = (uint64_t)(word >> 64);
+  for (int o = 32; o > 0; o >>= 1) {
+    seen |= (uint32_t)__shfl_xor((int)seen, o, 64);
+    inv += (uint32_t)__shfl_xor((int)inv, o, 64);
+    h += __shfl_xor(h, o, 64);
+    lo |= __shfl_xor(lo, o, 64);
+    hi |= __shfl_xor(hi, o, 64);
+  }
+  const uint64_t blank_m = __builtin_amdgcn_ballot_w64(on && v == 0);
   InstW r;
   r.lo = 0;
   r.hi = 0;
@@ -1339,47 +1325,15 @@ __global__ void ingestw_kernel(const uint8_t* __restrict__ states, const int64_t
   r.h0 = 0;
   r.status = -1;  // BPIDA_EINVAL
   r.width = w;
-  if (w < 3 || w > 5) {
-    out[i] = r;
-    return;
-  }
-  const int nn = w * w;
-  const int bits = w == 5 ? 5 : 4;
-  const uint8_t* s = states + (byte_off ? byte_off[i] : (int64_t)i * nn);
-  uint32_t seen = 0;
-  bool ok = true;
-  unsigned __int128 word = 0;
-  int blank = 0, h = 0;
-  uint32_t inv = 0;
-  for (int p = 0; p < nn; ++p) {
-    const uint32_t v = s[p];
-    if (v >= (uint32_t)nn || ((seen >> v) & 1u)) ok = false;
-    seen |= 1u << (v & 31u);
-    if (v == 0) blank = p;
-    word |= (unsigned __int128)(v & 31u) << (bits * p);
-    if (v != 0 && v < (uint32_t)nn) {
-      const int dr = p / w - (int)v / w, dc = p % w - (int)v % w;
-      h += (dr < 0 ? -dr : dr) + (dc < 0 ? -dc : dc);
-    }
-    for (int q = 0; q < p; ++q) inv ^= (uint32_t)(s[q] > v);
-  }
-  if (ok) {
-    const uint32_t bpar = (uint32_t)(blank / w + blank % w) & 1u;
-    r.status = inv == bpar ? 0 : -2;  // BPIDA_EUNSOLVABLE
-    r.lo = (uint64_t)word;
-    r.hi = (uint64_t)(word >> 64);
-    r.blank = blank;
+  if (seen == (1u << nn) - 1u) {  // nn cells with nn different tiles
+    r.blank = (int)__builtin_ctzll(blank_m);
+    const uint32_t bpar = (uint32_t)(r.blank / w + r.blank % w) & 1u;
+    r.status = (inv & 1u) == bpar ? 0 : -2;  // BPIDA_EUNSOLVABLE
+    r.lo = lo;
+    r.hi = hi;
     r.h0 = h;
   }
-  out[i] = r;
-}
-
-hipError_t launch_ingestw(const uint8_t* d_states, const int64_t* d_byte_off, const int32_t* d_widths,
-                          int width, int n, InstW* d_inst, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(ingestw_kernel, dim3((n + 127) / 128), dim3(128), 0, s, d_states, d_byte_off,
-                     d_widths, width, n, d_inst);
-  return hipGetLastError();
+  return r;
 }
 
 constexpr int kSplitThreadsW = 256;
@@ -1390,7 +1344,7 @@ constexpr int kSplitThreadsW = 256;
 // sizes come from the walk-count table of that width.
 template <int W>
 __device__ void split_impl(const InstW& I, int fb0, int depth, const int32_t* walks, NodeW* base,
-                           uint32_t* h_lds, int32_t* fill, int32_t* gmin, int32_t* err,
+                           uint32_t* h_lds, int32_t* fill, int32_t* gmin, int32_t* bad,
                            int64_t* lvl_out) {
   using B = Board<W>;
   using S = typename B::S;
@@ -1438,7 +1392,7 @@ __device__ void split_impl(const InstW& I, int fb0, int depth, const int32_t* wa
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-      if (*fill != lc[d + 1]) atomicOr(err, 1);
+      if (*fill != lc[d + 1]) *bad = 1;
       *fill = 0;
     }
     lvl = next;
@@ -1447,55 +1401,88 @@ __device__ void split_impl(const InstW& I, int fb0, int depth, const int32_t* wa
   *lvl_out = lvl;
 }
 
-// One workgroup of 256 threads per instance; the instance's region is
-// tree_off[i] (or i * stride).  `walks` = [width - 3][cell][first forbidden
-// move][length] counts; `forbid` (null: none) = per instance the move its
-// start may not make first (4: any).
-__global__ __launch_bounds__(kSplitThreadsW) void splitw_kernel(
-    const InstW* __restrict__ inst, int depth, const int64_t* __restrict__ tree_off, int64_t stride,
-    const int32_t* __restrict__ walks, const uint8_t* __restrict__ forbid, NodeW* __restrict__ tree,
-    uint32_t* __restrict__ hist, int32_t* __restrict__ goal_g, int32_t* __restrict__ err,
-    int64_t* __restrict__ root_off, int32_t* __restrict__ nroots) {
+// Workgroups 0..n-1 take an instance each, the others the queue (kPrepSlots
+// slots a thread).  The instance's split-tree region is tree_off[i] (or
+// i * stride); `forbid` (null: none) = per instance the move its start may
+// not make first (4: any).
+constexpr int kPrepSlots = 4;
+__global__ __launch_bounds__(kSplitThreadsW) void batch_prep_kernel(BatchArgs A, PrepArgs P) {
   const int i = blockIdx.x;
-  const InstW I = inst[i];
-  const int fb0 = forbid ? min((int)forbid[i], 4) : 4;
-  __shared__ uint32_t h_lds[kHistBins];
-  __shared__ int32_t fill;
-  __shared__ int32_t gmin;
-  for (int k = threadIdx.x; k < kHistBins; k += kSplitThreadsW) h_lds[k] = 0;
-  if (threadIdx.x == 0) {
-    gmin = INT_MAX;
-    fill = 0;
+  const int tid = threadIdx.x;
+  if (i >= A.n) {
+    const int64_t k0 = ((int64_t)(i - A.n) * kSplitThreadsW + tid) * kPrepSlots;
+    for (int64_t k = k0; k < k0 + kPrepSlots && k <= (int64_t)A.qmask; ++k) {
+      A.seq[k].seq = 4 * (uint64_t)k;
+      A.seq[k].abandoned = 0;
+    }
+    if (i == A.n) {
+      for (int k = tid; k < (int)(sizeof(QueueCtl) / 4); k += kSplitThreadsW) ((uint32_t*)A.q)[k] = 0;
+      __syncthreads();
+      if (tid == 0) A.q->remaining = A.n;
+    }
+    return;
   }
-  const int64_t region = tree_off ? tree_off[i] : (int64_t)i * stride;
-  NodeW* base = tree + region;
+  __shared__ InstW I;
+  __shared__ uint32_t h_lds[kHistBins];
+  __shared__ int32_t fill, gmin, bad;
+  if (tid < 64) {
+    const int w = P.widths ? P.widths[i] : P.width;
+    const InstW v = wave_ingest(P.states + (P.byte_off ? P.byte_off[i] : (int64_t)i * w * w), w);
+    if (tid == 0) {
+      I = v;
+      gmin = INT_MAX;
+      fill = 0;
+      bad = 0;
+      A.out_len[i] = -1;
+    }
+    A.out_nodes[(size_t)i * 64 + tid] = 0;
+  }
+  for (int k = tid; k < kHistBins; k += kSplitThreadsW) h_lds[k] = 0;
+  __syncthreads();
+  const int fb0 = P.forbid ? min((int)P.forbid[i], 4) : 4;
+  const int64_t region = P.tree_off ? P.tree_off[i] : (int64_t)i * P.stride;
+  NodeW* base = const_cast<NodeW*>(A.tree) + region;
+  const int32_t* wk = P.walks + (size_t)(I.width - 3) * kWalkStride;
   int64_t lvl = 0;
   if (I.status == 0) {
-    const int32_t* wk = walks + (size_t)(I.width - 3) * kWalkStride;
-    if (I.width == 3) split_impl<3>(I, fb0, depth, wk, base, h_lds, &fill, &gmin, err, &lvl);
-    else if (I.width == 4) split_impl<4>(I, fb0, depth, wk, base, h_lds, &fill, &gmin, err, &lvl);
-    else split_impl<5>(I, fb0, depth, wk, base, h_lds, &fill, &gmin, err, &lvl);
-  } else {
-    __syncthreads();
+    if (I.width == 3) split_impl<3>(I, fb0, P.depth, wk, base, h_lds, &fill, &gmin, &bad, &lvl);
+    else if (I.width == 4) split_impl<4>(I, fb0, P.depth, wk, base, h_lds, &fill, &gmin, &bad, &lvl);
+    else split_impl<5>(I, fb0, P.depth, wk, base, h_lds, &fill, &gmin, &bad, &lvl);
   }
-  for (int k = threadIdx.x; k < kHistBins; k += kSplitThreadsW) hist[(size_t)i * kHistBins + k] = h_lds[k];
-  if (threadIdx.x == 0) {
-    goal_g[i] = gmin;
-    root_off[i] = region + lvl;
-    nroots[i] = I.status == 0
-                    ? walks[(size_t)(I.width - 3) * kWalkStride + walk_row(I.blank, fb0) + depth]
-                    : 0;
+  for (int k = tid; k < kHistBins; k += kSplitThreadsW)
+    const_cast<uint32_t*>(A.hist)[(size_t)i * kHistBins + k] = h_lds[k];
+  if (tid == 0) {
+    const_cast<int32_t*>(A.goal_g)[i] = gmin;
+    InstState S;
+    S.limit = first_limit(I.h0, A.start_limit);
+    S.col = (S.limit - I.h0) / 2;
+    S.done = I.status;  // 0 = to search
+    if (A.exact_limit) {
+      // one limit only: a limit below h0 or of the other parity has no path
+      // of exactly that length
+      S.limit = A.exact_limit[i];
+      S.col = 0;
+      if (S.done == 0 && (S.limit < I.h0 || ((S.limit - I.h0) & 1))) S.done = 2;
+    }
+    S.outstanding = 0;
+    S.nodes = 0;
+    S.fmin = INT_MAX;
+    S.goals = 0;
+    S.stop = 0;
+    S.lost = 0;
+    S.root_off = region + lvl;
+    S.nroots = I.status == 0 ? wk[walk_row(I.blank, fb0) + P.depth] : 0;
+    S.width = I.width;
+    if (S.done == 0 && (S.limit > A.max_limit || S.col >= 64)) S.done = -3;  // BPIDA_ELIMIT
+    if (bad) S.done = -6;                                                    // BPIDA_EINTERNAL
+    A.is[i] = S;
   }
 }
 
-hipError_t launch_splitw(const InstW* d_inst, int n, int depth, const int64_t* d_tree_off,
-                         int64_t stride, const int32_t* d_walks, const uint8_t* d_forbid,
-                         NodeW* d_tree, uint32_t* d_hist, int32_t* d_goal_g, int32_t* d_err,
-                         int64_t* d_root_off, int32_t* d_nroots, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(splitw_kernel, dim3(n), dim3(kSplitThreadsW), 0, s, d_inst, depth, d_tree_off,
-                     stride, d_walks, d_forbid, d_tree, d_hist, d_goal_g, d_err, d_root_off,
-                     d_nroots);
+hipError_t launch_batch_prep(const BatchArgs& A, const PrepArgs& P, hipStream_t s) {
+  const int64_t per = (int64_t)kSplitThreadsW * kPrepSlots;
+  const int64_t blocks = A.n + ((int64_t)A.qmask + per) / per;
+  hipLaunchKernelGGL(batch_prep_kernel, dim3((unsigned)blocks), dim3(kSplitThreadsW), 0, s, A, P);
   return hipGetLastError();
 }
 
@@ -1521,19 +1508,10 @@ hipError_t launch_server_setup(const BatchArgs& A, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_batch_setup(const BatchArgs& A, const InstW* d_inst, const int64_t* d_root_off,
-                              const int32_t* d_nroots, hipStream_t s) {
-  const int64_t work = std::max<int64_t>((int64_t)A.qmask + 1, A.n);
-  hipLaunchKernelGGL(batch_setup_kernel, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, s, A,
-                     d_inst, d_root_off, d_nroots);
-  return hipGetLastError();
-}
-
-hipError_t launch_batch_status(const InstState* d_is, int n, const QueueCtl* d_q,
-                               const int32_t* d_split_err, int32_t* d_status, hipStream_t s) {
+hipError_t launch_batch_status(const InstState* d_is, int n, const QueueCtl* d_q, int32_t* d_status,
+                               hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(batch_status_kernel, dim3((n + 255) / 256), dim3(256), 0, s, d_is, n, d_q,
-                     d_split_err, d_status);
+  hipLaunchKernelGGL(batch_status_kernel, dim3((n + 255) / 256), dim3(256), 0, s, d_is, n, d_q, d_status);
   return hipGetLastError();
 }
 

@@ -92,12 +92,12 @@ struct Workspace {
   bool arch_ok = false;
   uint64_t qcap = 0;  // queue slots of the last batched launch
   DevBuf inst, tree, tree_off, hist, goal_g, err, cursor, part, spill_t, spill_m, res, stop;
-  DevBuf qctl, qseq, qslots, qhi, istate, root_off, nroots, status, wave_stats;
+  DevBuf qctl, qseq, qslots, qhi, istate, status, wave_stats;
   // non-backtracking walk counts per width (3, 4, 5), start cell and length:
   // the device table (d_walks) and its host copy
   const int32_t* d_walks = nullptr;
   WalkTable h_walks = make_walk_table();
-  DevBuf treew, winst, tree_offw, widths, byte_off;
+  DevBuf treew, tree_offw, widths, byte_off;
   DevBuf h2d_states, out_len, out_nodes, out_path;
   // path reconstruction: current states, moves left, previous moves, probes
   DevBuf p_cur, p_left, p_prev, p_probe, p_limit, p_forbid, p_len, p_nodes, p_status, p_err;
@@ -396,13 +396,9 @@ struct BatchPlan {
 
 // Device buffers of one batched solve.
 struct BatchBufs {
-  InstW* winst = nullptr;
   NodeW* treew = nullptr;
   uint32_t* hist = nullptr;
   int32_t* goal_g = nullptr;
-  int32_t* err = nullptr;
-  int64_t* root_off = nullptr;
-  int32_t* nroots = nullptr;
   QueueCtl* qctl = nullptr;
   SlotCtl* qseq = nullptr;
   QChunk* qslots = nullptr;
@@ -480,13 +476,9 @@ size_t carve_batched(uintptr_t base, const BatchPlan& P, BatchBufs* B) {
     return p;
   };
   const size_t n = (size_t)P.n;
-  B->winst = (InstW*)take(sizeof(InstW) * n);
   B->treew = (NodeW*)take(sizeof(NodeW) * (size_t)P.tree_nodes);
   B->hist = (uint32_t*)take(sizeof(uint32_t) * kHistBins * n);
   B->goal_g = (int32_t*)take(sizeof(int32_t) * n);
-  B->err = (int32_t*)take(sizeof(int32_t));
-  B->root_off = (int64_t*)take(sizeof(int64_t) * n);
-  B->nroots = (int32_t*)take(sizeof(int32_t) * n);
   B->qctl = (QueueCtl*)take(sizeof(QueueCtl));
   B->qseq = (SlotCtl*)take(sizeof(SlotCtl) * P.qcap);
   B->qslots = (QChunk*)take(sizeof(QChunk) * P.qcap);
@@ -505,12 +497,9 @@ size_t carve_batched(uintptr_t base, const BatchPlan& P, BatchBufs* B) {
 int alloc_batched(const BatchPlan& P, BatchBufs* B) {
   Workspace& W = g_ws;
   const size_t n = (size_t)P.n;
-  if (W.winst.ensure(sizeof(InstW) * n) != hipSuccess ||
-      W.treew.ensure(sizeof(NodeW) * (size_t)P.tree_nodes) != hipSuccess ||
+  if (W.treew.ensure(sizeof(NodeW) * (size_t)P.tree_nodes) != hipSuccess ||
       W.hist.ensure(sizeof(uint32_t) * kHistBins * n) != hipSuccess ||
-      W.goal_g.ensure(sizeof(int32_t) * n) != hipSuccess || W.err.ensure(sizeof(int32_t)) != hipSuccess ||
-      W.root_off.ensure(sizeof(int64_t) * n) != hipSuccess ||
-      W.nroots.ensure(sizeof(int32_t) * n) != hipSuccess ||
+      W.goal_g.ensure(sizeof(int32_t) * n) != hipSuccess ||
       W.qctl.ensure(sizeof(QueueCtl)) != hipSuccess ||
       W.qseq.ensure(sizeof(SlotCtl) * P.qcap) != hipSuccess ||
       W.qslots.ensure(sizeof(QChunk) * P.qcap) != hipSuccess ||
@@ -523,13 +512,9 @@ int alloc_batched(const BatchPlan& P, BatchBufs* B) {
        W.byte_off.ensure(sizeof(int64_t) * n) != hipSuccess ||
        W.tree_offw.ensure(sizeof(int64_t) * n) != hipSuccess))
     return g_no_alloc ? BPIDA_EINVAL : BPIDA_ENOMEM;
-  B->winst = W.winst.as<InstW>();
   B->treew = W.treew.as<NodeW>();
   B->hist = W.hist.as<uint32_t>();
   B->goal_g = W.goal_g.as<int32_t>();
-  B->err = W.err.as<int32_t>();
-  B->root_off = W.root_off.as<int64_t>();
-  B->nroots = W.nroots.as<int32_t>();
   B->qctl = W.qctl.as<QueueCtl>();
   B->qseq = W.qseq.as<SlotCtl>();
   B->qslots = W.qslots.as<QChunk>();
@@ -564,19 +549,12 @@ int enqueue_batched_into(const uint8_t* d_states, int32_t* d_len, uint64_t* d_no
     }                          \
   } while (0)
   const int n = P.n;
-  HIPCHK(launch_fill_outputs(d_len, d_nodes, n, st));
   if (n == 0) return BPIDA_OK;
   if (h_widths) {
     HIPCHK(hipMemcpyAsync(B.widths, h_widths, sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(B.byte_off, P.boff.data(), sizeof(int64_t) * (size_t)n, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(B.tree_offw, P.toff.data(), sizeof(int64_t) * (size_t)n, hipMemcpyHostToDevice, st));
   }
-  HIPCHK(launch_ingestw(d_states, h_widths ? B.byte_off : nullptr, h_widths ? B.widths : nullptr,
-                        P.width, n, B.winst, st));
-  HIPCHK(launch_zero_i32(B.err, 1, st));
-  HIPCHK(launch_splitw(B.winst, n, P.D, h_widths ? B.tree_offw : nullptr, P.stride, walks, root_forbid,
-                       B.treew, B.hist, B.goal_g, B.err, B.root_off, B.nroots, st));
-  HIPCHK(launch_zero_words(B.qctl, sizeof(QueueCtl), st));
 
   BatchArgs A;
   memset(&A, 0, sizeof A);
@@ -605,11 +583,21 @@ int enqueue_batched_into(const uint8_t* d_states, int32_t* d_len, uint64_t* d_no
   A.seed_chunk = P.sc;
   A.push_spin = (int32_t)O.push_spin;
   A.exact_limit = exact_limit;
-  HIPCHK(launch_batch_setup(A, B.winst, B.root_off, B.nroots, st));
+  PrepArgs R;
+  R.states = d_states;
+  R.byte_off = h_widths ? B.byte_off : nullptr;
+  R.widths = h_widths ? B.widths : nullptr;
+  R.tree_off = h_widths ? B.tree_offw : nullptr;
+  R.forbid = root_forbid;
+  R.walks = walks;
+  R.stride = P.stride;
+  R.width = P.width;
+  R.depth = P.D;
+  HIPCHK(launch_batch_prep(A, R, st));
   if (ev0) HIPCHK(hipEventRecord(ev0, st));
   HIPCHK(launch_batch4(P.cap, P.npl, P.wpg, (int)P.grid, A, st));
   if (ev1) HIPCHK(hipEventRecord(ev1, st));
-  HIPCHK(launch_batch_status(A.is, n, A.q, B.err, d_status, st));
+  HIPCHK(launch_batch_status(A.is, n, A.q, d_status, st));
   // (counters are read by the synchronous calls only, which are the timed ones)
   if (ev1) HIPCHK(launch_run_stats(B.wave_stats, (int)(P.grid * P.wpg), A.q, st));
   return BPIDA_OK;
@@ -658,10 +646,8 @@ int run_batched(const uint8_t* d_states, int n, int32_t* d_len, uint64_t* d_node
   if (rc0 != BPIDA_OK) return rc0;
   std::vector<int32_t> status((size_t)n);
   QueueCtl qc;
-  int32_t split_err = 0;
   HIPCHK(hipMemcpyAsync(status.data(), W.status.p, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost, st));
   HIPCHK(hipMemcpyAsync(&qc, W.qctl.p, sizeof(QueueCtl), hipMemcpyDeviceToHost, st));
-  HIPCHK(hipMemcpyAsync(&split_err, W.err.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
   float ms = 0.f;
   if (hipEventElapsedTime(&ms, W.ev0, W.ev1) == hipSuccess) stats[4] = (uint64_t)(ms * 1000.0f);
@@ -677,7 +663,7 @@ int run_batched(const uint8_t* d_states, int n, int32_t* d_len, uint64_t* d_node
   stats[11] = qc.stats.voluntary;
   stats[5] = qc.stats.qmax;
   stats[12] = (uint64_t)grid;
-  stats[13] = (uint64_t)(uint32_t)qc.err | ((uint64_t)(split_err != 0) << 8);
+  stats[13] = (uint64_t)(uint32_t)qc.err;
   stats[14] = W.qcap;
   stats[16] = qc.stats.roots_read;
   stats[17] = qc.stats.chunks_read_wide;

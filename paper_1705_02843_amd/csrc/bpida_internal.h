@@ -81,7 +81,7 @@ struct alignas(8) NodeW {
   uint32_t f;
 };
 
-// Ingest result of the batched path, any width.
+// An ingested state of the batched path, any width.
 struct InstW {
   uint64_t lo, hi;
   int32_t blank;
@@ -332,17 +332,20 @@ hipError_t launch_server_setup(const BatchArgs& A, hipStream_t s);
 // variable: no allocation).
 hipError_t walk_table_device(const int32_t** out);
 
-hipError_t launch_batch_setup(const BatchArgs& A, const InstW* d_inst, const int64_t* d_root_off,
-                              const int32_t* d_nroots, hipStream_t s);
-hipError_t launch_ingestw(const uint8_t* d_states, const int64_t* d_byte_off, const int32_t* d_widths,
-                          int width, int n, InstW* d_inst, hipStream_t s);
-hipError_t launch_splitw(const InstW* d_inst, int n, int depth, const int64_t* d_tree_off,
-                         int64_t stride, const int32_t* d_walks, const uint8_t* d_forbid,
-                         NodeW* d_tree, uint32_t* d_hist, int32_t* d_goal_g, int32_t* d_err,
-                         int64_t* d_root_off, int32_t* d_nroots, hipStream_t s);
+// What the launch before the search reads beside the search's arguments.
+struct PrepArgs {
+  const uint8_t* states;     // w*w bytes an instance, at byte_off[i] or back to back
+  const int64_t* byte_off;   // null: one width
+  const int32_t* widths;     // null: `width`
+  const int64_t* tree_off;   // split-tree region per instance (null: i * stride)
+  const uint8_t* forbid;     // null, or per instance the move its start may not make first
+  const int32_t* walks;      // walk-count table, [width - 3]...
+  int64_t stride;
+  int32_t width, depth;
+};
+hipError_t launch_batch_prep(const BatchArgs& A, const PrepArgs& P, hipStream_t s);
 hipError_t launch_batch4(int lds_cap, int npl, int wpg, int grid, const BatchArgs& A, hipStream_t s);
-hipError_t launch_batch_status(const InstState* d_is, int n, const QueueCtl* d_q,
-                               const int32_t* d_split_err, int32_t* d_status, hipStream_t s);
+hipError_t launch_batch_status(const InstState* d_is, int n, const QueueCtl* d_q, int32_t* d_status, hipStream_t s);
 // Sums `waves` records into q->stats.
 hipError_t launch_run_stats(const RunStats* d_wave_stats, int waves, QueueCtl* d_q, hipStream_t s);
 int batch4_max_blocks_per_cu(int lds_cap, int npl, int wpg);
