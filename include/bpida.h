@@ -363,7 +363,8 @@ int64_t bpida_get_option(const char *key);
  *   out[2] entries moved from LDS to HBM (plain: spills; batched: donated
  *          or spilled chunks x 64)
  *   out[3] search-kernel launches
- *   out[4] search-kernel time in microseconds (device events, summed)
+ *   out[4] search-kernel time in microseconds (plain: device events, summed;
+ *          batched: device clock, first wave's start to last wave's end)
  *   out[5] plain mode: largest per-workgroup spill stack seen, in entries;
  *          batched mode: most chunks queued at once (seen at a push)
  *   out[6] batched mode: chunks pushed to the work queue (seeds excluded)

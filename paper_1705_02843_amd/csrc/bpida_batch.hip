@@ -1109,7 +1109,9 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
     if (lane == 0) role = atomicCAS(A.srv.admitter, 0, 1) == 0;
     if (wave_bcast(role)) {
       admitter_loop(st, sm, wall_clock64() + A.budget_ticks);
-      if (lane == 0) A.wave_stats[blockIdx.x * WPG + (WPG == 1 ? 0 : threadIdx.x >> 6)] = RunStats{};
+      RunStats none = {};
+      none.t_first = ~0ull;
+      if (lane == 0) A.wave_stats[blockIdx.x * WPG + (WPG == 1 ? 0 : threadIdx.x >> 6)] = none;
       return;
     }
   }
@@ -1118,6 +1120,7 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
   // (every lane writes the same values to the same words)
   RunStats& wc = *(RunStats*)(st + kWords - kCounterBytes / 8);
   wc = RunStats{};
+  wc.t_first = wall_clock64();
 
   // Seed the first limit of every instance through a shared cursor: all
   // instances are seeded by workgroups that are running, whatever part of
@@ -1233,57 +1236,69 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
     wc.searched += expanded;
     release_unit(u.inst, u.limit, expanded, goals, fmin, st, sm, u, wc);
   }
+  wc.t_last = wall_clock64();
   if (lane == 0) A.wave_stats[blockIdx.x * WPG + (WPG == 1 ? 0 : threadIdx.x >> 6)] = wc;
 }
 
-// One workgroup: the waves' counters into q->stats.
-constexpr int kStatsThreads = 1024;
-__global__ __launch_bounds__(kStatsThreads) void run_stats_kernel(const RunStats* __restrict__ w, int waves,
-                                                                  QueueCtl* __restrict__ q) {
-  __shared__ uint64_t part[kStatsThreads / 64][kRunStats];
-  constexpr int kMax = offsetof(RunStats, qmax) / 8;  // the one that is a maximum
-  uint64_t sum[kRunStats] = {};
-  for (int i = threadIdx.x; i < waves; i += kStatsThreads)
+// ---------------------------------------------------------------------------
+// After the search, in one launch.  Workgroup 0 (with F.out) sums the waves'
+// counters.  The others: per-instance status, 1 solved, < 0 a bpida_status (a
+// queue that overflowed marks every instance: its dropped work invalidates
+// every count; a watchdog or deadline stop marks the unfinished ones), and the
+// outputs' copies for the host.  A call that waits reads statuses, counters
+// and, for small batches, outputs from pinned memory that this kernel wrote:
+// each copy by the runtime instead took 25 to 50 us.
+// ---------------------------------------------------------------------------
+constexpr int kFinishThreads = 512;
+__device__ __forceinline__ uint64_t stat_join(int k, uint64_t a, uint64_t b) {
+  if (k == offsetof(RunStats, t_first) / 8) return min(a, b);
+  if (k == offsetof(RunStats, qmax) / 8 || k == offsetof(RunStats, t_last) / 8) return max(a, b);
+  return a + b;
+}
+__global__ __launch_bounds__(kFinishThreads) void batch_finish_kernel(FinishArgs F) {
+  const int tid = threadIdx.x;
+  int block = (int)blockIdx.x;
+  if (F.out && block-- == 0) {
+    __shared__ uint64_t part[kFinishThreads / 64][kRunStats];
+    uint64_t sum[kRunStats] = {};
+    sum[offsetof(RunStats, t_first) / 8] = ~0ull;
+    for (int i = tid; i < F.waves; i += kFinishThreads) {
+      uint64_t v[kRunStats];
+      for (int k = 0; k < kRunStats; ++k) v[k] = ((const uint64_t*)(F.wave_stats + i))[k];
+      for (int k = 0; k < kRunStats; ++k) sum[k] = stat_join(k, sum[k], v[k]);
+    }
     for (int k = 0; k < kRunStats; ++k) {
-      const uint64_t v = ((const uint64_t*)(w + i))[k];
-      sum[k] = k == kMax ? max(sum[k], v) : sum[k] + v;
+      for (int o = 32; o > 0; o >>= 1) sum[k] = stat_join(k, sum[k], __shfl_xor(sum[k], o, 64));
+      if ((tid & 63) == 0) part[tid >> 6][k] = sum[k];
     }
-  for (int k = 0; k < kRunStats; ++k) {
-    for (int o = 32; o > 0; o >>= 1) {
-      const uint64_t v = __shfl_xor(sum[k], o, 64);
-      sum[k] = k == kMax ? max(sum[k], v) : sum[k] + v;
+    __syncthreads();
+    if (tid < kRunStats) {
+      uint64_t s = part[0][tid];
+      for (int j = 1; j < kFinishThreads / 64; ++j) s = stat_join(tid, s, part[j][tid]);
+      ((uint64_t*)&F.out->sum)[tid] = s;
     }
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][k] = sum[k];
+    if (tid == 0) F.out->err = F.q->err;
+    return;
   }
-  __syncthreads();
-  if (threadIdx.x < kRunStats) {
-    const int k = threadIdx.x;
-    uint64_t s = 0;
-    for (int j = 0; j < kStatsThreads / 64; ++j) s = k == kMax ? max(s, part[j][k]) : s + part[j][k];
-    ((uint64_t*)&q->stats)[k] = s;
+  const int64_t at = (int64_t)block * kFinishThreads + tid;
+  if (at < F.n) {
+    const int32_t done = F.is[at].done;
+    int32_t v = done;
+    if (F.q->err & kErrFatal) v = -4;  // BPIDA_ENOMEM
+    else if (F.q->err & 32) v = -6;    // LDS stack overrun: BPIDA_EINTERNAL
+    else if (done == 0) v = -6;        // stopped by the watchdog or the deadline
+    F.status[at] = v;
+    if (F.host_len) F.host_len[at] = F.len[at];
   }
+  if (F.host_nodes && at < (int64_t)F.n * 64) F.host_nodes[at] = F.nodes[at];
 }
 
-hipError_t launch_run_stats(const RunStats* d_wave_stats, int waves, QueueCtl* d_q, hipStream_t s) {
-  hipLaunchKernelGGL(run_stats_kernel, dim3(1), dim3(kStatsThreads), 0, s, d_wave_stats, waves, d_q);
+hipError_t launch_batch_finish(const FinishArgs& F, hipStream_t s) {
+  const int64_t work = !F.is ? 0 : F.host_nodes ? (int64_t)F.n * 64 : F.n;
+  const int64_t blocks = (F.out ? 1 : 0) + (work + kFinishThreads - 1) / kFinishThreads;
+  if (blocks == 0) return hipSuccess;
+  hipLaunchKernelGGL(batch_finish_kernel, dim3((unsigned)blocks), dim3(kFinishThreads), 0, s, F);
   return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// After the search: per-instance status, 1 solved, < 0 a bpida_status.  A
-// queue that overflowed (its dropped work invalidates every count) marks
-// every instance; a watchdog or deadline stop marks the unfinished ones.
-// ---------------------------------------------------------------------------
-__global__ void batch_status_kernel(const InstState* __restrict__ is, int n,
-                                    const QueueCtl* __restrict__ q, int32_t* __restrict__ st) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  const int32_t done = is[k].done;
-  int32_t v = done;
-  if (q->err & kErrFatal) v = -4;           // BPIDA_ENOMEM
-  else if (q->err & 32) v = -6;             // LDS stack overrun: BPIDA_EINTERNAL
-  else if (done == 0) v = -6;               // stopped by the watchdog or the deadline
-  st[k] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -1508,13 +1523,6 @@ hipError_t launch_server_setup(const BatchArgs& A, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_batch_status(const InstState* d_is, int n, const QueueCtl* d_q, int32_t* d_status,
-                               hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(batch_status_kernel, dim3((n + 255) / 256), dim3(256), 0, s, d_is, n, d_q, d_status);
-  return hipGetLastError();
-}
-
 // The first-solution search is a kernel of its own: with both unit loops in
 // one kernel the register allocation of each suffers.
 template <int CAP, int NPL, int WPG>
@@ -1528,13 +1536,18 @@ static hipError_t launch_batch_t(int grid, const BatchArgs& A, hipStream_t s) {
 
 template <int CAP, int NPL, int WPG>
 static int occupancy_t() {
+  // (asked once: it does not change, every call needs it, and each of the two
+  // queries takes some 5 us; the callers hold the library's lock)
+  static int known = -1;
+  if (known >= 0) return known;
   int nb = 0, nf = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, batch4_kernel<CAP, NPL, WPG, false>, 64 * WPG, 0) !=
           hipSuccess ||
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&nf, batch4_kernel<CAP, NPL, WPG, true>, 64 * WPG, 0) !=
           hipSuccess)
     return 0;
-  return nb < nf ? nb : nf;  // the grid suits either kernel
+  known = nb < nf ? nb : nf;  // the grid suits either kernel
+  return known;
 }
 
 // Supported (stack capacity, nodes per round, waves per workgroup) triples.

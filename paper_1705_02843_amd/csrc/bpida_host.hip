@@ -85,6 +85,36 @@ struct DevBuf {
   }
 };
 
+// Grow-only pinned host buffer, which kernels read and write in place.
+struct HostBuf {
+  void* p = nullptr;
+  size_t bytes = 0;
+  hipError_t ensure(size_t want) {
+    if (want <= bytes) return hipSuccess;
+    if (p) (void)hipHostFree(p);
+    p = nullptr;
+    bytes = 0;
+    const size_t b = std::max<size_t>(want, 4096);
+    const hipError_t e = hipHostMalloc(&p, b, hipHostMallocCoherent | hipHostMallocMapped);
+    if (e != hipSuccess) {
+      p = nullptr;
+      (void)hipGetLastError();
+      return e;
+    }
+    bytes = b;
+    return hipSuccess;
+  }
+  template <class T>
+  T* as() const {
+    return static_cast<T*>(p);
+  }
+};
+
+// Host-buffer calls of up to this many instances pass their states and
+// outputs through pinned memory that the kernels read and write in place
+// (2.3 MB in all); a larger batch's outputs are worth the copy engine.
+constexpr size_t kPinnedInstances = 4096;
+
 struct Workspace {
   int device = -1;
   int num_cu = 0;
@@ -92,12 +122,13 @@ struct Workspace {
   bool arch_ok = false;
   uint64_t qcap = 0;  // queue slots of the last batched launch
   DevBuf inst, tree, tree_off, hist, goal_g, err, cursor, part, spill_t, spill_m, res, stop;
-  DevBuf qctl, qseq, qslots, qhi, istate, status, wave_stats;
+  DevBuf qctl, qseq, qslots, qhi, istate, wave_stats;
+  HostBuf run_out, status, tables, h_states, h_len, h_nodes;
   // non-backtracking walk counts per width (3, 4, 5), start cell and length:
   // the device table (d_walks) and its host copy
   const int32_t* d_walks = nullptr;
   WalkTable h_walks = make_walk_table();
-  DevBuf treew, tree_offw, widths, byte_off;
+  DevBuf treew;
   DevBuf h2d_states, out_len, out_nodes, out_path;
   // path reconstruction: current states, moves left, previous moves, probes
   DevBuf p_cur, p_left, p_prev, p_probe, p_limit, p_forbid, p_len, p_nodes, p_status, p_err;
@@ -162,7 +193,8 @@ int depth_for(const Options& O) {
 }
 
 int run_batched(const uint8_t* d_states, int n, int32_t* d_len, uint64_t* d_nodes, hipStream_t st,
-                const Options& O, int width = 4, const int32_t* h_widths = nullptr);
+                const Options& O, int width = 4, const int32_t* h_widths = nullptr,
+                int32_t* h_len = nullptr, uint64_t* h_nodes = nullptr);
 
 // The plain BPIDA* driver (Alg. 1 as printed: one search launch per f-limit
 // and instance, one root per workgroup, no dynamic balancing).  All buffers
@@ -391,7 +423,10 @@ struct BatchPlan {
   int64_t tree_nodes = 0, stride = 0, seed_chunks = 0, grid = 0;
   uint64_t qcap = 64;       // queue slots (a power of two)
   uint64_t qwant = 64;      // the default queue size (queue_capacity option, or sized from the batch)
-  std::vector<int64_t> toff, boff;  // mixed widths: split-tree and byte offsets per instance
+  // mixed widths: split-tree and byte offsets and width per instance, in
+  // pinned memory that the launch before the search reads
+  int64_t *toff = nullptr, *boff = nullptr;
+  int32_t* widths = nullptr;
 };
 
 // Device buffers of one batched solve.
@@ -405,9 +440,6 @@ struct BatchBufs {
   uint64_t* qhi = nullptr;  // 5x5 high words (any5 only)
   InstState* istate = nullptr;
   RunStats* wave_stats = nullptr;
-  int32_t* widths = nullptr;    // mixed widths only
-  int64_t* byte_off = nullptr;  // mixed widths only
-  int64_t* tree_offw = nullptr; // mixed widths only
 };
 
 int plan_batched(int n, int width, const int32_t* h_widths, const Options& O, int num_cu,
@@ -430,20 +462,22 @@ int plan_batched(int n, int width, const int32_t* h_widths, const Options& O, in
     P->tree_nodes = P->stride * n;
     P->seed_chunks = (int64_t)n * ((mr + kQChunk - 1) / kQChunk);
   } else {
-    P->toff.assign((size_t)n, 0);
-    P->boff.assign((size_t)n, 0);
-    int64_t bytes = 0;
+    if (g_ws.tables.ensure(20 * (size_t)n) != hipSuccess) return BPIDA_ENOMEM;
+    P->toff = g_ws.tables.as<int64_t>();
+    P->boff = P->toff + n;
+    P->widths = (int32_t*)(P->boff + n);
+    int64_t bytes = 0, sw[3], mr[3];
+    for (int w = 3; w <= 5; ++w) tree_size(W, w, P->D, &sw[w - 3], &mr[w - 3]);
     for (int i = 0; i < n; ++i) {
       const int w = h_widths[i];
       if (w < 3 || w > 5 || !ring_fits(w, P->cap, P->npl)) return BPIDA_EINVAL;
       P->any5 = P->any5 || w == 5;
-      int64_t sw = 0, mr = 0;
-      tree_size(W, w, P->D, &sw, &mr);
+      P->widths[i] = w;
       P->toff[i] = P->tree_nodes;
       P->boff[i] = bytes;
-      P->tree_nodes += sw;
+      P->tree_nodes += sw[w - 3];
       bytes += (int64_t)w * w;
-      P->seed_chunks += (mr + kQChunk - 1) / kQChunk;
+      P->seed_chunks += (mr[w - 3] + kQChunk - 1) / kQChunk;
     }
   }
   P->grid = (int64_t)per_cu * num_cu;
@@ -485,11 +519,6 @@ size_t carve_batched(uintptr_t base, const BatchPlan& P, BatchBufs* B) {
   B->qhi = P.any5 ? (uint64_t*)take(sizeof(uint64_t) * kQChunk * P.qcap) : nullptr;
   B->istate = (InstState*)take(sizeof(InstState) * n);
   B->wave_stats = (RunStats*)take(sizeof(RunStats) * (size_t)(P.grid * P.wpg));
-  if (!P.toff.empty()) {
-    B->widths = (int32_t*)take(sizeof(int32_t) * n);
-    B->byte_off = (int64_t*)take(sizeof(int64_t) * n);
-    B->tree_offw = (int64_t*)take(sizeof(int64_t) * n);
-  }
   return off;
 }
 
@@ -507,11 +536,6 @@ int alloc_batched(const BatchPlan& P, BatchBufs* B) {
       W.istate.ensure(sizeof(InstState) * n) != hipSuccess ||
       W.wave_stats.ensure(sizeof(RunStats) * (size_t)(P.grid * P.wpg)) != hipSuccess)
     return g_no_alloc ? BPIDA_EINVAL : BPIDA_ENOMEM;
-  if (!P.toff.empty() &&
-      (W.widths.ensure(sizeof(int32_t) * n) != hipSuccess ||
-       W.byte_off.ensure(sizeof(int64_t) * n) != hipSuccess ||
-       W.tree_offw.ensure(sizeof(int64_t) * n) != hipSuccess))
-    return g_no_alloc ? BPIDA_EINVAL : BPIDA_ENOMEM;
   B->treew = W.treew.as<NodeW>();
   B->hist = W.hist.as<uint32_t>();
   B->goal_g = W.goal_g.as<int32_t>();
@@ -521,23 +545,24 @@ int alloc_batched(const BatchPlan& P, BatchBufs* B) {
   B->qhi = P.any5 ? W.qhi.as<uint64_t>() : nullptr;
   B->istate = W.istate.as<InstState>();
   B->wave_stats = W.wave_stats.as<RunStats>();
-  if (!P.toff.empty()) {
-    B->widths = W.widths.as<int32_t>();
-    B->byte_off = W.byte_off.as<int64_t>();
-    B->tree_offw = W.tree_offw.as<int64_t>();
-  }
   return BPIDA_OK;
 }
 
+// Where a call that waits finds what it returns (all pinned): null members
+// are left out.
+struct HostOut {
+  RunOut* out = nullptr;
+  int32_t* len = nullptr;
+  uint64_t* nodes = nullptr;
+};
+
 // Enqueues the whole batched solve of plan P on `st` into buffers B;
-// per-instance status (1 solved, < 0 bpida_status) lands in d_status.  No
-// host synchronisation and no copy to the host except the mixed-width
-// tables: the sequence can be recorded into a HIP graph.  `walks` is the
-// device walk-count table.
+// per-instance status (1 solved, < 0 bpida_status) lands in status (device or
+// pinned).  Three launches, no host synchronisation and no copy: the sequence
+// can be recorded into a HIP graph.  `walks` is the device walk-count table.
 int enqueue_batched_into(const uint8_t* d_states, int32_t* d_len, uint64_t* d_nodes,
-                         int32_t* d_status, hipStream_t st, const Options& O, const BatchPlan& P,
-                         const BatchBufs& B, const int32_t* walks, const int32_t* h_widths,
-                         hipEvent_t ev0, hipEvent_t ev1, int wall_khz,
+                         int32_t* status, hipStream_t st, const Options& O, const BatchPlan& P,
+                         const BatchBufs& B, const int32_t* walks, int wall_khz, const HostOut& H,
                          const int32_t* exact_limit = nullptr, const uint8_t* root_forbid = nullptr) {
   hipError_t e;
 #define HIPCHK(x)              \
@@ -550,12 +575,6 @@ int enqueue_batched_into(const uint8_t* d_states, int32_t* d_len, uint64_t* d_no
   } while (0)
   const int n = P.n;
   if (n == 0) return BPIDA_OK;
-  if (h_widths) {
-    HIPCHK(hipMemcpyAsync(B.widths, h_widths, sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(B.byte_off, P.boff.data(), sizeof(int64_t) * (size_t)n, hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(B.tree_offw, P.toff.data(), sizeof(int64_t) * (size_t)n, hipMemcpyHostToDevice, st));
-  }
-
   BatchArgs A;
   memset(&A, 0, sizeof A);
   A.q = B.qctl;
@@ -585,27 +604,35 @@ int enqueue_batched_into(const uint8_t* d_states, int32_t* d_len, uint64_t* d_no
   A.exact_limit = exact_limit;
   PrepArgs R;
   R.states = d_states;
-  R.byte_off = h_widths ? B.byte_off : nullptr;
-  R.widths = h_widths ? B.widths : nullptr;
-  R.tree_off = h_widths ? B.tree_offw : nullptr;
+  R.byte_off = P.boff;
+  R.widths = P.widths;
+  R.tree_off = P.toff;
   R.forbid = root_forbid;
   R.walks = walks;
   R.stride = P.stride;
   R.width = P.width;
   R.depth = P.D;
   HIPCHK(launch_batch_prep(A, R, st));
-  if (ev0) HIPCHK(hipEventRecord(ev0, st));
   HIPCHK(launch_batch4(P.cap, P.npl, P.wpg, (int)P.grid, A, st));
-  if (ev1) HIPCHK(hipEventRecord(ev1, st));
-  HIPCHK(launch_batch_status(A.is, n, A.q, d_status, st));
-  // (counters are read by the synchronous calls only, which are the timed ones)
-  if (ev1) HIPCHK(launch_run_stats(B.wave_stats, (int)(P.grid * P.wpg), A.q, st));
+  FinishArgs F;
+  F.is = A.is;
+  F.n = n;
+  F.q = A.q;
+  F.status = status;
+  F.out = H.out;
+  F.wave_stats = B.wave_stats;
+  F.waves = (int32_t)(P.grid * P.wpg);
+  F.host_len = H.len;
+  F.host_nodes = H.nodes;
+  F.len = d_len;
+  F.nodes = d_nodes;
+  HIPCHK(launch_batch_finish(F, st));
   return BPIDA_OK;
 #undef HIPCHK
 }
 
 int enqueue_batched(const uint8_t* d_states, int n, int32_t* d_len, uint64_t* d_nodes,
-                    int32_t* d_status, hipStream_t st, const Options& O, bool timed,
+                    int32_t* status, hipStream_t st, const Options& O, const HostOut& H,
                     int64_t* grid_out, int width = 4, const int32_t* h_widths = nullptr) {
   Workspace& W = g_ws;
   if (n == 0) return map_err(launch_fill_outputs(d_len, d_nodes, n, st));
@@ -617,13 +644,13 @@ int enqueue_batched(const uint8_t* d_states, int n, int32_t* d_len, uint64_t* d_
   if (rc != BPIDA_OK) return rc;
   W.qcap = P.qcap;
   *grid_out = P.grid;
-  return enqueue_batched_into(d_states, d_len, d_nodes, d_status, st, O, P, B, W.d_walks, h_widths,
-                              timed ? W.ev0 : nullptr, timed ? W.ev1 : nullptr, W.wall_khz);
+  return enqueue_batched_into(d_states, d_len, d_nodes, status, st, O, P, B, W.d_walks, W.wall_khz, H);
 }
 
-// The batched driver: enqueue, then wait and read the status back.
+// The batched driver: enqueue, then wait and read what the last launch left
+// in pinned memory.
 int run_batched(const uint8_t* d_states, int n, int32_t* d_len, uint64_t* d_nodes, hipStream_t st,
-                const Options& O, int width, const int32_t* h_widths) {
+                const Options& O, int width, const int32_t* h_widths, int32_t* h_len, uint64_t* h_nodes) {
   Workspace& W = g_ws;
   uint64_t stats[kStats] = {0};
   hipError_t e;
@@ -640,34 +667,40 @@ int run_batched(const uint8_t* d_states, int n, int32_t* d_len, uint64_t* d_node
     return BPIDA_OK;
   }
   HIPCHK(W.status.ensure(sizeof(int32_t) * (size_t)n));
+  HIPCHK(W.run_out.ensure(sizeof(RunOut)));
+  HostOut H;
+  H.out = W.run_out.as<RunOut>();
+  H.len = h_len;
+  H.nodes = h_nodes;
   int64_t grid = 0;
-  int rc0 = enqueue_batched(d_states, n, d_len, d_nodes, W.status.as<int32_t>(), st, O, true, &grid,
+  int rc0 = enqueue_batched(d_states, n, d_len, d_nodes, W.status.as<int32_t>(), st, O, H, &grid,
                             width, h_widths);
-  if (rc0 != BPIDA_OK) return rc0;
-  std::vector<int32_t> status((size_t)n);
-  QueueCtl qc;
-  HIPCHK(hipMemcpyAsync(status.data(), W.status.p, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost, st));
-  HIPCHK(hipMemcpyAsync(&qc, W.qctl.p, sizeof(QueueCtl), hipMemcpyDeviceToHost, st));
+  if (rc0 != BPIDA_OK) {
+    (void)hipStreamSynchronize(st);  // pinned buffers may be in use by what was launched
+    return rc0;
+  }
   HIPCHK(hipStreamSynchronize(st));
-  float ms = 0.f;
-  if (hipEventElapsedTime(&ms, W.ev0, W.ev1) == hipSuccess) stats[4] = (uint64_t)(ms * 1000.0f);
-  stats[0] = qc.stats.rounds;
-  stats[1] = qc.stats.searched;
-  stats[2] = qc.stats.pushes * kQChunk;
+  const RunStats& s = H.out->sum;
+  const uint64_t per_us = (uint64_t)std::max(1, W.wall_khz / 1000);
+  stats[0] = s.rounds;
+  stats[1] = s.searched;
+  stats[2] = s.pushes * kQChunk;
   stats[3] = 1;
-  stats[6] = qc.stats.pushes;
-  stats[7] = qc.stats.pops;
-  stats[8] = qc.stats.t_work / (uint64_t)std::max(1, W.wall_khz / 1000);  // microseconds
-  stats[9] = qc.stats.t_queue / (uint64_t)std::max(1, W.wall_khz / 1000);
-  stats[10] = qc.stats.t_idle / (uint64_t)std::max(1, W.wall_khz / 1000);
-  stats[11] = qc.stats.voluntary;
-  stats[5] = qc.stats.qmax;
+  stats[4] = (s.t_last - s.t_first) / per_us;
+  stats[6] = s.pushes;
+  stats[7] = s.pops;
+  stats[8] = s.t_work / per_us;
+  stats[9] = s.t_queue / per_us;
+  stats[10] = s.t_idle / per_us;
+  stats[11] = s.voluntary;
+  stats[5] = s.qmax;
   stats[12] = (uint64_t)grid;
-  stats[13] = (uint64_t)(uint32_t)qc.err;
+  stats[13] = (uint64_t)(uint32_t)H.out->err;
   stats[14] = W.qcap;
-  stats[16] = qc.stats.roots_read;
-  stats[17] = qc.stats.chunks_read_wide;
+  stats[16] = s.roots_read;
+  stats[17] = s.chunks_read_wide;
   memcpy(g_stats, stats, sizeof stats);
+  const int32_t* status = W.status.as<int32_t>();
   int rc = BPIDA_OK;
   for (int i = 0; i < n && rc == BPIDA_OK; ++i)
     if (status[i] != 1) rc = status[i];
@@ -730,8 +763,8 @@ int run_paths(const uint8_t* d_states, int n, int width, int32_t* d_len, uint64_
                              width, W.p_probe.as<uint8_t>(), W.p_limit.as<int32_t>(),
                              W.p_forbid.as<uint8_t>(), st));
     prc = enqueue_batched_into(W.p_probe.as<uint8_t>(), W.p_len.as<int32_t>(), W.p_nodes.as<uint64_t>(),
-                               W.p_status.as<int32_t>(), st, Op, P, B, W.d_walks, nullptr, nullptr,
-                               nullptr, W.wall_khz, W.p_limit.as<int32_t>(), W.p_forbid.as<uint8_t>());
+                               W.p_status.as<int32_t>(), st, Op, P, B, W.d_walks, W.wall_khz, HostOut{},
+                               W.p_limit.as<int32_t>(), W.p_forbid.as<uint8_t>());
     if (prc != BPIDA_OK) return prc;
     HIPCHK(launch_path_select(W.p_probe.as<uint8_t>(), W.p_status.as<int32_t>(), d_len, n, nn,
                               W.p_cur.as<uint8_t>(), W.p_left.as<int32_t>(), W.p_prev.as<uint8_t>(),
@@ -756,6 +789,48 @@ int check_opts(int width) {
 
 using namespace bpida;
 
+namespace bpida {
+namespace {
+
+// A host-buffer solve: `bytes` of states, one width (h_widths null) or mixed.
+int solve_host(const uint8_t* states, size_t bytes, size_t n, int width, const int32_t* h_widths, const Options& O,
+               int32_t* out_len, uint64_t* out_nodes) {
+  Workspace& W = g_ws;
+  hipStream_t st = nullptr;
+  if (W.out_len.ensure(n * sizeof(int32_t)) != hipSuccess ||
+      W.out_nodes.ensure(n * BPIDA_MAX_THRESHOLDS * sizeof(uint64_t)) != hipSuccess)
+    return BPIDA_ENOMEM;
+  if (n <= kPinnedInstances && O.mode == kModeBatched && W.h_states.ensure(bytes) == hipSuccess &&
+      W.h_len.ensure(n * sizeof(int32_t)) == hipSuccess &&
+      W.h_nodes.ensure(n * BPIDA_MAX_THRESHOLDS * sizeof(uint64_t)) == hipSuccess) {
+    // (no values of an earlier call: one refused before its launches returns
+    // what the device buffers would hold, nothing solved)
+    memset(W.h_len.p, 0xFF, n * sizeof(int32_t));
+    memset(W.h_nodes.p, 0, n * BPIDA_MAX_THRESHOLDS * sizeof(uint64_t));
+    memcpy(W.h_states.p, states, bytes);
+    const int rc = run_batched(W.h_states.as<uint8_t>(), (int)n, W.out_len.as<int32_t>(), W.out_nodes.as<uint64_t>(),
+                               st, O, width, h_widths, W.h_len.as<int32_t>(), W.h_nodes.as<uint64_t>());
+    memcpy(out_len, W.h_len.p, n * sizeof(int32_t));
+    memcpy(out_nodes, W.h_nodes.p, n * BPIDA_MAX_THRESHOLDS * sizeof(uint64_t));
+    return rc;
+  }
+  if (W.h2d_states.ensure(bytes) != hipSuccess) return BPIDA_ENOMEM;
+  if (hipMemcpyAsync(W.h2d_states.p, states, bytes, hipMemcpyHostToDevice, st) != hipSuccess) return BPIDA_EDEVICE;
+  const int rc = h_widths ? run_batched(W.h2d_states.as<uint8_t>(), (int)n, W.out_len.as<int32_t>(),
+                                        W.out_nodes.as<uint64_t>(), st, O, 0, h_widths)
+                          : run_plain(W.h2d_states.as<uint8_t>(), (int)n, W.out_len.as<int32_t>(),
+                                      W.out_nodes.as<uint64_t>(), st, O, width);
+  if (hipMemcpyAsync(out_len, W.out_len.p, n * sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess ||
+      hipMemcpyAsync(out_nodes, W.out_nodes.p, n * BPIDA_MAX_THRESHOLDS * sizeof(uint64_t), hipMemcpyDeviceToHost,
+                     st) != hipSuccess ||
+      hipStreamSynchronize(st) != hipSuccess)
+    return BPIDA_EDEVICE;
+  return rc;
+}
+
+}  // namespace
+}  // namespace bpida
+
 extern "C" int bpida_solve(const uint8_t* states, int32_t n_instances, int32_t width,
                            int32_t* out_len, uint64_t* out_nodes_per_threshold) {
   try {
@@ -767,22 +842,8 @@ extern "C" int bpida_solve(const uint8_t* states, int32_t n_instances, int32_t w
     if (n == 0) return BPIDA_OK;
     int rc = ensure_device();
     if (rc != BPIDA_OK) return rc;
-    Workspace& W = g_ws;
-    hipStream_t st = nullptr;
-    const size_t bytes = n * (size_t)width * (size_t)width;
-    if (W.h2d_states.ensure(bytes) != hipSuccess || W.out_len.ensure(n * sizeof(int32_t)) != hipSuccess ||
-        W.out_nodes.ensure(n * BPIDA_MAX_THRESHOLDS * sizeof(uint64_t)) != hipSuccess)
-      return BPIDA_ENOMEM;
-    if (hipMemcpyAsync(W.h2d_states.p, states, bytes, hipMemcpyHostToDevice, st) != hipSuccess)
-      return BPIDA_EDEVICE;
-    rc = run_plain(W.h2d_states.as<uint8_t>(), (int)n, W.out_len.as<int32_t>(),
-                   W.out_nodes.as<uint64_t>(), st, O, width);
-    if (hipMemcpyAsync(out_len, W.out_len.p, n * sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipMemcpyAsync(out_nodes_per_threshold, W.out_nodes.p, n * BPIDA_MAX_THRESHOLDS * sizeof(uint64_t),
-                       hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-      return BPIDA_EDEVICE;
-    return rc;
+    return solve_host(states, n * (size_t)width * (size_t)width, n, width, nullptr, O, out_len,
+                      out_nodes_per_threshold);
   } catch (const std::bad_alloc&) {
     return BPIDA_ENOMEM;
   } catch (...) {
@@ -862,21 +923,7 @@ extern "C" int bpida_solve_mixed(const uint8_t* states, const int32_t* widths, i
     if (n == 0) return BPIDA_OK;
     int rc = ensure_device();
     if (rc != BPIDA_OK) return rc;
-    Workspace& W = g_ws;
-    hipStream_t st = nullptr;
-    if (W.h2d_states.ensure(bytes) != hipSuccess || W.out_len.ensure(n * sizeof(int32_t)) != hipSuccess ||
-        W.out_nodes.ensure(n * BPIDA_MAX_THRESHOLDS * sizeof(uint64_t)) != hipSuccess)
-      return BPIDA_ENOMEM;
-    if (hipMemcpyAsync(W.h2d_states.p, states, bytes, hipMemcpyHostToDevice, st) != hipSuccess)
-      return BPIDA_EDEVICE;
-    rc = run_batched(W.h2d_states.as<uint8_t>(), (int)n, W.out_len.as<int32_t>(),
-                     W.out_nodes.as<uint64_t>(), st, O, 0, widths);
-    if (hipMemcpyAsync(out_len, W.out_len.p, n * sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipMemcpyAsync(out_nodes_per_threshold, W.out_nodes.p, n * BPIDA_MAX_THRESHOLDS * sizeof(uint64_t),
-                       hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-      return BPIDA_EDEVICE;
-    return rc;
+    return solve_host(states, bytes, n, 0, widths, O, out_len, out_nodes_per_threshold);
   } catch (const std::bad_alloc&) {
     return BPIDA_ENOMEM;
   } catch (...) {
@@ -937,6 +984,7 @@ struct Server {
   ServerHostCtl* host = nullptr;
   ServerReq* req = nullptr;
   ServerRes* res = nullptr;
+  HostBuf out;  // RunOut of the last run
   std::vector<uint8_t> collected;
   uint64_t tail = 0, min_uncollected = 0;
   DevBuf qctl, qseq, qslots, istate, tree, hist, goal_g, out_len, out_nodes, busy, ticket, admitter,
@@ -1007,6 +1055,7 @@ extern "C" int bpida_server_start(int32_t width, int32_t max_inflight, int32_t r
         V.busy.ensure(sizeof(int32_t) * S) != hipSuccess ||
         V.ticket.ensure(sizeof(uint64_t) * S) != hipSuccess ||
         V.wave_stats.ensure(sizeof(RunStats) * (size_t)(grid * wpg)) != hipSuccess ||
+        V.out.ensure(sizeof(RunOut)) != hipSuccess ||
         V.admitter.ensure(sizeof(int32_t)) != hipSuccess || V.inflight.ensure(sizeof(int32_t)) != hipSuccess)
       return BPIDA_ENOMEM;
     const unsigned fl = hipHostMallocCoherent | hipHostMallocMapped;
@@ -1070,10 +1119,16 @@ extern "C" int bpida_server_start(int32_t width, int32_t max_inflight, int32_t r
     A.srv.admitter = V.admitter.as<int32_t>();
     A.srv.in_flight = V.inflight.as<int32_t>();
     A.srv.backlog_max = O.admit_backlog < 0 ? (int64_t)(qcap / 2) : O.admit_backlog;
+    FinishArgs F;
+    memset(&F, 0, sizeof F);
+    F.q = A.q;
+    F.out = V.out.as<RunOut>();
+    F.wave_stats = A.wave_stats;
+    F.waves = (int32_t)(grid * wpg);
     if (launch_zero_words(V.qctl.p, sizeof(QueueCtl), V.stream) != hipSuccess ||
         launch_server_setup(A, V.stream) != hipSuccess ||
         launch_batch4(cap, npl, wpg, (int)grid, A, V.stream) != hipSuccess ||
-        launch_run_stats(A.wave_stats, (int)(grid * wpg), A.q, V.stream) != hipSuccess) {
+        launch_batch_finish(F, V.stream) != hipSuccess) {
       (void)hipGetLastError();
       return BPIDA_EDEVICE;
     }
@@ -1126,27 +1181,26 @@ extern "C" int bpida_server_stop(void) {
     Server& V = g_srv;
     if (!V.running) return BPIDA_EINVAL;
     __atomic_store_n(&V.host->stop, 1, __ATOMIC_RELEASE);
-    QueueCtl qc;
-    if (hipStreamSynchronize(V.stream) != hipSuccess ||
-        hipMemcpy(&qc, V.qctl.p, sizeof(QueueCtl), hipMemcpyDeviceToHost) != hipSuccess) {
+    if (hipStreamSynchronize(V.stream) != hipSuccess) {
       (void)hipGetLastError();
       V.running = false;
       return BPIDA_EDEVICE;
     }
     V.running = false;
+    const RunOut& R = *V.out.as<RunOut>();
     uint64_t stats[kStats] = {0};
-    stats[0] = qc.stats.rounds;
-    stats[1] = qc.stats.searched;
-    stats[2] = qc.stats.pushes * kQChunk;
+    stats[0] = R.sum.rounds;
+    stats[1] = R.sum.searched;
+    stats[2] = R.sum.pushes * kQChunk;
     stats[3] = 1;
-    stats[6] = qc.stats.pushes;
-    stats[7] = qc.stats.pops;
-    stats[11] = qc.stats.voluntary;
+    stats[6] = R.sum.pushes;
+    stats[7] = R.sum.pops;
+    stats[11] = R.sum.voluntary;
     stats[12] = (uint64_t)V.grid;
-    stats[13] = (uint64_t)(uint32_t)qc.err;
+    stats[13] = (uint64_t)(uint32_t)R.err;
     memcpy(g_stats, stats, sizeof stats);
-    if (qc.err & kErrFatal) return BPIDA_ENOMEM;
-    if (qc.err) return BPIDA_EINTERNAL;
+    if (R.err & kErrFatal) return BPIDA_ENOMEM;
+    if (R.err) return BPIDA_EINTERNAL;
     return BPIDA_OK;
   } catch (...) {
     return BPIDA_EINTERNAL;
@@ -1174,7 +1228,7 @@ extern "C" int bpida_solve_device_async(const uint8_t* d_states, int32_t n_insta
     int64_t grid = 0;
     Options Ob = O;
     Ob.mode = kModeBatched;
-    rc = enqueue_batched(d_states, n_instances, d_len, d_nodes, d_status, st, Ob, false, &grid, width);
+    rc = enqueue_batched(d_states, n_instances, d_len, d_nodes, d_status, st, Ob, HostOut{}, &grid, width);
     g_no_alloc = false;
     return rc;
   } catch (const std::bad_alloc&) {
@@ -1401,7 +1455,7 @@ extern "C" int bpida_solve_device_noalloc(const uint8_t* d_states, int32_t n_ins
     if (carve_batched(0, P, &B) > (size_t)BPIDA_NOALLOC_SCRATCH_BYTES) return BPIDA_ENOMEM;
     carve_batched((uintptr_t)D.ptr, P, &B);
     return enqueue_batched_into(d_states, d_len, d_nodes, d_status, (hipStream_t)hip_stream, O, P, B,
-                                D.walks, nullptr, nullptr, nullptr, D.wall_khz);
+                                D.walks, D.wall_khz, HostOut{});
   } catch (const std::bad_alloc&) {
     return BPIDA_ENOMEM;
   } catch (...) {

@@ -240,6 +240,7 @@ struct RunStats {
   uint64_t qmax;                     // most chunks queued at once (seen at every 8th push; a maximum)
   uint64_t roots_read;               // split-tree roots read while seeding limits
   uint64_t chunks_read_wide;         // 5x5 chunks taken (their high words read too)
+  uint64_t t_first, t_last;          // wall-clock ticks at the start (a minimum) and the end (a maximum)
 };
 constexpr int kRunStats = sizeof(RunStats) / 8;
 
@@ -253,7 +254,6 @@ struct QueueCtl {
   alignas(128) int32_t err;  // 1: queue full while seeding, 2: entries dropped,
                              // 4: idle watchdog, 8: deadline passed, 16: ring full
   alignas(128) int32_t fed;  // a look at head and tail found no waiting wave; cleared by one that waits
-  alignas(128) RunStats stats;  // summed over the waves after the search
 };
 
 // ---------------------------------------------------------------------------
@@ -345,9 +345,25 @@ struct PrepArgs {
 };
 hipError_t launch_batch_prep(const BatchArgs& A, const PrepArgs& P, hipStream_t s);
 hipError_t launch_batch4(int lds_cap, int npl, int wpg, int grid, const BatchArgs& A, hipStream_t s);
-hipError_t launch_batch_status(const InstState* d_is, int n, const QueueCtl* d_q, int32_t* d_status, hipStream_t s);
-// Sums `waves` records into q->stats.
-hipError_t launch_run_stats(const RunStats* d_wave_stats, int waves, QueueCtl* d_q, hipStream_t s);
+// What the launch after the search leaves for the host.
+struct RunOut {
+  RunStats sum;
+  int32_t err;  // QueueCtl::err
+};
+struct FinishArgs {
+  const InstState* is;         // null (server): no statuses
+  int32_t n;
+  const QueueCtl* q;
+  int32_t* status;
+  RunOut* out;                 // null: no counters (may be pinned host memory, as the three below)
+  const RunStats* wave_stats;
+  int32_t waves;
+  int32_t* host_len;           // null, or copies of the outputs for the host
+  uint64_t* host_nodes;
+  const int32_t* len;
+  const uint64_t* nodes;
+};
+hipError_t launch_batch_finish(const FinishArgs& F, hipStream_t s);
 int batch4_max_blocks_per_cu(int lds_cap, int npl, int wpg);
 
 // Path reconstruction by exact-limit probes (bpida_path.hip).

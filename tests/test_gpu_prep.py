@@ -61,3 +61,29 @@ def test_status_mixed_widths(opts):
     order = rng.permutation(len(states))
     rc, ln, nd = B.solve_mixed_raw([states[k] for k in order])
     assert rc == want[order][0] and (ln == -1).all() and not nd.any()
+
+
+@pytest.mark.parametrize("n", [1, 4095, 4096, 4097])
+def test_host_buffers_around_the_pinned_size(opts, n):
+    """Host-buffer calls pass up to 4096 instances through pinned memory and
+    copy larger batches: easy states against the oracle, one invalid among
+    them, and a second, smaller call on the same buffers."""
+    from oracle import oracle
+    from paper_1705_02843_amd import instances as I
+    B = opts
+    set_mode(B, "batched")
+    rng = np.random.Generator(np.random.PCG64(n))
+    base = np.stack([I.random_walk(rng, 4, k % 17)[0] for k in range(64)])
+    states = base[np.arange(n) % 64].copy()
+    want = oracle.solve(base, 4, nthreads=8)
+    if n > 1:
+        states[n // 2, 0] = states[n // 2, 1]
+    for m in (n, (n + 1) // 2):
+        rc, ln, nd = B.solve_raw(states[:m])
+        k = np.arange(m)
+        ok = np.ones(m, bool)
+        if n > 1 and n // 2 < m:
+            ok[n // 2] = False
+        assert rc == (B.OK if ok.all() else B.EINVAL)
+        assert (ln[ok] == want.length[k[ok] % 64]).all() and (nd[ok] == want.nodes[k[ok] % 64]).all()
+        assert (ln[~ok] == -1).all() and not nd[~ok].any()
