@@ -1237,7 +1237,7 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
     release_unit(u.inst, u.limit, expanded, goals, fmin, st, sm, u, wc);
   }
   wc.t_last = wall_clock64();
-  if (lane == 0) A.wave_stats[blockIdx.x * WPG + (WPG == 1 ? 0 : threadIdx.x >> 6)] = wc;
+  if (lane == 0 && A.wave_stats) A.wave_stats[blockIdx.x * WPG + (WPG == 1 ? 0 : threadIdx.x >> 6)] = wc;
 }
 
 // ---------------------------------------------------------------------------

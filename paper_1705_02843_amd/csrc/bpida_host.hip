@@ -518,7 +518,7 @@ size_t carve_batched(uintptr_t base, const BatchPlan& P, BatchBufs* B) {
   B->qslots = (QChunk*)take(sizeof(QChunk) * P.qcap);
   B->qhi = P.any5 ? (uint64_t*)take(sizeof(uint64_t) * kQChunk * P.qcap) : nullptr;
   B->istate = (InstState*)take(sizeof(InstState) * n);
-  B->wave_stats = (RunStats*)take(sizeof(RunStats) * (size_t)(P.grid * P.wpg));
+  B->wave_stats = nullptr;  // (this call reports no counters, and its memory is for the batch)
   return off;
 }
 

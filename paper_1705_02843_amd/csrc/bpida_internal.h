@@ -309,7 +309,7 @@ struct BatchArgs {
   const int32_t* goal_g;
   int32_t* out_len;
   uint64_t* out_nodes;  // n x 64
-  RunStats* wave_stats; // per wave of the grid
+  RunStats* wave_stats; // per wave of the grid (null: not wanted)
   int32_t n;
   int32_t max_limit;
   uint64_t idle_ticks;   // an idle workgroup gives up after this many wall-clock ticks
