@@ -118,51 +118,90 @@ struct Unit {
   int count = 0, inst = 0, kind = 0, limit = 0, width = 0;
 };
 
-// Returns false if the ring stayed full for the whole bounded wait (the
-// entries were not queued).  `hi` goes to the slot's row of A.hi.
-__device__ __forceinline__ bool q_push(const Unit& u, RunStats& wc) {
+// Work of instance i that had been added to its outstanding units could not be
+// queued: takes `units` of them back and marks the instance's counts void.
+__device__ __forceinline__ void drop_units(int i, int units, int err) {
+  Args& A = fresh();
+  if (lane_id() == 0) {
+    st_relaxed(&A.is[i].lost, 1);
+    atomicOr(&A.q->err, err);
+    performed();
+    __hip_atomic_fetch_add(&A.is[i].outstanding, -units, __ATOMIC_RELAXED, AGENT);
+  }
+}
+
+// lane / parts for parts 1, 3 and 7 (lane below 64).
+__device__ __forceinline__ uint32_t lane_over(uint32_t lane, int parts) {
+  return parts == 1 ? lane : (lane * (parts == 3 ? 21846u : 9363u)) >> 16;
+}
+constexpr bool check_lane_over() {
+  for (uint32_t l = 0; l < 64; ++l)
+    if (((l * 21846u) >> 16) != l / 3 || ((l * 9363u) >> 16) != l / 7) return false;
+  return true;
+}
+static_assert(check_lane_over(), "lane division");
+
+// Pushes the unit's entries as `parts` (1, 3 or 7) chunks, entry j to chunk j
+// modulo parts.  One part: returns false if the ring stayed full for the whole
+// bounded wait (the entries were not queued).  Several parts cost what one
+// does, and go to waves that wait; a part that a full ring refuses all the
+// same is dropped, its instance's counts void.
+__device__ __forceinline__ bool q_push(const Unit& u, RunStats& wc, int parts = 1) {
   Args& A = fresh();
   const int lane = lane_id();
   QueueCtl* q = A.q;
   const uint64_t mask = A.qmask;
   uint64_t pos = 0, depth = 0;
-  int ok = 0;
   if (lane == 0) {
-    pos = __hip_atomic_fetch_add(&q->tail, (uint64_t)1, __ATOMIC_RELAXED, AGENT);
+    pos = __hip_atomic_fetch_add(&q->tail, (uint64_t)parts, __ATOMIC_RELAXED, AGENT);
     if ((pos & 7) == 0) {  // (the line of `head` is busy with takes)
       const uint64_t h = ld_relaxed(&q->head);
       if (pos + 1 > h) depth = pos + 1 - h;
     }
-    SlotCtl* sc = A.seq + (pos & mask);
-    for (int k = 0; k < A.push_spin; ++k) {
-      const uint64_t v = ld_relaxed(&sc->seq);
-      if (v == 4 * pos) {
-        ok = cas64(&sc->seq, 4 * pos, 4 * pos + 1) ? 1 : 0;
-        break;
-      }
-      if (v > 4 * pos) break;  // handed on past this ticket by its consumer
-      __builtin_amdgcn_s_sleep(1);
-    }
-    if (!ok) {
-      __hip_atomic_fetch_max(&sc->abandoned, pos + 1, __ATOMIC_RELAXED, AGENT);
-      atomicOr(&q->err, 16);  // ticket lost: the call reports BPIDA_ENOMEM
-    }
   }
-  ok = wave_bcast(ok);
-  wc.qmax = max(wc.qmax, bcast64(depth));
-  if (!ok) return false;
   pos = bcast64(pos);
-  QChunk* c = A.slots + (pos & mask);
-  st_relaxed(&c->tiles[lane], u.tile);
-  if (u.kind & kChunkWide) st_relaxed(&A.hi[(pos & mask) * kQChunk + lane], u.hi);
-  st_relaxed(&c->meta[lane], u.meta);
-  if (lane == 0) {
+  const bool head = lane < parts;  // lane c looks after chunk c
+  const uint64_t my = pos + (uint64_t)(head ? lane : 0);
+  SlotCtl* sc = A.seq + (my & mask);
+  bool ok = false, open = head;
+  for (int k = 0; k < A.push_spin; ++k) {
+    if (open) {
+      const uint64_t v = ld_relaxed(&sc->seq);
+      if (v == 4 * my) {
+        ok = cas64(&sc->seq, 4 * my, 4 * my + 1);
+        open = false;
+      } else if (v > 4 * my) {
+        open = false;  // handed on past this ticket by its consumer
+      }
+    }
+    if (!__builtin_amdgcn_ballot_w64(open)) break;
+    __builtin_amdgcn_s_sleep(1);
+  }
+  if (head && !ok) {
+    __hip_atomic_fetch_max(&sc->abandoned, my + 1, __ATOMIC_RELAXED, AGENT);
+    atomicOr(&q->err, 16);  // ticket lost: the call reports BPIDA_ENOMEM
+  }
+  const uint64_t okm = __builtin_amdgcn_ballot_w64(ok);
+  wc.qmax = max(wc.qmax, bcast64(depth));
+  if (parts == 1 && okm == 0) return false;
+  const uint32_t row = lane_over((uint32_t)lane, parts), part = (uint32_t)lane - row * (uint32_t)parts;
+  if (lane < u.count && ((okm >> part) & 1ull)) {
+    const uint64_t slot = (pos + part) & mask;
+    st_relaxed(&A.slots[slot].tiles[row], u.tile);
+    if (u.kind & kChunkWide) st_relaxed(&A.hi[slot * kQChunk + row], u.hi);
+    st_relaxed(&A.slots[slot].meta[row], u.meta);
+  }
+  if (ok) {
+    QChunk* c = A.slots + (my & mask);
+    const int count = (int)lane_over((uint32_t)(u.count - lane + parts - 1), parts);
     st_relaxed(&c->inst, (int32_t)u.inst);
-    st_relaxed(&c->info, (int32_t)(u.count | (u.kind << 8) | (u.width << 16)));
+    st_relaxed(&c->info, (int32_t)(count | (u.kind << 8) | (u.width << 16)));
     st_relaxed(&c->limit, (int32_t)u.limit);
   }
   performed();  // the payload, and the atomics on the instance before it, come first
-  if (lane == 0) st_relaxed(&A.seq[pos & mask].seq, 4 * pos + 2);
+  if (ok) st_relaxed(&sc->seq, 4 * my + 2);
+  const int lost = parts - (int)__popcll(okm);
+  if (lost) drop_units(u.inst, lost, 2);
   return true;
 }
 
@@ -238,17 +277,6 @@ __device__ __forceinline__ void end_search() {
 // Limit bookkeeping, executed by one wave.
 // ---------------------------------------------------------------------------
 
-// Work of instance i that had been added to its outstanding units could not be
-// queued: takes the unit back and marks the instance's counts void.
-__device__ __forceinline__ void drop_unit(int i) {
-  Args& A = fresh();
-  if (lane_id() == 0) {
-    __hip_atomic_fetch_add(&A.is[i].outstanding, -1, __ATOMIC_RELAXED, AGENT);
-    st_relaxed(&A.is[i].lost, 1);
-    atomicOr(&A.q->err, 1);
-  }
-}
-
 // Hands the roots of instance i with f <= L out as chunks: the last one stays
 // with the caller (`mine`: it is searched next, or pushed), the others go to
 // the queue.  A guard unit keeps the limit from completing meanwhile; it
@@ -257,8 +285,15 @@ __device__ __forceinline__ void drop_unit(int i) {
 // must complete the limit itself.
 // `stage` (128 u64) and `stage_m` (64 u16) are LDS the caller does not use
 // while seeding (its LDS stack is empty whenever a limit is seeded).
-__device__ __forceinline__ bool seed_limit(int i, int L, uint64_t* stage, uint16_t* stage_m, Unit& mine,
-                           RunStats& wc) {
+// `nodes`: what the limit before it expanded (0: the first).  A limit that
+// will keep one wave busy for long (the next one expands some four times the
+// nodes) is dealt out at once to the waves that wait: every 64 roots go to 2,
+// 4 or 8 of them (this wave among them for the last), 8192 nodes' worth each
+// at least.  Against one wave that donates from its 32nd round on: one hard
+// state 1.25 -> 1.14 ms, 64 easy ones 562 -> 525 us; at half these counts the
+// easy ones take 3 % longer.
+__device__ __forceinline__ bool seed_limit(int i, int L, uint64_t nodes, uint64_t* stage, uint16_t* stage_m,
+                                           Unit& mine, RunStats& wc) {
   Args& A = fresh();
   const int lane = lane_id();
   InstState* S = A.is + i;
@@ -271,6 +306,13 @@ __device__ __forceinline__ bool seed_limit(int i, int L, uint64_t* stage, uint16
   const int nroots = (A.first_solution && A.goal_g[i] <= L) ? 0 : S->nroots;
   int fm = INT_MAX;
   bool full = false;
+  int parts = 0;  // chunks dealt out beside this wave's own
+  if (nodes >= 4096) {
+    int64_t ht = 0;
+    if (lane == 0) ht = (int64_t)(ld_relaxed(&A.q->head) - ld_relaxed(&A.q->tail));
+    const int wait = wave_bcast((int)ht);
+    parts = wait >= 7 && nodes >= 16384 ? 7 : wait >= 3 && nodes >= 8192 ? 3 : wait >= 1 ? 1 : 0;
+  }
   mine.count = 0;
   mine.inst = i;
   mine.limit = L;
@@ -305,19 +347,34 @@ __device__ __forceinline__ bool seed_limit(int i, int L, uint64_t* stage, uint16
     // per workgroup, so the whole grid has work from the start
     const int sc = A.seed_chunk > 0 ? A.seed_chunk : kQChunk;
     for (int p0 = 0; p0 < cnt && !full; p0 += sc) {
-      if (mine.count) {
-        if (lane == 0) __hip_atomic_fetch_add(&S->outstanding, 1, __ATOMIC_RELAXED, AGENT);
-        full = !q_push(mine, wc);
+      const int n = min(sc, cnt - p0);
+      const bool deal = n > parts && parts > 0;
+      // entry e of the chunk stays if e is a multiple of parts + 1
+      const int stride = deal ? parts + 1 : 1;
+      const int keep = deal ? (int)((uint32_t)(n + parts) / (uint32_t)stride) : n;
+      auto from_stage = [&](int e, int count) {
+        const bool on = lane < count;
+        mine.count = count;
+        mine.tile = on ? stage[p0 + e] : 0ull;
+        mine.hi = on ? stage[64 + p0 + e] : 0ull;
+        mine.meta = on ? stage_m[p0 + e] : (uint16_t)0;
+      };
+      // first the chunk kept so far, then what this one deals out
+#pragma unroll 1
+      for (int turn = mine.count ? 0 : 1; turn < (deal ? 2 : 1) && !full; ++turn) {
+        const int k = turn ? parts : 1;
+        if (turn) {
+          const uint32_t row = lane_over((uint32_t)lane, parts);
+          from_stage((int)(row * (uint32_t)stride + 1 + ((uint32_t)lane - row * (uint32_t)parts)), n - keep);
+        }
+        if (lane == 0) __hip_atomic_fetch_add(&S->outstanding, k, __ATOMIC_RELAXED, AGENT);
+        full = !q_push(mine, wc, k);
       }
-      mine.count = min(sc, cnt - p0);
-      const bool on = lane < mine.count;
-      mine.tile = on ? stage[p0 + lane] : 0ull;
-      mine.hi = on ? stage[64 + p0 + lane] : 0ull;
-      mine.meta = on ? stage_m[p0 + lane] : (uint16_t)0;
+      if (!full) from_stage(lane * stride, keep);
     }
     WAVE_SYNC();
   }
-  if (full) drop_unit(i);  // the remaining roots are dropped; the call reports BPIDA_ENOMEM
+  if (full) drop_units(i, 1, 1);  // the remaining roots are dropped; the call reports BPIDA_ENOMEM
   fm = wave_min(fm);
   if (lane == 0 && fm != INT_MAX) __hip_atomic_fetch_min(&S->fmin, fm, __ATOMIC_RELAXED, AGENT);
   wc.roots_read += (uint64_t)nroots;
@@ -383,8 +440,9 @@ __device__ __forceinline__ void complete_limit(int i, int L, uint64_t* stage, ui
     fm = wave_min(fm);
     int state = 0;  // 0: advance, 1: solved, <0: error code
     int left = 1;
+    const uint64_t total = searched + interior;
     if (lane == 0) {
-      st_relaxed(&A.out_nodes[(size_t)i * 64 + col], searched + interior);
+      st_relaxed(&A.out_nodes[(size_t)i * 64 + col], total);
       const int fnext = min(fm, fsearch);
       if (lost) {
         state = -4;  // BPIDA_ENOMEM: work of this limit was dropped, its counts are void
@@ -417,7 +475,7 @@ __device__ __forceinline__ void complete_limit(int i, int L, uint64_t* stage, ui
       return;
     }
     L += 2;
-    if (!seed_limit(i, L, stage, stage_m, mine, wc)) return;
+    if (!seed_limit(i, L, total, stage, stage_m, mine, wc)) return;
   }
 }
 
@@ -540,7 +598,7 @@ __device__ __forceinline__ void admit_limit(int i, int L, uint64_t* st, uint16_t
   Args& A = fresh();
   Unit mine;
   RunStats wc = {};  // (the admitter's own counts are not reported)
-  if (seed_limit(i, L, st, sm, mine, wc)) complete_limit(i, L, st, sm, mine, wc);
+  if (seed_limit(i, L, 0, st, sm, mine, wc)) complete_limit(i, L, st, sm, mine, wc);
   while (mine.count && !q_push(mine, wc)) {
     // lost: this was the instance's last unit unless other chunks are out
     int last = 0;
@@ -728,12 +786,12 @@ struct NodeStack {
     sm[i] = e.m;
   }
   // (u: the unit's instance and limit)
-  __device__ __forceinline__ bool push(Unit u, Entry e, int count, RunStats& wc) const {
+  __device__ __forceinline__ bool push(Unit u, Entry e, int count, RunStats& wc, int parts = 1) const {
     u.tile = e.s;
     u.meta = e.m;
     u.kind = kChunkNodes;
     u.count = count;
-    return q_push(u, wc);
+    return q_push(u, wc, parts);
   }
   __device__ __forceinline__ uint32_t round(uint32_t top, int kp, int& goals, int& fmin) {
     return bp_round<CAP>(st, sm, top, kp, limit, M, goals, fmin);
@@ -766,12 +824,12 @@ struct RingStack {
       : st((Entry*)lds), k(make_ring_consts<W>((char*)lds, kTable)) {}
   __device__ __forceinline__ Entry get(uint32_t i) const { return st[i]; }
   __device__ __forceinline__ void put(uint32_t i, Entry e) { st[i] = e; }
-  __device__ __forceinline__ bool push(Unit u, Entry e, int count, RunStats& wc) const {
+  __device__ __forceinline__ bool push(Unit u, Entry e, int count, RunStats& wc, int parts = 1) const {
     u.tile = (uint64_t)e.r | ((uint64_t)e.c << 32);
     u.meta = (uint16_t)ring_pack(e.m);
     u.kind = kChunkRing;
     u.count = count;
-    return q_push(u, wc);
+    return q_push(u, wc, parts);
   }
   __device__ __forceinline__ uint32_t round(uint32_t top, int kp, int& goals, int&) {
     uint64_t gm = 0;
@@ -827,14 +885,14 @@ struct RingStack<5, CAP> {
   __device__ __forceinline__ RingStack(uint64_t* lds) : st((Entry*)lds), k(make_r5_consts((char*)lds, kTable)) {}
   __device__ __forceinline__ Entry get(uint32_t i) const { return st[i]; }
   __device__ __forceinline__ void put(uint32_t i, Entry e) { st[i] = e; }
-  __device__ __forceinline__ bool push(Unit u, Entry e, int count, RunStats& wc) const {
+  __device__ __forceinline__ bool push(Unit u, Entry e, int count, RunStats& wc, int parts = 1) const {
     const unsigned __int128 s = r5_board(e.s, (e.m >> 4) & 31u);
     u.tile = (uint64_t)s;
     u.hi = (uint64_t)(s >> 64);
     u.meta = (uint16_t)r5_pack(e.m);
     u.kind = kChunkRing | kChunkWide;
     u.count = count;
-    return q_push(u, wc);
+    return q_push(u, wc, parts);
   }
   __device__ __forceinline__ uint32_t round(uint32_t top, int kp, int& goals, int&) {
     uint64_t gm = 0;
@@ -958,20 +1016,23 @@ __device__ __forceinline__ bool run_unit(const Unit& u, ST& S, uint32_t top, Run
         clk.next_look = tick + (uint32_t)max((int)kLookMin, (int)((float)(waves - wait) * look_share));
         const int dmin = wait > waves - wait ? dlow : dhigh;
         if (wait > 0 && avail >= dmin) {
-          const int w = min(avail, A.donate_window) & ~1;
-          const int h = w >> 1;
+          const int parts = avail >= 64 && wait >= 15 * (waves - wait) ? 3 : 1;
+          const int w = min(avail, parts == 1 ? A.donate_window : 64 + 64 / parts);
+          const int keep_n = (int)((uint32_t)(w + parts) / (uint32_t)(parts + 1)), h = w - keep_n;
           // (positions up to 127: inside the stack's storage, read for every lane)
-          const Entry give = S.get(2 * lane), keep = S.get(2 * lane + 1);
+          const uint32_t row = lane_over((uint32_t)lane, parts);
+          const Entry give = S.get(row * (uint32_t)(parts + 1) + 1 + ((uint32_t)lane - row * (uint32_t)parts));
+          const Entry keep = S.get(min((uint32_t)lane * (uint32_t)(parts + 1), 127u));
           WAVE_SYNC();
-          if (lane == 0) __hip_atomic_fetch_add(&A.is[inst].outstanding, 1, __ATOMIC_RELAXED, AGENT);
-          if (S.push(u, give, h, wc)) {
-            wc.pushes += 1;
+          if (lane == 0) __hip_atomic_fetch_add(&A.is[inst].outstanding, parts, __ATOMIC_RELAXED, AGENT);
+          if (S.push(u, give, h, wc, parts)) {
+            wc.pushes += (uint64_t)parts;
             wc.voluntary += 1;
-            // the kept half becomes the bottom, the entries above the window
-            // close up behind it
-            if (lane < h) S.put(lane, keep);
+            // the kept entries become the bottom, those above the window
+            // close up behind them
+            if (lane < keep_n) S.put(lane, keep);
             WAVE_SYNC();
-            stack_down(S, (uint32_t)h, (uint32_t)w, top - (uint32_t)w);
+            stack_down(S, (uint32_t)keep_n, (uint32_t)w, top - (uint32_t)w);
             top -= (uint32_t)h;
             avail -= h;
           } else if (lane == 0) {
@@ -1140,9 +1201,9 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
       if (wave_bcast(left) == 0) end_search();
       continue;
     }
-    if (u.count && !q_push(u, wc)) drop_unit(u.inst);
+    if (u.count && !q_push(u, wc)) drop_units(u.inst, 1, 1);
     const int L = A.is[i].limit;
-    if (seed_limit(i, L, st, sm, u, wc)) complete_limit(i, L, st, sm, u, wc);
+    if (seed_limit(i, L, 0, st, sm, u, wc)) complete_limit(i, L, st, sm, u, wc);
   }
 
   uint64_t t_mark = wall_clock64();
