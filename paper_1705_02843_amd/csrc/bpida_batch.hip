@@ -292,12 +292,13 @@ __device__ __forceinline__ void end_search() {
 // at least.  Against one wave that donates from its 32nd round on: one hard
 // state 1.25 -> 1.14 ms, 64 easy ones 562 -> 525 us; at half these counts the
 // easy ones take 3 % longer.
+template <int W>
 __device__ __forceinline__ bool seed_limit(int i, int L, uint64_t nodes, uint64_t* stage, uint16_t* stage_m,
                                            Unit& mine, RunStats& wc) {
   Args& A = fresh();
   const int lane = lane_id();
   InstState* S = A.is + i;
-  const int width = S->width;
+  const int width = W ? W : S->width;
   const bool wide = width == 5;
   if (lane == 0) st_relaxed(&S->outstanding, 1);
   const NodeW* roots = A.tree + S->root_off;
@@ -412,6 +413,7 @@ __device__ __forceinline__ void emit_result(int i, int status) {
 // wave observed it), then advances it.  Loops while a new limit has no work;
 // the new limit's last chunk is left in `mine` (count 0: the instance is
 // done).
+template <int W>
 __device__ __forceinline__ void complete_limit(int i, int L, uint64_t* stage, uint16_t* stage_m, Unit& mine,
                            RunStats& wc) {
   Args& A = fresh();
@@ -475,7 +477,7 @@ __device__ __forceinline__ void complete_limit(int i, int L, uint64_t* stage, ui
       return;
     }
     L += 2;
-    if (!seed_limit(i, L, total, stage, stage_m, mine, wc)) return;
+    if (!seed_limit<W>(i, L, total, stage, stage_m, mine, wc)) return;
   }
 }
 
@@ -598,7 +600,7 @@ __device__ __forceinline__ void admit_limit(int i, int L, uint64_t* st, uint16_t
   Args& A = fresh();
   Unit mine;
   RunStats wc = {};  // (the admitter's own counts are not reported)
-  if (seed_limit(i, L, 0, st, sm, mine, wc)) complete_limit(i, L, st, sm, mine, wc);
+  if (seed_limit<4>(i, L, 0, st, sm, mine, wc)) complete_limit<4>(i, L, st, sm, mine, wc);
   while (mine.count && !q_push(mine, wc)) {
     // lost: this was the instance's last unit unless other chunks are out
     int last = 0;
@@ -610,7 +612,7 @@ __device__ __forceinline__ void admit_limit(int i, int L, uint64_t* st, uint16_t
     }
     L = mine.limit;
     mine.count = 0;
-    if (wave_bcast(last)) complete_limit(i, L, st, sm, mine, wc);
+    if (wave_bcast(last)) complete_limit<4>(i, L, st, sm, mine, wc);
   }
 }
 
@@ -726,6 +728,7 @@ __device__ __forceinline__ void admitter_loop(uint64_t* st, uint16_t* sm, uint64
 // Adds this wave's counts for the unit of instance i it held at limit L and
 // releases the unit; completes the limit if it was the last unit, which may
 // leave the next limit's chunk in `mine`.
+template <int W>
 __device__ __forceinline__ void release_unit(int i, int L, uint64_t expanded, int goals, int fmin,
                              uint64_t* stage, uint16_t* stage_m, Unit& mine,
                            RunStats& wc) {
@@ -742,7 +745,7 @@ __device__ __forceinline__ void release_unit(int i, int L, uint64_t expanded, in
   performed();  // the counts are in before the unit is gone
   int last = 0;
   if (lane == 0) last = __hip_atomic_fetch_add(&S->outstanding, -1, __ATOMIC_RELAXED, AGENT) == 1;
-  if (wave_bcast(last)) complete_limit(i, L, stage, stage_m, mine, wc);
+  if (wave_bcast(last)) complete_limit<W>(i, L, stage, stage_m, mine, wc);
 }
 
 // ---------------------------------------------------------------------------
@@ -1148,7 +1151,7 @@ constexpr int ring5_cap() {
   return (CAP * 10 - (int)kR5Table - kCounterBytes) / 28 / 16 * 16;
 }
 
-template <int CAP, int NPL, int WPG, bool FS>
+template <int CAP, int NPL, int WPG, bool FS, int W>
 __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void batch4_kernel(BatchArgs) {
   Args& A = fresh();
   static_assert(CAP % 16 == 0 && (NPL == 64 || (CAP & (CAP - 1)) == 0), "stack size");
@@ -1165,7 +1168,7 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
   const int lane = lane_id();
   QueueCtl* q = A.q;
 
-  if (A.server) {
+  if (W == 0 && A.server) {
     int role = 0;
     if (lane == 0) role = atomicCAS(A.srv.admitter, 0, 1) == 0;
     if (wave_bcast(role)) {
@@ -1203,7 +1206,7 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
     }
     if (u.count && !q_push(u, wc)) drop_units(u.inst, 1, 1);
     const int L = A.is[i].limit;
-    if (seed_limit(i, L, 0, st, sm, u, wc)) complete_limit(i, L, st, sm, u, wc);
+    if (seed_limit<W>(i, L, 0, st, sm, u, wc)) complete_limit<W>(i, L, st, sm, u, wc);
   }
 
   uint64_t t_mark = wall_clock64();
@@ -1266,20 +1269,21 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
     uint64_t expanded = 0;
     int goals = 0, fmin = INT_MAX;
     bool ok = true;
-    if (u.width == 5) {
+    if (W ? W == 5 : u.width == 5) {
       // (smaller stacks take no 5x5 batch: the host refuses it)
-      if constexpr (CAP / 2 >= 512) {
+      if constexpr (CAP / 2 >= 512 && (W == 0 || W == 5)) {
         RingStack<5, ring5_cap<CAP>()> S(st);
         const uint32_t top = S.load(u, expanded, goals);
         ok = run_unit<RingStack<5, ring5_cap<CAP>()>, FS>(u, S, top, wc, clk, deadline, expanded, goals, fmin);
       }
-    } else if (u.width == 3) {
-      if constexpr (CAP >= 256) {
+    } else if (W ? W == 3 : u.width == 3) {
+      if constexpr (CAP >= 256 && (W == 0 || W == 3)) {
         RingStack<3, ring_cap<CAP>()> S(st);
         const uint32_t top = S.load(u, expanded, goals);
         ok = run_unit<RingStack<3, ring_cap<CAP>()>, FS>(u, S, top, wc, clk, deadline, expanded, goals,
                                                          fmin);
       }
+    } else if constexpr (W == 3 || W == 5) {
     } else if constexpr (NPL == 64) {
       RingStack<4, ring_cap<CAP>()> S(st);
       const uint32_t top = S.load(u, expanded, goals);
@@ -1295,7 +1299,7 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
     wc.t_work += now - t_mark;
     t_mark = now;
     wc.searched += expanded;
-    release_unit(u.inst, u.limit, expanded, goals, fmin, st, sm, u, wc);
+    release_unit<W>(u.inst, u.limit, expanded, goals, fmin, st, sm, u, wc);
   }
   wc.t_last = wall_clock64();
   if (lane == 0 && A.wave_stats) A.wave_stats[blockIdx.x * WPG + (WPG == 1 ? 0 : threadIdx.x >> 6)] = wc;
@@ -1585,14 +1589,34 @@ hipError_t launch_server_setup(const BatchArgs& A, hipStream_t s) {
 }
 
 // The first-solution search is a kernel of its own: with both unit loops in
-// one kernel the register allocation of each suffers.
-template <int CAP, int NPL, int WPG>
+// one kernel the register allocation of each suffers.  So is, for 64-node
+// rounds of single-wave workgroups, the search of a batch of one width (W; 0:
+// any, by chunk, and the server): with the rounds of all three widths and the
+// admitter in one kernel it is 56 KB of code against 25, and a 640-entry
+// 4x4 stack's wave spills 160 bytes against 60 (batch of 100 hard states 25.8
+// -> 24.0 ms, 3x3 batch of 2048 367 -> 351 us).  The arguments stay within 256
+// bytes: 8 more (with the 256 hidden ones a ninth 64-byte line) made every
+// short search 5 to 10 us longer.
+template <int CAP, int NPL, int WPG, int W>
 static hipError_t launch_batch_t(int grid, const BatchArgs& A, hipStream_t s) {
   if (A.first_solution)
-    hipLaunchKernelGGL((batch4_kernel<CAP, NPL, WPG, true>), dim3(grid), dim3(64 * WPG), 0, s, A);
+    hipLaunchKernelGGL((batch4_kernel<CAP, NPL, WPG, true, W>), dim3(grid), dim3(64 * WPG), 0, s, A);
   else
-    hipLaunchKernelGGL((batch4_kernel<CAP, NPL, WPG, false>), dim3(grid), dim3(64 * WPG), 0, s, A);
+    hipLaunchKernelGGL((batch4_kernel<CAP, NPL, WPG, false, W>), dim3(grid), dim3(64 * WPG), 0, s, A);
   return hipGetLastError();
+}
+
+template <int CAP, int NPL, int WPG>
+static hipError_t launch_batch_w(int width, int grid, const BatchArgs& A, hipStream_t s) {
+  if constexpr (NPL == 64 && WPG == 1) {
+    // (smaller stacks take no batch of that width: the host refuses it)
+    if (width == 3) return launch_batch_t<CAP, NPL, WPG, 3>(grid, A, s);
+    if constexpr (CAP >= 512)
+      if (width == 4) return launch_batch_t<CAP, NPL, WPG, 4>(grid, A, s);
+    if constexpr (CAP >= 1024)
+      if (width == 5) return launch_batch_t<CAP, NPL, WPG, 5>(grid, A, s);
+  }
+  return launch_batch_t<CAP, NPL, WPG, 0>(grid, A, s);
 }
 
 template <int CAP, int NPL, int WPG>
@@ -1602,9 +1626,9 @@ static int occupancy_t() {
   static int known = -1;
   if (known >= 0) return known;
   int nb = 0, nf = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, batch4_kernel<CAP, NPL, WPG, false>, 64 * WPG, 0) !=
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, batch4_kernel<CAP, NPL, WPG, false, 0>, 64 * WPG, 0) !=
           hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&nf, batch4_kernel<CAP, NPL, WPG, true>, 64 * WPG, 0) !=
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&nf, batch4_kernel<CAP, NPL, WPG, true, 0>, 64 * WPG, 0) !=
           hipSuccess)
     return 0;
   known = nb < nf ? nb : nf;  // the grid suits either kernel
@@ -1618,10 +1642,10 @@ static int occupancy_t() {
   X(512, 64, 2) X(1024, 64, 2) X(2048, 64, 2)                                                     \
   X(512, 64, 4) X(1024, 64, 4) X(2048, 64, 4)
 
-hipError_t launch_batch4(int lds_cap, int npl, int wpg, int grid, const BatchArgs& A, hipStream_t s) {
+hipError_t launch_batch4(int lds_cap, int npl, int wpg, int width, int grid, const BatchArgs& A, hipStream_t s) {
   if (grid <= 0) return hipSuccess;
 #define X(C, N, G) \
-  if (lds_cap == C && npl == N && wpg == G) return launch_batch_t<C, N, G>(grid, A, s);
+  if (lds_cap == C && npl == N && wpg == G) return launch_batch_w<C, N, G>(width, grid, A, s);
   BATCH_CONFIGS(X)
 #undef X
   return hipErrorInvalidValue;

@@ -613,7 +613,7 @@ int enqueue_batched_into(const uint8_t* d_states, int32_t* d_len, uint64_t* d_no
   R.width = P.width;
   R.depth = P.D;
   HIPCHK(launch_batch_prep(A, R, st));
-  HIPCHK(launch_batch4(P.cap, P.npl, P.wpg, (int)P.grid, A, st));
+  HIPCHK(launch_batch4(P.cap, P.npl, P.wpg, P.widths ? 0 : P.width, (int)P.grid, A, st));
   FinishArgs F;
   F.is = A.is;
   F.n = n;
@@ -1127,7 +1127,7 @@ extern "C" int bpida_server_start(int32_t width, int32_t max_inflight, int32_t r
     F.waves = (int32_t)(grid * wpg);
     if (launch_zero_words(V.qctl.p, sizeof(QueueCtl), V.stream) != hipSuccess ||
         launch_server_setup(A, V.stream) != hipSuccess ||
-        launch_batch4(cap, npl, wpg, (int)grid, A, V.stream) != hipSuccess ||
+        launch_batch4(cap, npl, wpg, 0, (int)grid, A, V.stream) != hipSuccess ||
         launch_batch_finish(F, V.stream) != hipSuccess) {
       (void)hipGetLastError();
       return BPIDA_EDEVICE;

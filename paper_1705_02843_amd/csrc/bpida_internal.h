@@ -344,7 +344,8 @@ struct PrepArgs {
   int32_t width, depth;
 };
 hipError_t launch_batch_prep(const BatchArgs& A, const PrepArgs& P, hipStream_t s);
-hipError_t launch_batch4(int lds_cap, int npl, int wpg, int grid, const BatchArgs& A, hipStream_t s);
+// width: of every instance (0: several widths, or the server)
+hipError_t launch_batch4(int lds_cap, int npl, int wpg, int width, int grid, const BatchArgs& A, hipStream_t s);
 // What the launch after the search leaves for the host.
 struct RunOut {
   RunStats sum;
