@@ -59,7 +59,7 @@ MODES = {"plain": 0, "batched": 1}
 # The device sources the search kernels are built from (host-side driver
 # code does not change what a kernel launch moves or executes).
 DEVICE_SOURCES = ("bpida_batch.hip", "bpida_board.h", "bpida_internal.h", "bpida_kernels.hip",
-                  "bpida_lb.hip", "bpida_round.h")
+                  "bpida_lb.hip", "bpida_ring.h", "bpida_ring5.h", "bpida_round.h")
 
 
 def kernel_source_hash() -> str:
@@ -425,8 +425,10 @@ def main():
     if cap < 0:
         cap = 1024 if npl == 64 else 512
     if args.mode == "batched":
-        kname = "batch4_kernel<%d, %d, %d, %s>" % (cap, npl, bpida.get_option("wg_size") // 64,
-                                                    "true" if bpida.get_option("first_solution") else "false")
+        waves = bpida.get_option("wg_size") // 64
+        one_width = width if widths is None and npl == 64 and waves == 1 else 0
+        kname = "batch4_kernel<%d, %d, %d, %s, %d>" % (
+            cap, npl, waves, "true" if bpida.get_option("first_solution") else "false", one_width)
     else:
         pn = bpida.get_option("plain_nodes_per_round")
         kname = ("search64_kernel<%d>" if pn == 64 else "search4_kernel<%d>") % cap

@@ -266,8 +266,8 @@ int bpida_server_stop(void);
  *                        entries, batches of thousands of 4x4 instances can
  *                        overflow the default work queue (BPIDA_ENOMEM)
  *   "nodes_per_round"    batched mode: 64 (default) pops one entry per lane
- *                        (3x3, 4x4: each lane makes one move; 5x5: all four);
- *                        16 uses Alg. 1's map
+ *                        (an expanded node, of which each lane makes one
+ *                        move); 16 uses Alg. 1's map
  *                        (lane l expands node l/4 with move l%4).
  *   "wg_size"            batched mode and server: threads per workgroup of the
  *                        persistent kernel, 64 (default), 128 or 256: 1, 2 or
@@ -277,8 +277,8 @@ int bpida_server_stop(void);
  *                        need 64-node rounds and a stack of 512+ entries.
  *                        Results do not depend on it.
  *   "plain_nodes_per_round"
- *                        plain mode: 16 (default, Alg. 1's map) or 64 (the
- *                        batched kernel's round: one node per lane; needs an
+ *                        plain mode: 16 (default, Alg. 1's map) or 64 (one
+ *                        node per lane, which makes all four moves; needs an
  *                        LDS stack of at least 512 entries, default 1024)
  *   "spill_capacity"     plain mode: per-workgroup HBM spill entries, a
  *                        multiple of 64 (default 16384)
