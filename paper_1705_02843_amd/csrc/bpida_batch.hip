@@ -48,6 +48,14 @@ __device__ __forceinline__ Args& fresh() {
   asm("" : "+s"(p));
   return *p;
 }
+// (where BatchArgs::server is set only)
+using Srv = const __attribute__((address_space(4))) ServerArgs;
+__device__ __forceinline__ Srv& fresh_server() {
+  using All = const __attribute__((address_space(4))) ServerBatchArgs;
+  All* p = (All*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm("" : "+s"(p));
+  return p->srv;
+}
 
 __device__ __forceinline__ uint64_t ld_relaxed(uint64_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, AGENT);
@@ -391,7 +399,7 @@ __device__ __forceinline__ bool seed_limit(int i, int L, uint64_t nodes, uint64_
 __device__ __forceinline__ void emit_result(int i, int status) {
   Args& A = fresh();
   const int lane = lane_id();
-  const auto& V = A.srv;
+  Srv& V = fresh_server();
   WAVE_SYNC_MEM();  // the slot's output row, written by lane 0, is visible
   const uint64_t t = V.ticket[i];
   ServerRes* r = V.res + (t & V.ring_mask);
@@ -620,7 +628,7 @@ __device__ __forceinline__ void admit_limit(int i, int L, uint64_t* st, uint16_t
 __device__ __forceinline__ void admitter_loop(uint64_t* st, uint16_t* sm, uint64_t deadline) {
   Args& A = fresh();
   const int lane = lane_id();
-  const auto& V = A.srv;
+  Srv& V = fresh_server();
   QueueCtl* q = A.q;
   uint32_t* hist_lds = (uint32_t*)st;  // the stack is unused by the admitter
   uint64_t head = 0;
@@ -1152,7 +1160,8 @@ constexpr int ring5_cap() {
 }
 
 template <int CAP, int NPL, int WPG, bool FS, int W>
-__global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void batch4_kernel(BatchArgs) {
+__global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>()))
+void batch4_kernel(std::conditional_t<W == 0, ServerBatchArgs, BatchArgs>) {
   Args& A = fresh();
   static_assert(CAP % 16 == 0 && (NPL == 64 || (CAP & (CAP - 1)) == 0), "stack size");
   static_assert(NPL == 16 || NPL == 64, "nodes per round");
@@ -1170,7 +1179,7 @@ __global__ __launch_bounds__(64 * WPG, (batch_waves_per_simd<CAP, NPL>())) void 
 
   if (W == 0 && A.server) {
     int role = 0;
-    if (lane == 0) role = atomicCAS(A.srv.admitter, 0, 1) == 0;
+    if (lane == 0) role = atomicCAS(fresh_server().admitter, 0, 1) == 0;
     if (wave_bcast(role)) {
       admitter_loop(st, sm, wall_clock64() + A.budget_ticks);
       RunStats none = {};
@@ -1568,23 +1577,23 @@ hipError_t launch_batch_prep(const BatchArgs& A, const PrepArgs& P, hipStream_t 
 
 // Server set-up: queue sequence numbers, free instance slots, one sentinel in
 // `remaining` (cleared by the admitter when the server shuts down).
-__global__ void server_setup_kernel(BatchArgs A) {
+__global__ void server_setup_kernel(BatchArgs A, ServerArgs V) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k <= (int64_t)A.qmask) {
     A.seq[k].seq = 4 * (uint64_t)k;
     A.seq[k].abandoned = 0;
   }
-  if (k < A.srv.slots) A.srv.busy[k] = 0;
+  if (k < V.slots) V.busy[k] = 0;
   if (k == 0) {
     A.q->remaining = 1;
-    *A.srv.admitter = 0;
-    *A.srv.in_flight = 0;
+    *V.admitter = 0;
+    *V.in_flight = 0;
   }
 }
 
-hipError_t launch_server_setup(const BatchArgs& A, hipStream_t s) {
-  const int64_t work = std::max<int64_t>((int64_t)A.qmask + 1, A.srv.slots);
-  hipLaunchKernelGGL(server_setup_kernel, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, s, A);
+hipError_t launch_server_setup(const BatchArgs& A, const ServerArgs& V, hipStream_t s) {
+  const int64_t work = std::max<int64_t>((int64_t)A.qmask + 1, V.slots);
+  hipLaunchKernelGGL(server_setup_kernel, dim3((unsigned)((work + 255) / 256)), dim3(256), 0, s, A, V);
   return hipGetLastError();
 }
 
@@ -1594,20 +1603,24 @@ hipError_t launch_server_setup(const BatchArgs& A, hipStream_t s) {
 // any, by chunk, and the server): with the rounds of all three widths and the
 // admitter in one kernel it is 56 KB of code against 25, and a 640-entry
 // 4x4 stack's wave spills 160 bytes against 60 (batch of 100 hard states 25.8
-// -> 24.0 ms, 3x3 batch of 2048 367 -> 351 us).  The arguments stay within 256
-// bytes: 8 more (with the 256 hidden ones a ninth 64-byte line) made every
-// short search 5 to 10 us longer.
+// -> 24.0 ms, 3x3 batch of 2048 367 -> 351 us).  The
+// server's arguments go to the general kernel alone: with them 256 bytes
+// long (and 256 hidden ones), the others' made an easy state from host
+// buffers take 252 us on average against 241, and 264 bytes 5 to 10 us more.
 template <int CAP, int NPL, int WPG, int W>
-static hipError_t launch_batch_t(int grid, const BatchArgs& A, hipStream_t s) {
+static hipError_t launch_batch_t(int grid, const BatchArgs& A, hipStream_t s, const ServerArgs* srv = nullptr) {
+  std::conditional_t<W == 0, ServerBatchArgs, BatchArgs> K;
+  if constexpr (W == 0) K = ServerBatchArgs{A, srv ? *srv : ServerArgs{}};
+  else K = A;
   if (A.first_solution)
-    hipLaunchKernelGGL((batch4_kernel<CAP, NPL, WPG, true, W>), dim3(grid), dim3(64 * WPG), 0, s, A);
+    hipLaunchKernelGGL((batch4_kernel<CAP, NPL, WPG, true, W>), dim3(grid), dim3(64 * WPG), 0, s, K);
   else
-    hipLaunchKernelGGL((batch4_kernel<CAP, NPL, WPG, false, W>), dim3(grid), dim3(64 * WPG), 0, s, A);
+    hipLaunchKernelGGL((batch4_kernel<CAP, NPL, WPG, false, W>), dim3(grid), dim3(64 * WPG), 0, s, K);
   return hipGetLastError();
 }
 
 template <int CAP, int NPL, int WPG>
-static hipError_t launch_batch_w(int width, int grid, const BatchArgs& A, hipStream_t s) {
+static hipError_t launch_batch_w(int width, int grid, const BatchArgs& A, hipStream_t s, const ServerArgs* srv) {
   if constexpr (NPL == 64 && WPG == 1) {
     // (smaller stacks take no batch of that width: the host refuses it)
     if (width == 3) return launch_batch_t<CAP, NPL, WPG, 3>(grid, A, s);
@@ -1616,7 +1629,7 @@ static hipError_t launch_batch_w(int width, int grid, const BatchArgs& A, hipStr
     if constexpr (CAP >= 1024)
       if (width == 5) return launch_batch_t<CAP, NPL, WPG, 5>(grid, A, s);
   }
-  return launch_batch_t<CAP, NPL, WPG, 0>(grid, A, s);
+  return launch_batch_t<CAP, NPL, WPG, 0>(grid, A, s, srv);
 }
 
 template <int CAP, int NPL, int WPG>
@@ -1642,10 +1655,11 @@ static int occupancy_t() {
   X(512, 64, 2) X(1024, 64, 2) X(2048, 64, 2)                                                     \
   X(512, 64, 4) X(1024, 64, 4) X(2048, 64, 4)
 
-hipError_t launch_batch4(int lds_cap, int npl, int wpg, int width, int grid, const BatchArgs& A, hipStream_t s) {
+hipError_t launch_batch4(int lds_cap, int npl, int wpg, int width, int grid, const BatchArgs& A, hipStream_t s,
+                         const ServerArgs* srv) {
   if (grid <= 0) return hipSuccess;
 #define X(C, N, G) \
-  if (lds_cap == C && npl == N && wpg == G) return launch_batch_w<C, N, G>(width, grid, A, s);
+  if (lds_cap == C && npl == N && wpg == G) return launch_batch_w<C, N, G>(width, grid, A, s, srv);
   BATCH_CONFIGS(X)
 #undef X
   return hipErrorInvalidValue;

@@ -1106,19 +1106,20 @@ extern "C" int bpida_server_start(int32_t width, int32_t max_inflight, int32_t r
     A.seed_chunk = sc_srv;
     A.push_spin = (int32_t)O.push_spin;
     A.server = 1;
-    A.srv.host = V.host;
-    A.srv.req = V.req;
-    A.srv.res = V.res;
-    A.srv.ring_mask = ring - 1;
-    A.srv.slots = (int32_t)S;
-    A.srv.depth = D;
-    A.srv.stride = stride;
-    A.srv.busy = V.busy.as<int32_t>();
-    A.srv.ticket = V.ticket.as<uint64_t>();
-    A.srv.walks = W.d_walks + kWalkStride;
-    A.srv.admitter = V.admitter.as<int32_t>();
-    A.srv.in_flight = V.inflight.as<int32_t>();
-    A.srv.backlog_max = O.admit_backlog < 0 ? (int64_t)(qcap / 2) : O.admit_backlog;
+    ServerArgs K;
+    K.host = V.host;
+    K.req = V.req;
+    K.res = V.res;
+    K.ring_mask = ring - 1;
+    K.slots = (int32_t)S;
+    K.depth = D;
+    K.stride = stride;
+    K.busy = V.busy.as<int32_t>();
+    K.ticket = V.ticket.as<uint64_t>();
+    K.walks = W.d_walks + kWalkStride;
+    K.admitter = V.admitter.as<int32_t>();
+    K.in_flight = V.inflight.as<int32_t>();
+    K.backlog_max = O.admit_backlog < 0 ? (int64_t)(qcap / 2) : O.admit_backlog;
     FinishArgs F;
     memset(&F, 0, sizeof F);
     F.q = A.q;
@@ -1126,8 +1127,8 @@ extern "C" int bpida_server_start(int32_t width, int32_t max_inflight, int32_t r
     F.wave_stats = A.wave_stats;
     F.waves = (int32_t)(grid * wpg);
     if (launch_zero_words(V.qctl.p, sizeof(QueueCtl), V.stream) != hipSuccess ||
-        launch_server_setup(A, V.stream) != hipSuccess ||
-        launch_batch4(cap, npl, wpg, 0, (int)grid, A, V.stream) != hipSuccess ||
+        launch_server_setup(A, K, V.stream) != hipSuccess ||
+        launch_batch4(cap, npl, wpg, 0, (int)grid, A, V.stream, &K) != hipSuccess ||
         launch_batch_finish(F, V.stream) != hipSuccess) {
       (void)hipGetLastError();
       return BPIDA_EDEVICE;

@@ -323,11 +323,18 @@ struct BatchArgs {
   const int32_t* exact_limit;  // null, or per instance the one f-limit to search
                                // (status 1: a goal within it, 2: none)
   int32_t push_spin;     // polls of a full slot before a push gives its ticket up
-  int32_t server;        // nonzero: continuous-batching server (srv below)
+  int32_t server;        // nonzero: continuous-batching server (ServerArgs behind these)
+};
+
+// The arguments of the kernel that can serve.  The others take BatchArgs
+// alone: a wave's first read of each line of its arguments is a miss that a
+// short search waits for.
+struct ServerBatchArgs {
+  BatchArgs batch;
   ServerArgs srv;
 };
 
-hipError_t launch_server_setup(const BatchArgs& A, hipStream_t s);
+hipError_t launch_server_setup(const BatchArgs& A, const ServerArgs& V, hipStream_t s);
 // Device address of the walk-count table (a constant-initialised device
 // variable: no allocation).
 hipError_t walk_table_device(const int32_t** out);
@@ -345,7 +352,8 @@ struct PrepArgs {
 };
 hipError_t launch_batch_prep(const BatchArgs& A, const PrepArgs& P, hipStream_t s);
 // width: of every instance (0: several widths, or the server)
-hipError_t launch_batch4(int lds_cap, int npl, int wpg, int width, int grid, const BatchArgs& A, hipStream_t s);
+hipError_t launch_batch4(int lds_cap, int npl, int wpg, int width, int grid, const BatchArgs& A, hipStream_t s,
+                         const ServerArgs* srv = nullptr);
 // What the launch after the search leaves for the host.
 struct RunOut {
   RunStats sum;
