@@ -803,8 +803,7 @@ int solve_host(const uint8_t* states, size_t bytes, size_t n, int width, const i
   if (n <= kPinnedInstances && O.mode == kModeBatched && W.h_states.ensure(bytes) == hipSuccess &&
       W.h_len.ensure(n * sizeof(int32_t)) == hipSuccess &&
       W.h_nodes.ensure(n * BPIDA_MAX_THRESHOLDS * sizeof(uint64_t)) == hipSuccess) {
-    // (no values of an earlier call: one refused before its launches returns
-    // what the device buffers would hold, nothing solved)
+    // (a call refused before its launches returns lengths -1 and counts 0)
     memset(W.h_len.p, 0xFF, n * sizeof(int32_t));
     memset(W.h_nodes.p, 0, n * BPIDA_MAX_THRESHOLDS * sizeof(uint64_t));
     memcpy(W.h_states.p, states, bytes);
@@ -815,7 +814,10 @@ int solve_host(const uint8_t* states, size_t bytes, size_t n, int width, const i
     return rc;
   }
   if (W.h2d_states.ensure(bytes) != hipSuccess) return BPIDA_ENOMEM;
-  if (hipMemcpyAsync(W.h2d_states.p, states, bytes, hipMemcpyHostToDevice, st) != hipSuccess) return BPIDA_EDEVICE;
+  // a refused call returns lengths -1 and counts 0, not an earlier call's
+  if (launch_fill_outputs(W.out_len.as<int32_t>(), W.out_nodes.as<uint64_t>(), (int)n, st) != hipSuccess ||
+      hipMemcpyAsync(W.h2d_states.p, states, bytes, hipMemcpyHostToDevice, st) != hipSuccess)
+    return BPIDA_EDEVICE;
   const int rc = h_widths ? run_batched(W.h2d_states.as<uint8_t>(), (int)n, W.out_len.as<int32_t>(),
                                         W.out_nodes.as<uint64_t>(), st, O, 0, h_widths)
                           : run_plain(W.h2d_states.as<uint8_t>(), (int)n, W.out_len.as<int32_t>(),
@@ -870,7 +872,10 @@ extern "C" int bpida_solve_paths(const uint8_t* states, int32_t n_instances, int
         W.out_nodes.ensure(n * BPIDA_MAX_THRESHOLDS * sizeof(uint64_t)) != hipSuccess ||
         W.out_path.ensure(n * BPIDA_MAX_PATH) != hipSuccess)
       return BPIDA_ENOMEM;
-    if (hipMemcpyAsync(W.h2d_states.p, states, bytes, hipMemcpyHostToDevice, st) != hipSuccess)
+    // a refused call returns lengths -1, counts 0 and no moves, not an earlier call's
+    if (launch_fill_outputs(W.out_len.as<int32_t>(), W.out_nodes.as<uint64_t>(), (int)n, st) != hipSuccess ||
+        hipMemsetAsync(W.out_path.p, 0xFF, n * BPIDA_MAX_PATH, st) != hipSuccess ||
+        hipMemcpyAsync(W.h2d_states.p, states, bytes, hipMemcpyHostToDevice, st) != hipSuccess)
       return BPIDA_EDEVICE;
     rc = run_paths(W.h2d_states.as<uint8_t>(), (int)n, width, W.out_len.as<int32_t>(),
                    W.out_nodes.as<uint64_t>(), W.out_path.as<uint8_t>(), st, O);
