@@ -523,7 +523,10 @@ size_t carve_batched(uintptr_t base, const BatchPlan& P, BatchBufs* B) {
 }
 
 // The buffers of plan P from the library's grow-only workspace.
-int alloc_batched(const BatchPlan& P, BatchBufs* B) {
+// `counters`: the call reports the waves' counters.  One that does not takes no
+// buffer for them: it is the only one whose size follows the grid alone, and a
+// call being captured may allocate nothing.
+int alloc_batched(const BatchPlan& P, bool counters, BatchBufs* B) {
   Workspace& W = g_ws;
   const size_t n = (size_t)P.n;
   if (W.treew.ensure(sizeof(NodeW) * (size_t)P.tree_nodes) != hipSuccess ||
@@ -534,7 +537,7 @@ int alloc_batched(const BatchPlan& P, BatchBufs* B) {
       W.qslots.ensure(sizeof(QChunk) * P.qcap) != hipSuccess ||
       (P.any5 && W.qhi.ensure(sizeof(uint64_t) * kQChunk * P.qcap) != hipSuccess) ||
       W.istate.ensure(sizeof(InstState) * n) != hipSuccess ||
-      W.wave_stats.ensure(sizeof(RunStats) * (size_t)(P.grid * P.wpg)) != hipSuccess)
+      (counters && W.wave_stats.ensure(sizeof(RunStats) * (size_t)(P.grid * P.wpg)) != hipSuccess))
     return g_no_alloc ? BPIDA_EINVAL : BPIDA_ENOMEM;
   B->treew = W.treew.as<NodeW>();
   B->hist = W.hist.as<uint32_t>();
@@ -544,7 +547,7 @@ int alloc_batched(const BatchPlan& P, BatchBufs* B) {
   B->qslots = W.qslots.as<QChunk>();
   B->qhi = P.any5 ? W.qhi.as<uint64_t>() : nullptr;
   B->istate = W.istate.as<InstState>();
-  B->wave_stats = W.wave_stats.as<RunStats>();
+  B->wave_stats = counters ? W.wave_stats.as<RunStats>() : nullptr;
   return BPIDA_OK;
 }
 
@@ -640,7 +643,7 @@ int enqueue_batched(const uint8_t* d_states, int n, int32_t* d_len, uint64_t* d_
   int rc = plan_batched(n, width, h_widths, O, W.num_cu, &P);
   if (rc != BPIDA_OK) return rc;
   BatchBufs B;
-  rc = alloc_batched(P, &B);
+  rc = alloc_batched(P, H.out != nullptr, &B);
   if (rc != BPIDA_OK) return rc;
   W.qcap = P.qcap;
   *grid_out = P.grid;
@@ -756,7 +759,7 @@ int run_paths(const uint8_t* d_states, int n, int width, int32_t* d_len, uint64_
   int prc = plan_batched((int)np, width, nullptr, Op, W.num_cu, &P);
   if (prc != BPIDA_OK) return prc;
   BatchBufs B;
-  prc = alloc_batched(P, &B);
+  prc = alloc_batched(P, false, &B);
   if (prc != BPIDA_OK) return prc;
   for (int step = 0; step < maxlen; ++step) {
     HIPCHK(launch_path_probe(W.p_cur.as<uint8_t>(), W.p_left.as<int32_t>(), W.p_prev.as<uint8_t>(), n,
