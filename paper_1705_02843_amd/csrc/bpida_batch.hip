@@ -285,6 +285,25 @@ __device__ __forceinline__ void end_search() {
 // Limit bookkeeping, executed by one wave.
 // ---------------------------------------------------------------------------
 
+// Chunks of every 64 roots that seed_limit deals out: 7, 3, 1 or 0.  As many
+// waves have to wait on tickets no queued chunk covers, so that what is dealt
+// goes to them and does not fill the queue, which is sized for the chunks of 64
+// roots and for spills.  `budget`: chunks it may deal before it looks again.
+// All waves that search (waves - wait) may deal on the same look, so their
+// budgets add up to 7 chunks a wave of the grid, for which the queue must have
+// room (BatchArgs::deal).  Looked at once a limit, a deep split on a small grid
+// filled its queue, every wave that had to push stopped searching, and the call
+// could end in BPIDA_ENOMEM; looked at before every 64 roots, 100 hard states
+// take 1.5 % longer.
+__device__ __forceinline__ int waiting_parts(uint64_t nodes, int& budget) {
+  Args& A = fresh();
+  int64_t ht = 0;
+  if (lane_id() == 0) ht = (int64_t)(ld_relaxed(&A.q->head) - ld_relaxed(&A.q->tail));
+  const int wait = wave_bcast((int)ht), waves = A.deal;
+  budget = min(wait, (int)(7u * (uint32_t)waves / (uint32_t)max(waves - wait, 1)));
+  return wait >= 7 && nodes >= 16384 ? 7 : wait >= 3 && nodes >= 8192 ? 3 : wait >= 1 ? 1 : 0;
+}
+
 // Hands the roots of instance i with f <= L out as chunks: the last one stays
 // with the caller (`mine`: it is searched next, or pushed), the others go to
 // the queue.  A guard unit keeps the limit from completing meanwhile; it
@@ -315,13 +334,8 @@ __device__ __forceinline__ bool seed_limit(int i, int L, uint64_t nodes, uint64_
   const int nroots = (A.first_solution && A.goal_g[i] <= L) ? 0 : S->nroots;
   int fm = INT_MAX;
   bool full = false;
-  int parts = 0;  // chunks dealt out beside this wave's own
-  if (nodes >= 4096) {
-    int64_t ht = 0;
-    if (lane == 0) ht = (int64_t)(ld_relaxed(&A.q->head) - ld_relaxed(&A.q->tail));
-    const int wait = wave_bcast((int)ht);
-    parts = wait >= 7 && nodes >= 16384 ? 7 : wait >= 3 && nodes >= 8192 ? 3 : wait >= 1 ? 1 : 0;
-  }
+  int budget = 0;
+  int parts = nodes >= 4096 && A.deal ? waiting_parts(nodes, budget) : 0;  // chunks dealt out beside this wave's own
   mine.count = 0;
   mine.inst = i;
   mine.limit = L;
@@ -357,7 +371,9 @@ __device__ __forceinline__ bool seed_limit(int i, int L, uint64_t nodes, uint64_
     const int sc = A.seed_chunk > 0 ? A.seed_chunk : kQChunk;
     for (int p0 = 0; p0 < cnt && !full; p0 += sc) {
       const int n = min(sc, cnt - p0);
+      if (parts > budget) parts = waiting_parts(nodes, budget);
       const bool deal = n > parts && parts > 0;
+      if (deal) budget -= parts;
       // entry e of the chunk stays if e is a multiple of parts + 1
       const int stride = deal ? parts + 1 : 1;
       const int keep = deal ? (int)((uint32_t)(n + parts) / (uint32_t)stride) : n;

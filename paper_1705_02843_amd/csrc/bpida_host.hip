@@ -604,6 +604,7 @@ int enqueue_batched_into(const uint8_t* d_states, int32_t* d_len, uint64_t* d_no
   A.start_limit = (int32_t)O.start_threshold;
   A.seed_chunk = P.sc;
   A.push_spin = (int32_t)O.push_spin;
+  A.deal = P.qcap >= kDealSlots * (uint64_t)(P.grid * P.wpg);
   A.exact_limit = exact_limit;
   PrepArgs R;
   R.states = d_states;
@@ -1114,6 +1115,7 @@ extern "C" int bpida_server_start(int32_t width, int32_t max_inflight, int32_t r
     A.seed_chunk = sc_srv;
     A.push_spin = (int32_t)O.push_spin;
     A.server = 1;
+    A.deal = qcap >= kDealSlots * (uint64_t)(grid * wpg);
     ServerArgs K;
     K.host = V.host;
     K.req = V.req;
