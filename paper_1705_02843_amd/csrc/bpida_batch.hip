@@ -787,10 +787,18 @@ struct RoundClock {
 // map, lane l expands node l/4 with move l%4), RingStack expanded nodes with
 // the moves they have left (one move per lane and round; bpida_ring.h, 5x5:
 // bpida_ring5.h).
+constexpr int kCounterBytes = (sizeof(RunStats) + 15) / 16 * 16;
+// The wave's counters take the last bytes of its 10 * CAP, except behind a
+// 16-node stack too small to miss them, which is not bound by LDS either.
+template <int CAP, int NPL>
+constexpr bool counters_inside() {
+  return NPL == 64 || CAP >= 1024;
+}
+
 template <int CAP>
 struct NodeStack {
   static_assert((CAP & (CAP - 1)) == 0 && CAP >= 128, "stack");
-  static constexpr int kCap = CAP, kNpl = 16;
+  static constexpr int kCap = CAP - (counters_inside<CAP, 16>() ? kCounterBytes / 2 : 0), kNpl = 16;
   // largest growth of one round: a node has at most 3 children (its parent's
   // cell is excluded).  Only a root of the split (depth 0) has no parent and
   // may have 4, and a root is expanded in the unit's first round, which
@@ -822,6 +830,12 @@ struct NodeStack {
   }
   __device__ __forceinline__ uint32_t round(uint32_t top, int kp, int& goals, int& fmin) {
     return bp_round<CAP>(st, sm, top, kp, limit, M, goals, fmin);
+  }
+  __device__ __forceinline__ uint32_t full_round(uint32_t top, uint64_t& gm, int& fmin) {
+    int goals = 0;
+    top = bp_round<CAP>(st, sm, top, kNpl, limit, M, goals, fmin);
+    gm |= (uint64_t)goals;
+    return top;
   }
   __device__ __forceinline__ uint32_t load(const Unit& u, uint64_t&, int&) {
     if (lane_id() < u.count) put((uint32_t)lane_id(), {u.tile, u.meta});
@@ -864,7 +878,7 @@ struct RingStack {
     goals += __popcll(gm);
     return top;
   }
-  __device__ __forceinline__ uint32_t full_round(uint32_t top, uint64_t& gm) {
+  __device__ __forceinline__ uint32_t full_round(uint32_t top, uint64_t& gm, int&) {
     return ring_round<W, kTable, true>(top, 64, gm, k);
   }
 
@@ -927,7 +941,7 @@ struct RingStack<5, CAP> {
     goals += __popcll(gm);
     return top;
   }
-  __device__ __forceinline__ uint32_t full_round(uint32_t top, uint64_t& gm) {
+  __device__ __forceinline__ uint32_t full_round(uint32_t top, uint64_t& gm, int&) {
     return r5_round<kTable, true>(top, 64, gm, k);
   }
   // As RingStack::load.
@@ -1109,21 +1123,22 @@ __device__ __forceinline__ bool run_unit(const Unit& u, ST& S, uint32_t top, Run
       if (poll && wave_bcast(lane == 0 ? ld_relaxed(&A.is[inst].stop) : 0))
         break;
     }
-    if constexpr (kNpl == 64) {
-      // Full rounds with nothing else to test: while the stack holds 64
+    {
+      // Full rounds with nothing else to test: while the stack holds a round's
       // entries and has room for what they leave (the condition under which
-      // the round above needs no spill) and no poll is due, 64-node rounds
+      // the round above needs no spill) and no poll is due, full rounds
       // run back to back; their counts are added once at the end.  The
       // first-solution search also leaves after a round that expanded a goal
       // (a test of the wave's goal mask, uniform), and stops its instance
-      // outside the loop.
+      // outside the loop.  (16-node rounds one at a time: 4096 uneven states
+      // 5.2 s, back to back 3.0 s.)
       const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane(max(min((int)(63u - (tick & 63u)), (int)(clk.next_look - tick) - 1), 0));
       uint32_t r = 0;
-      uint64_t gm = 0;  // lanes that expanded a goal (only "any" matters)
+      uint64_t gm = 0;  // nonzero: a round expanded a goal
       for (;;) {
         if (r >= n) break;
-        if (top - 64u > (uint32_t)(kCap - kGrow - 64)) break;
-        top = S.full_round(top, gm);
+        if (top - (uint32_t)kNpl > (uint32_t)(kCap - kGrow - kNpl)) break;
+        top = S.full_round(top, gm, fmin);
         ++r;
         if constexpr (FS) {
           if (gm != 0) break;
@@ -1131,7 +1146,7 @@ __device__ __forceinline__ bool run_unit(const Unit& u, ST& S, uint32_t top, Run
       }
       if (gm != 0) goals += 1;
       tick += r;
-      expanded += 64ull * r;
+      expanded += (uint64_t)kNpl * r;
       wc.rounds += r;
       if constexpr (FS) {
         if (goals > 0) {
@@ -1159,13 +1174,13 @@ __device__ __forceinline__ bool run_unit(const Unit& u, ST& S, uint32_t top, Run
 //
 // Waves per SIMD a one-wave workgroup's stack allows (LDS: 160 KB per compute
 // unit).  The launch bound keeps the vector registers within that occupancy,
-// capped at 8.
+// capped at 8, for 16-node rounds at 5: left alone the compiler takes 135 to
+// 151 registers there, 3 waves (4096 uneven states 6.4 s at 3 waves, 5.2 s at 5).
 template <int CAP, int NPL>
 constexpr int batch_waves_per_simd() {
-  constexpr int w = NPL != 64 ? 1 : (int)(163840u / (10u * CAP)) / 4;
-  return w > 8 ? 8 : w < 1 ? 1 : w;
+  constexpr int w = (int)(163840u / (10u * CAP)) / 4, most = NPL == 64 ? 8 : 5;
+  return w > most ? most : w < 1 ? 1 : w;
 }
-constexpr int kCounterBytes = (sizeof(RunStats) + 15) / 16 * 16;
 template <int CAP>
 constexpr int ring_cap() {
   return (CAP * 10 - (int)kRingTable - kCounterBytes) / 12 / 16 * 16;
@@ -1183,10 +1198,10 @@ void batch4_kernel(std::conditional_t<W == 0, ServerBatchArgs, BatchArgs>) {
   static_assert(NPL == 16 || NPL == 64, "nodes per round");
   static_assert(NPL == 16 || CAP >= 256, "stack too small for 64-node rounds");
   static_assert(WPG == 1 || WPG == 2 || WPG == 4, "waves per workgroup");
-  // u64 words of one wave's stack, and behind it the wave's counters: in
-  // registers they cost 22 scalar registers the search loop has better uses
+  // u64 words of one wave's stack and counters: in
+  // registers these cost 22 scalar registers the search loop has better uses
   // for (it spilled 40 to 190 vector registers around them)
-  constexpr int kWords = 10 * CAP / 8 + (NPL == 64 ? 0 : kCounterBytes / 8);
+  constexpr int kWords = 10 * CAP / 8 + (counters_inside<CAP, NPL>() ? 0 : kCounterBytes / 8);
   __shared__ __attribute__((aligned(16))) uint64_t lds[WPG * kWords];
   uint64_t* st = lds + (WPG == 1 ? 0 : (int)(threadIdx.x >> 6) * kWords);
   uint16_t* sm = (uint16_t*)(st + CAP);  // staging of the seeds' meta words

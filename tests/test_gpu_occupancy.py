@@ -1,0 +1,45 @@
+"""The search kernels keep the occupancy their stacks allow.
+
+Waves a compute unit, as the persistent grid shows them: 16-node rounds up to
+5 a SIMD, 64-node rounds what the stack's LDS allows, up to 6.  And the 16-node
+rounds' results, first solutions too, against the stored oracle results.
+"""
+import pytest
+
+from test_gpu_first_solution import check_first_solution
+from test_gpu_parity import B, assert_parity, load_golden, opts, set_mode  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("npl,cap,waves", [(16, 128, 20), (16, 256, 20), (16, 512, 20), (16, 1024, 16), (16, 2048, 8),
+                                           (64, 512, 24), (64, 640, 24), (64, 672, 24), (64, 768, 20), (64, 1024, 16)])
+def test_waves_per_compute_unit(opts, npl, cap, waves):
+    import torch
+    B = opts
+    set_mode(B, "batched")
+    print("case: %d-node rounds, %d entries" % (npl, cap), flush=True)
+    states, length, nodes = load_golden("c1_walk40")
+    B.set_option("nodes_per_round", npl)
+    B.set_option("lds_stack_capacity", cap)
+    rc, ln, got = B.solve_raw(states, 4)
+    assert rc == B.OK
+    assert_parity(ln, got, length, nodes)
+    assert B.last_stats()["grid"] >= waves * torch.cuda.get_device_properties(0).multi_processor_count
+
+
+@pytest.mark.parametrize("cap", [128, 512, 1024])
+def test_16_node_rounds_back_to_back(opts, cap):
+    B = opts
+    set_mode(B, "batched16")
+    B.set_option("lds_stack_capacity", cap)
+    states, length, nodes = load_golden("c2_md30_38")
+    states, length, nodes = states[:12], length[:12], nodes[:12]
+    print("case: 12 hard states, %d entries" % cap, flush=True)
+    rc, ln, got = B.solve_raw(states, 4)
+    assert rc == B.OK
+    assert_parity(ln, got, length, nodes)
+    B.set_option("first_solution", 1)
+    rc, ln, got = B.solve_raw(states, 4)
+    assert rc == B.OK
+    check_first_solution(ln, got, length, nodes, "16-node rounds")
