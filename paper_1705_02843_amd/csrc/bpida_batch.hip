@@ -1174,11 +1174,17 @@ __device__ __forceinline__ bool run_unit(const Unit& u, ST& S, uint32_t top, Run
 //
 // Waves per SIMD a one-wave workgroup's stack allows (LDS: 160 KB per compute
 // unit).  The launch bound keeps the vector registers within that occupancy,
-// capped at 8, for 16-node rounds at 5: left alone the compiler takes 135 to
-// 151 registers there, 3 waves (4096 uneven states 6.4 s at 3 waves, 5.2 s at 5).
+// capped at 6, for 16-node rounds at 5.  Those left alone take 135 to 151
+// registers, 3 waves (4096 uneven states 6.4 s at 3 waves, 5.2 s at 5).  256 and
+// 512 entries have room for 8 waves, but at 64 registers a wave spills 37 to
+// 118 of them: at 8 against 6 waves 512 entries take 785 against 670 us for 64
+// easy states (a quarter of the grid, as tuned: 405 against 389), 540 against
+// 480 for 2048 3x3, 2.5 against 2.3 ms for 1000 easy, 33.9 against 32.9 for 100
+// hard; only batches that keep every wave busy gain (777 uneven: 89.7 against
+// 95.7 ms).
 template <int CAP, int NPL>
 constexpr int batch_waves_per_simd() {
-  constexpr int w = (int)(163840u / (10u * CAP)) / 4, most = NPL == 64 ? 8 : 5;
+  constexpr int w = (int)(163840u / (10u * CAP)) / 4, most = NPL == 64 ? 6 : 5;
   return w > most ? most : w < 1 ? 1 : w;
 }
 template <int CAP>

@@ -4,6 +4,7 @@ Waves a compute unit, as the persistent grid shows them: 16-node rounds up to
 5 a SIMD, 64-node rounds what the stack's LDS allows, up to 6.  And the 16-node
 rounds' results, first solutions too, against the stored oracle results.
 """
+import numpy as np
 import pytest
 
 from test_gpu_first_solution import check_first_solution
@@ -26,6 +27,22 @@ def test_waves_per_compute_unit(opts, npl, cap, waves):
     assert rc == B.OK
     assert_parity(ln, got, length, nodes)
     assert B.last_stats()["grid"] >= waves * torch.cuda.get_device_properties(0).multi_processor_count
+
+
+@pytest.mark.parametrize("cap,wg", [(256, 64), (512, 64), (512, 128), (512, 256)])
+def test_small_stacks_keep_their_registers(opts, cap, wg):
+    """256 and 512 entries leave LDS for 8 waves a SIMD, whose registers would be spilled: 6."""
+    import torch
+    B = opts
+    set_mode(B, "batched")
+    print("case: 64-node rounds, %d entries, workgroups of %d" % (cap, wg), flush=True)
+    B.set_option("lds_stack_capacity", cap)
+    B.set_option("wg_size", wg)
+    goal = np.arange(9, dtype=np.uint8)[None]
+    rc, ln, _ = B.solve_raw(goal, 3)
+    assert rc == B.OK and ln[0] == 0
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert B.last_stats()["grid"] * (wg // 64) == 24 * cus
 
 
 @pytest.mark.parametrize("cap", [128, 512, 1024])
