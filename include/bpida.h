@@ -326,7 +326,11 @@ int bpida_server_stop(void);
  *   "queue_chunk"        batched mode: entries per donated chunk, 16, 32 or
  *                        64 (default); a donation splits the oldest
  *                        2 x queue_chunk entries of the donor's stack
- *                        alternately.  Overflow spills always move 64.
+ *                        alternately.  Where at least 15 of 16 workgroups
+ *                        wait, it deals the oldest 4 x queue_chunk, at most
+ *                        85, to four of them, itself included: no chunk has
+ *                        more than queue_chunk.  Overflow spills always
+ *                        move 64.
  *   "donate_min"         batched mode: smallest LDS stack (entries) that
  *                        donates (2..2048; -1 = four rounds' worth of pops,
  *                        at most half the stack: 256 for 64-node rounds, half

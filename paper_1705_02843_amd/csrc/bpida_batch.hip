@@ -138,12 +138,13 @@ __device__ __forceinline__ void drop_units(int i, int units, int err) {
   }
 }
 
-// lane / parts for parts 1, 3 and 7 (lane below 64).
+// lane / parts for parts 1, 3 and 7 (lane below 64, and the counts up to 70
+// that q_push rounds up).
 __device__ __forceinline__ uint32_t lane_over(uint32_t lane, int parts) {
   return parts == 1 ? lane : (lane * (parts == 3 ? 21846u : 9363u)) >> 16;
 }
 constexpr bool check_lane_over() {
-  for (uint32_t l = 0; l < 64; ++l)
+  for (uint32_t l = 0; l <= 70; ++l)
     if (((l * 21846u) >> 16) != l / 3 || ((l * 9363u) >> 16) != l / 7) return false;
   return true;
 }
@@ -987,6 +988,28 @@ __device__ __forceinline__ void stack_down(ST& S, uint32_t dst, uint32_t src, ui
   WAVE_SYNC();
 }
 
+// The oldest entries of a stack of `avail` that a donation to `parts` (1 or 3)
+// waves splits, and how many of them stay: every chunk takes at most the
+// donated chunk's entries (half the two-way window), all together 64, a lane
+// each.
+__host__ __device__ constexpr int donation_window(int avail, int parts, int window) {
+  const int most = parts == 1 ? window : (parts + 1) * (window / 2), lanes = 64 + 64 / parts;
+  const int w = most < lanes ? most : lanes;
+  return avail < w ? avail : w;
+}
+__host__ __device__ constexpr int donation_kept(int w, int parts) { return (w + parts) / (parts + 1); }
+constexpr bool check_donation() {
+  for (int chunk = 16; chunk <= 64; chunk *= 2)
+    for (int parts = 1; parts <= 3; parts += 2)
+      for (int avail = parts == 1 ? 2 : 64; avail <= 256; ++avail) {
+        const int w = donation_window(avail, parts, 2 * chunk), keep = donation_kept(w, parts), give = w - keep;
+        if (w > avail || give < parts || give > 64 || keep < 1 || keep > 64) return false;
+        if (keep > chunk || (give + parts - 1) / parts > chunk) return false;
+      }
+  return true;
+}
+static_assert(check_donation(), "donated chunks");
+
 // Searches one unit (the entries [0, top) of stack S) of an instance until
 // its stack is empty: BPDFS rounds, with spills to the queue when LDS would
 // overflow and donations to waiting workgroups.  Returns false if the time
@@ -1058,8 +1081,8 @@ __device__ __forceinline__ bool run_unit(const Unit& u, ST& S, uint32_t top, Run
         const int dmin = wait > waves - wait ? dlow : dhigh;
         if (wait > 0 && avail >= dmin) {
           const int parts = avail >= 64 && wait >= 15 * (waves - wait) ? 3 : 1;
-          const int w = min(avail, parts == 1 ? A.donate_window : 64 + 64 / parts);
-          const int keep_n = (int)((uint32_t)(w + parts) / (uint32_t)(parts + 1)), h = w - keep_n;
+          const int w = donation_window(avail, parts, A.donate_window);
+          const int keep_n = donation_kept(w, parts), h = w - keep_n;
           // (positions up to 127: inside the stack's storage, read for every lane)
           const uint32_t row = lane_over((uint32_t)lane, parts);
           const Entry give = S.get(row * (uint32_t)(parts + 1) + 1 + ((uint32_t)lane - row * (uint32_t)parts));
