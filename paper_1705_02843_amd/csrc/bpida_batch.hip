@@ -153,14 +153,14 @@ static_assert(check_lane_over(), "lane division");
 // Pushes the unit's entries as `parts` (1, 3 or 7) chunks, entry j to chunk j
 // modulo parts.  One part: returns false if the ring stayed full for the whole
 // bounded wait (the entries were not queued).  Several parts cost what one
-// does, and go to waves that wait; a part that a full ring refuses all the
-// same is dropped, its instance's counts void.
-__device__ __forceinline__ bool q_push(const Unit& u, RunStats& wc, int parts = 1) {
+// does; a part that a full ring refuses is dropped, its instance's counts void.
+// `pos`: the first ticket.
+__device__ __forceinline__ bool q_push(const Unit& u, RunStats& wc, uint64_t& pos, int parts) {
   Args& A = fresh();
   const int lane = lane_id();
   QueueCtl* q = A.q;
   const uint64_t mask = A.qmask;
-  uint64_t pos = 0, depth = 0;
+  uint64_t depth = 0;
   if (lane == 0) {
     pos = __hip_atomic_fetch_add(&q->tail, (uint64_t)parts, __ATOMIC_RELAXED, AGENT);
     if ((pos & 7) == 0) {  // (the line of `head` is busy with takes)
@@ -212,6 +212,11 @@ __device__ __forceinline__ bool q_push(const Unit& u, RunStats& wc, int parts = 
   const int lost = parts - (int)__popcll(okm);
   if (lost) drop_units(u.inst, lost, 2);
   return true;
+}
+
+__device__ __forceinline__ bool q_push(const Unit& u, RunStats& wc, int parts = 1) {
+  uint64_t pos = 0;
+  return q_push(u, wc, pos, parts);
 }
 
 // Takes a consumer ticket if `ticket` holds none, then checks whether that
@@ -286,23 +291,14 @@ __device__ __forceinline__ void end_search() {
 // Limit bookkeeping, executed by one wave.
 // ---------------------------------------------------------------------------
 
-// Chunks of every 64 roots that seed_limit deals out: 7, 3, 1 or 0.  As many
-// waves have to wait on tickets no queued chunk covers, so that what is dealt
-// goes to them and does not fill the queue, which is sized for the chunks of 64
-// roots and for spills.  `budget`: chunks it may deal before it looks again.
-// All waves that search (waves - wait) may deal on the same look, so their
-// budgets add up to 7 chunks a wave of the grid, for which the queue must have
-// room (BatchArgs::deal).  Looked at once a limit, a deep split on a small grid
-// filled its queue, every wave that had to push stopped searching, and the call
-// could end in BPIDA_ENOMEM; looked at before every 64 roots, 100 hard states
-// take 1.5 % longer.
-__device__ __forceinline__ int waiting_parts(uint64_t nodes, int& budget) {
+// Whether the queue has A.deal slots free beyond producer ticket t (the slot
+// that far ahead is ready for its next ticket; slots fill in order).
+__device__ __forceinline__ bool queue_has_room(uint64_t t) {
   Args& A = fresh();
-  int64_t ht = 0;
-  if (lane_id() == 0) ht = (int64_t)(ld_relaxed(&A.q->head) - ld_relaxed(&A.q->tail));
-  const int wait = wave_bcast((int)ht), waves = A.deal;
-  budget = min(wait, (int)(7u * (uint32_t)waves / (uint32_t)max(waves - wait, 1)));
-  return wait >= 7 && nodes >= 16384 ? 7 : wait >= 3 && nodes >= 8192 ? 3 : wait >= 1 ? 1 : 0;
+  const uint64_t ahead = t + (uint64_t)A.deal;
+  int room = 0;
+  if (lane_id() == 0) room = ld_relaxed(&A.seq[ahead & A.qmask].seq) >= 4 * ahead;
+  return wave_bcast(room) != 0;
 }
 
 // Hands the roots of instance i with f <= L out as chunks: the last one stays
@@ -317,7 +313,12 @@ __device__ __forceinline__ int waiting_parts(uint64_t nodes, int& budget) {
 // will keep one wave busy for long (the next one expands some four times the
 // nodes) is dealt out at once to the waves that wait: every 64 roots go to 2,
 // 4 or 8 of them (this wave among them for the last), 8192 nodes' worth each
-// at least.  Against one wave that donates from its 32nd round on: one hard
+// at least, whether they go on waiting or not, as long as the queue keeps room
+// for all chunks of 64 roots and for spills (BatchArgs::deal).  (Without that
+// a deep split on a small grid filled the queue, every wave that had to push
+// stopped searching, and the call could end in BPIDA_ENOMEM.  Dealing no more
+// chunks than waves wait at each 64 roots costs 4096 easy states 11 %: many small
+// chunks even their ends out.)  Against one wave that donates from its 32nd round on: one hard
 // state 1.25 -> 1.14 ms, 64 easy ones 562 -> 525 us; at half these counts the
 // easy ones take 3 % longer.
 template <int W>
@@ -335,8 +336,14 @@ __device__ __forceinline__ bool seed_limit(int i, int L, uint64_t nodes, uint64_
   const int nroots = (A.first_solution && A.goal_g[i] <= L) ? 0 : S->nroots;
   int fm = INT_MAX;
   bool full = false;
-  int budget = 0;
-  int parts = nodes >= 4096 && A.deal ? waiting_parts(nodes, budget) : 0;  // chunks dealt out beside this wave's own
+  int parts = 0;  // chunks dealt out beside this wave's own
+  uint64_t pushed = kNoTicket;  // ticket of the last push
+  if (nodes >= 4096 && A.deal) {
+    int64_t ht = 0;
+    if (lane == 0) ht = (int64_t)(ld_relaxed(&A.q->head) - ld_relaxed(&A.q->tail));
+    const int wait = wave_bcast((int)ht);
+    parts = wait >= 7 && nodes >= 16384 ? 7 : wait >= 3 && nodes >= 8192 ? 3 : wait >= 1 ? 1 : 0;
+  }
   mine.count = 0;
   mine.inst = i;
   mine.limit = L;
@@ -372,9 +379,8 @@ __device__ __forceinline__ bool seed_limit(int i, int L, uint64_t nodes, uint64_
     const int sc = A.seed_chunk > 0 ? A.seed_chunk : kQChunk;
     for (int p0 = 0; p0 < cnt && !full; p0 += sc) {
       const int n = min(sc, cnt - p0);
-      if (parts > budget) parts = waiting_parts(nodes, budget);
+      if (parts && pushed != kNoTicket && !queue_has_room(pushed)) parts = 0;
       const bool deal = n > parts && parts > 0;
-      if (deal) budget -= parts;
       // entry e of the chunk stays if e is a multiple of parts + 1
       const int stride = deal ? parts + 1 : 1;
       const int keep = deal ? (int)((uint32_t)(n + parts) / (uint32_t)stride) : n;
@@ -394,7 +400,7 @@ __device__ __forceinline__ bool seed_limit(int i, int L, uint64_t nodes, uint64_
           from_stage((int)(row * (uint32_t)stride + 1 + ((uint32_t)lane - row * (uint32_t)parts)), n - keep);
         }
         if (lane == 0) __hip_atomic_fetch_add(&S->outstanding, k, __ATOMIC_RELAXED, AGENT);
-        full = !q_push(mine, wc, k);
+        full = !q_push(mine, wc, pushed, k);
       }
       if (!full) from_stage(lane * stride, keep);
     }

@@ -422,7 +422,7 @@ struct BatchPlan {
   bool any5 = false;
   int64_t tree_nodes = 0, stride = 0, seed_chunks = 0, grid = 0;
   uint64_t qcap = 64;       // queue slots (a power of two)
-  uint64_t qwant = 64;      // the default queue size (queue_capacity option, or sized from the batch)
+  uint64_t qneed = 0;       // slots for the seeds and the stacks' overflow
   // mixed widths: split-tree and byte offsets and width per instance, in
   // pinned memory that the launch before the search reads
   int64_t *toff = nullptr, *boff = nullptr;
@@ -441,6 +441,22 @@ struct BatchBufs {
   InstState* istate = nullptr;
   RunStats* wave_stats = nullptr;
 };
+
+// Queue slots, a power of two: the option, or what the seeds and the stacks'
+// overflow need and as much again as all waves may deal out at once.
+uint64_t queue_slots(const Options& O, uint64_t need, int64_t waves) {
+  const uint64_t want = O.queue_capacity > 0 ? (uint64_t)O.queue_capacity : need + 2 * kDealSlots * (uint64_t)waves;
+  uint64_t q = 64;
+  while (q < want) q <<= 1;
+  return q;
+}
+
+// BatchArgs::deal: what is dealt leaves `need` slots free even if every wave
+// deals on the same look; a queue without that room deals nothing.
+int32_t deal_reserve(uint64_t need, int64_t waves, uint64_t slots) {
+  const uint64_t keep = need + kDealSlots * (uint64_t)waves;
+  return keep < slots ? (int32_t)keep : 0;
+}
 
 int plan_batched(int n, int width, const int32_t* h_widths, const Options& O, int num_cu,
                  BatchPlan* P) {
@@ -483,20 +499,16 @@ int plan_batched(int n, int width, const int32_t* h_widths, const Options& O, in
   P->grid = (int64_t)per_cu * num_cu;
   if (O.max_workgroups > 0) P->grid = std::min<int64_t>(P->grid, O.max_workgroups);
   // Default queue size: the seeds plus, per wave, room for the chunks its
-  // stack overflows into.  Smaller stacks spill more (64-node rounds on
-  // a 512-entry stack spill ~10x more than on 1024), and a 5x5 subtree's
-  // stack runs deeper on a stack of half as many entries (measured peaks:
-  // about 6 chunks per workgroup for 4x4 batches on 1024 entries, 36 for
-  // 5x5).  Smaller seed chunks were measured not to help (the grid fills
+  // stack overflows into and for dealt ones (kDealSlots).  Smaller stacks spill
+  // more, and a 5x5 subtree's stack runs deeper on a third of the entries
+  // (largest queue seen, chunks a wave: under 1 for 777 uneven 4x4 states on
+  // 1024 entries, 7 on 512; 5 for 61 5x5 states, 9 for 1088 of mixed widths).  Smaller seed chunks were measured not to help (the grid fills
   // through donation within the first rounds), so 64 is the default.
   P->sc = (int)O.seed_chunk;
   P->seed_chunks *= kQChunk / P->sc;
   const int64_t per_wg = P->any5 ? 64 : std::min<int64_t>(64, std::max<int64_t>(16, 32768 / P->cap));
-  const uint64_t want = O.queue_capacity > 0 ? (uint64_t)O.queue_capacity
-                                              : (uint64_t)(P->seed_chunks + P->grid * P->wpg * per_wg + 1024);
-  uint64_t q = 64;
-  while (q < want) q <<= 1;
-  P->qcap = P->qwant = q;
+  P->qneed = (uint64_t)(P->seed_chunks + P->grid * P->wpg * per_wg + 1024);
+  P->qcap = queue_slots(O, P->qneed, P->grid * P->wpg);
   return BPIDA_OK;
 }
 
@@ -604,7 +616,7 @@ int enqueue_batched_into(const uint8_t* d_states, int32_t* d_len, uint64_t* d_no
   A.start_limit = (int32_t)O.start_threshold;
   A.seed_chunk = P.sc;
   A.push_spin = (int32_t)O.push_spin;
-  A.deal = P.qcap >= kDealSlots * (uint64_t)(P.grid * P.wpg);
+  A.deal = deal_reserve(P.qneed, P.grid * P.wpg, P.qcap);
   A.exact_limit = exact_limit;
   PrepArgs R;
   R.states = d_states;
@@ -1044,14 +1056,11 @@ extern "C" int bpida_server_start(int32_t width, int32_t max_inflight, int32_t r
     uint64_t ring = 64;
     while (ring < (uint64_t)ring_capacity) ring <<= 1;
     const int sc_srv = (int)O.seed_chunk;
-    uint64_t qcap = 64;
     // as a batch: the seeds of every slot plus, per workgroup, room for the
     // chunks its stack overflows into (smaller stacks spill more)
     const int64_t per_wg = std::min<int64_t>(64, std::max<int64_t>(16, 32768 / cap));
-    const uint64_t want = O.queue_capacity > 0
-                              ? (uint64_t)O.queue_capacity
-                              : (uint64_t)(S * ((max_roots + sc_srv - 1) / sc_srv) + grid * wpg * per_wg + 1024);
-    while (qcap < want) qcap <<= 1;
+    const uint64_t need = (uint64_t)(S * ((max_roots + sc_srv - 1) / sc_srv) + grid * wpg * per_wg + 1024);
+    const uint64_t qcap = queue_slots(O, need, grid * wpg);
     free_server_host(V);
     if (V.qctl.ensure(sizeof(QueueCtl)) != hipSuccess || V.qseq.ensure(sizeof(SlotCtl) * qcap) != hipSuccess ||
         V.qslots.ensure(sizeof(QChunk) * qcap) != hipSuccess ||
@@ -1115,7 +1124,7 @@ extern "C" int bpida_server_start(int32_t width, int32_t max_inflight, int32_t r
     A.seed_chunk = sc_srv;
     A.push_spin = (int32_t)O.push_spin;
     A.server = 1;
-    A.deal = qcap >= kDealSlots * (uint64_t)(grid * wpg);
+    A.deal = deal_reserve(need, grid * wpg, qcap);
     ServerArgs K;
     K.host = V.host;
     K.req = V.req;

@@ -297,8 +297,7 @@ struct ServerArgs {
                         // beyond the waiting workgroups (<= 0: no limit)
 };
 
-// Queue slots a wave of the grid without which no limit is dealt out: all
-// dealing waves together add at most 7 chunks a wave to the queue.
+// Chunks a wave may queue between two looks for room while it deals a limit out.
 constexpr uint64_t kDealSlots = 8;
 
 struct BatchArgs {
@@ -328,7 +327,7 @@ struct BatchArgs {
                                // (status 1: a goal within it, 2: none)
   int32_t push_spin;     // polls of a full slot before a push gives its ticket up
   int32_t server;        // nonzero: continuous-batching server (ServerArgs behind these)
-  int32_t deal;          // waves of the grid if the queue has room for dealt chunks (kDealSlots), else 0
+  int32_t deal;          // free queue slots that dealing leaves for the rest (0: no dealing)
 };
 
 // The arguments of the kernel that can serve.  The others take BatchArgs

@@ -1,12 +1,12 @@
-"""Dealing a limit's roots adds nothing to the queue.
+"""Dealing a limit's roots leaves the queue room for the rest.
 
 A queue that holds the chunks of 64 roots and what the stacks spill must stay
 enough when limits are dealt out.  A deep split on a small grid has thousands
 of root chunks and few waves to take them; a push that finds its slot taken
 gives up at once here (push_spin 1), so a queue that fills up for a moment
-shows as BPIDA_ENOMEM.  And with a queue of 64 slots under a full grid, where a
-dealt chunk's slot may still hold an earlier one: exact, or BPIDA_ENOMEM, but
-never short counts, and the next call is exact again.
+shows as BPIDA_ENOMEM.  And with a queue of 64 slots under a full grid, where
+any push may find its slot taken: exact, or BPIDA_ENOMEM, but never short
+counts, and the next call is exact again.
 """
 import pytest
 
@@ -32,7 +32,7 @@ def test_deep_split_on_a_small_grid(opts, name, width, depth, k):
 
 
 @pytest.mark.parametrize("depth", [2, 8])
-def test_refused_dealt_chunks_never_shorten_counts(opts, depth):
+def test_refused_chunks_never_shorten_counts(opts, depth):
     B = opts
     set_mode(B, "batched")
     states, length, nodes = load("c2_md30_38")
