@@ -452,10 +452,12 @@ uint64_t queue_slots(const Options& O, uint64_t need, int64_t waves) {
 }
 
 // BatchArgs::deal: what is dealt leaves `need` slots free even if every wave
-// deals on the same look; a queue without that room deals nothing.
+// deals on the same look.  A smaller queue (an option, or the call without
+// allocation) is dealt into while it is a quarter full, if all waves' chunks
+// of one look fit at all.
 int32_t deal_reserve(uint64_t need, int64_t waves, uint64_t slots) {
-  const uint64_t keep = need + kDealSlots * (uint64_t)waves;
-  return keep < slots ? (int32_t)keep : 0;
+  const uint64_t look = kDealSlots * (uint64_t)waves;
+  return slots < look ? 0 : (int32_t)std::min(need + look, slots - slots / 4);
 }
 
 int plan_batched(int n, int width, const int32_t* h_widths, const Options& O, int num_cu,

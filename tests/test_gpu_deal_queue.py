@@ -50,3 +50,17 @@ def test_refused_chunks_never_shorten_counts(opts, depth):
         rc, ln, got = B.solve_raw(states[k:k + 1], 4)
         assert rc == B.OK
         assert_parity(ln, got, length[k:k + 1], nodes[k:k + 1], "after it")
+
+
+@pytest.mark.parametrize("queue", [64, 128, 256, 4096])
+def test_small_queues_on_a_small_grid(opts, queue):
+    """16 workgroups: from 128 slots (8 a wave) on a limit is dealt out while the queue is a quarter full."""
+    B = opts
+    set_mode(B, "batched")
+    states, length, nodes = load("c2_md30_38")
+    print("case: c2_md30_38[0..5], 16 workgroups, %d slots" % queue, flush=True)
+    B.set_option("max_workgroups", 16)
+    B.set_option("queue_capacity", queue)
+    rc, ln, got = B.solve_raw(states[:6], 4)
+    assert rc == B.OK, B.strerror(rc)
+    assert_parity(ln, got, length[:6], nodes[:6], "%d slots" % queue)
