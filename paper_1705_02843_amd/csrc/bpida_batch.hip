@@ -301,6 +301,14 @@ __device__ __forceinline__ bool queue_has_room(uint64_t t) {
   return wave_bcast(room) != 0;
 }
 
+// Most roots of a limit that is dealt out.  Chunks of 64 of more of them are
+// enough for the waves there are, and more but smaller ones cost their
+// hand-overs: dealt, split depth 12 took 5.3 ms for 2 hard 4x4 states against
+// 3.3 and 28.9 for 4 5x5 states against 19.2, depth 8 (1383 roots on average)
+// 5.8 ms for 30 5x5 states against 5.0; but 30 hard 4x4 states at depth 8 (635
+// roots) 13.6 against 14.6.
+constexpr int kDealRoots = 768;
+
 // Hands the roots of instance i with f <= L out as chunks: the last one stays
 // with the caller (`mine`: it is searched next, or pushed), the others go to
 // the queue.  A guard unit keeps the limit from completing meanwhile; it
@@ -338,7 +346,7 @@ __device__ __forceinline__ bool seed_limit(int i, int L, uint64_t nodes, uint64_
   bool full = false;
   int parts = 0;  // chunks dealt out beside this wave's own
   uint64_t pushed = kNoTicket;  // ticket of the last push
-  if (nodes >= 4096 && A.deal) {
+  if (nodes >= 4096 && nroots <= kDealRoots && A.deal) {
     int64_t ht = 0;
     if (lane == 0) ht = (int64_t)(ld_relaxed(&A.q->head) - ld_relaxed(&A.q->tail));
     const int wait = wave_bcast((int)ht);
@@ -1668,7 +1676,7 @@ hipError_t launch_server_setup(const BatchArgs& A, const ServerArgs& V, hipStrea
 // rounds of single-wave workgroups, the search of a batch of one width (W; 0:
 // any, by chunk, and the server): with the rounds of all three widths and the
 // admitter in one kernel it is 56 KB of code against 25, and a 640-entry
-// 4x4 stack's wave spills 160 bytes against 60 (batch of 100 hard states 25.8
+// 4x4 stack's wave spills 136 bytes against 52 (batch of 100 hard states 25.8
 // -> 24.0 ms, 3x3 batch of 2048 367 -> 351 us).  The
 // server's arguments go to the general kernel alone: with them 256 bytes
 // long (and 256 hidden ones), the others' made an easy state from host

@@ -64,3 +64,20 @@ def test_small_queues_on_a_small_grid(opts, queue):
     rc, ln, got = B.solve_raw(states[:6], 4)
     assert rc == B.OK, B.strerror(rc)
     assert_parity(ln, got, length[:6], nodes[:6], "%d slots" % queue)
+
+
+@pytest.mark.parametrize("name,width,depth", [("c2_md30_38", 4, 10), ("c2_md30_38", 4, 14), ("c4_mixed_w5", 5, 8),
+                                              ("c4_mixed_w5", 5, 12)])
+def test_a_deep_split_is_not_dealt(opts, name, width, depth):
+    """More than 768 roots make chunks enough: no more are taken than 64 roots each and what stacks push."""
+    B = opts
+    set_mode(B, "batched")
+    states, length, nodes = load(name)
+    print("case: %s[0], depth %d" % (name, depth), flush=True)
+    B.set_option("frontier_depth", depth)
+    rc, ln, got = B.solve_raw(states[:1], width)
+    assert rc == B.OK
+    assert_parity(ln, got, length[:1], nodes[:1], name)
+    s = B.last_stats()
+    limits = int((nodes[0] > 0).sum())
+    assert s["chunks_popped"] <= s["roots_read"] // 64 + limits + s["chunks_pushed"]
