@@ -254,8 +254,8 @@ int bpida_server_stop(void);
  *                        for 16-node rounds, 1024 for 64-node rounds (64-node
  *                        rounds need at least 512 on 4x4 and 1024 on 5x5, 256
  *                        on 3x3; 640, 672 and 768 only for batched 64-node
- *                        rounds with one-wave workgroups, where they let 25,
- *                        23 and 20 waves share a compute unit instead of 16;
+ *                        rounds with one-wave workgroups, where they let 24,
+ *                        24 and 20 waves share a compute unit instead of 16;
  *                        other combinations are BPIDA_EINVAL at solve time).
  *                        An entry is 10 bytes; batched 64-node rounds keep
  *                        3x3 and 4x4 stacks as 12-byte entries, four fifths
@@ -299,8 +299,10 @@ int bpida_server_stop(void);
  *   "donate_every"       batched mode: a quarter of the rounds between a
  *                        workgroup's looks for waiting workgroups to donate
  *                        to while every workgroup searches; when some wait,
- *                        the searching ones look more often, in proportion
- *                        (a power of two in 4..1024, default 128)
+ *                        the searching ones look more often, in proportion,
+ *                        down to every 32 rounds, the shortest period there
+ *                        is: 4 and 8 act alike (a power of two in 4..1024,
+ *                        default 128)
  *   "start_threshold"    first f-limit to search: -1 (default) = h0; else the
  *                        smallest h0 + 2j >= the value.  Columns of skipped
  *                        limits stay 0.  out_len is then the first searched
@@ -370,7 +372,8 @@ int64_t bpida_get_option(const char *key);
  *   out[4] search-kernel time in microseconds (plain: device events, summed;
  *          batched: device clock, first wave's start to last wave's end)
  *   out[5] plain mode: largest per-workgroup spill stack seen, in entries;
- *          batched mode: most chunks queued at once (seen at a push)
+ *          batched mode: most chunks queued at once (seen at every eighth
+ *          push)
  *   out[6] batched mode: chunks pushed to the work queue (seeds excluded)
  *   out[7] batched mode: chunks popped from the work queue
  *   out[8..10] batched mode: microseconds summed over workgroups spent

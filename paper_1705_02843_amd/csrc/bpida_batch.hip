@@ -322,11 +322,10 @@ constexpr int kDealRoots = 768;
 // nodes) is dealt out at once to the waves that wait: every 64 roots go to 2,
 // 4 or 8 of them (this wave among them for the last), 8192 nodes' worth each
 // at least, whether they go on waiting or not, as long as the queue keeps room
-// for all chunks of 64 roots and for spills (BatchArgs::deal).  (Without that
-// a deep split on a small grid filled the queue, every wave that had to push
-// stopped searching, and the call could end in BPIDA_ENOMEM.  Dealing no more
-// chunks than waves wait at each 64 roots costs 4096 easy states 11 %: many small
-// chunks even their ends out.)  Against one wave that donates from its 32nd round on: one hard
+// for all chunks of 64 roots and for spills (BatchArgs::deal): a queue that
+// dealt chunks fill stops every wave that has to push, and the call can end in
+// BPIDA_ENOMEM.  (Dealing no more chunks than waves wait at each 64 roots costs
+// 4096 easy states 11 %: many small chunks even their ends out.)  Against one wave that donates from its 32nd round on: one hard
 // state 1.25 -> 1.14 ms, 64 easy ones 562 -> 525 us; at half these counts the
 // easy ones take 3 % longer.
 template <int W>
@@ -1241,9 +1240,9 @@ void batch4_kernel(std::conditional_t<W == 0, ServerBatchArgs, BatchArgs>) {
   static_assert(NPL == 16 || NPL == 64, "nodes per round");
   static_assert(NPL == 16 || CAP >= 256, "stack too small for 64-node rounds");
   static_assert(WPG == 1 || WPG == 2 || WPG == 4, "waves per workgroup");
-  // u64 words of one wave's stack and counters: in
-  // registers these cost 22 scalar registers the search loop has better uses
-  // for (it spilled 40 to 190 vector registers around them)
+  // u64 words of one wave's stack and counters: in registers these cost 22
+  // scalar registers the search loop has better uses for (it spilled 40 to 190
+  // vector registers around them)
   constexpr int kWords = 10 * CAP / 8 + (counters_inside<CAP, NPL>() ? 0 : kCounterBytes / 8);
   __shared__ __attribute__((aligned(16))) uint64_t lds[WPG * kWords];
   uint64_t* st = lds + (WPG == 1 ? 0 : (int)(threadIdx.x >> 6) * kWords);

@@ -402,12 +402,14 @@ void tree_size(const Workspace& W, int w, int D, int64_t* stride, int64_t* max_r
 }
 
 // Whether a width can run with this LDS stack option.  3x3 and 5x5
-// instances always run 64-node rounds; a 5x5 state takes two entries, so its
-// stack holds cap / 2 of them.  A 64-node round can add 192 entries, so a
-// stack of 256 spills on almost every round: the spilled chunks, taken
-// oldest first, turn the search breadth-first and the work queue grows
-// without bound on 4x4 and 5x5 trees (measured: 2 million chunks were not
-// enough).  3x3 trees are small enough for 256.
+// instances always run 64-node rounds, which add up to 64 entries: the option
+// 256 gives 4x4 a stack of 176, 1024 gives 5x5 one of 336.  Smaller stacks spill
+// so often that the chunks, taken oldest first, turn the search breadth-first
+// and the work queue grows without bound on 4x4 and 5x5 trees.  (The lines were
+// measured when a round built a node's four children and added up to 192: 2
+// million chunks were not enough for 4x4 at 256.  They are kept as the
+// interface; how much smaller a stack today's rounds could take was not
+// measured.)  3x3 trees are small enough for 256.
 bool ring_fits(int w, int cap, int npl) {
   if (w == 3) return cap >= 256;
   if (w == 4) return npl == 16 || cap >= 512;

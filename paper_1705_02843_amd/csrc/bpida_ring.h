@@ -11,11 +11,11 @@
 // the stack if it keeps any, and the parent if it has moves left; a child that
 // keeps none (a third of all) is counted and never stored.  Every lane's work
 // is a node, at 34 vector and 7 LDS instructions a round.
-// Measured, 4096 uneven 4x4 states: 0.949 s before, 0.541 s with this round
-// (139 cycles a round and SIMD; 31 issue slots of 4 are vector issue, about
-// 98 of the 139 cycles are LDS).  With the per-cell constants from two
-// ds_bpermute (4 more LDS cycles a round and wave) it took 0.584 s where the
-// table below takes 0.507 s (stored states, stack option 640).
+// Measured, 4096 uneven 4x4 states: 0.949 s before, 0.541 s with this round.
+// Another such batch (the stored states), at stack option 640: 0.507 s, 139
+// cycles a round and SIMD, of which 31 issue slots of 4 are vector issue and
+// about 98 are LDS; with the per-cell constants from two ds_bpermute (4 more
+// LDS cycles a round and wave) instead of the table below 0.584 s.
 //
 // Two things make the move cheap although it differs from lane to lane:
 //

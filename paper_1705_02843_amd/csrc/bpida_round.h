@@ -105,29 +105,6 @@ __device__ __forceinline__ uint32_t bp_round(uint64_t* st, uint16_t* sm, uint32_
   return base + (uint32_t)__popcll(km);
 }
 
-// Moves LDS stack entries [src, src + n) down to [dst, dst + n), dst < src,
-// 64 at a time in ascending order: every entry is read before anything is
-// written over it.
-template <typename S>
-__device__ __forceinline__ void move_down(S* st, uint16_t* sm, uint32_t dst, uint32_t src, uint32_t n) {
-  const uint32_t lane = (uint32_t)lane_id();
-  for (uint32_t i = 0; i < n; i += 64u) {
-    const uint32_t k = i + lane;
-    if (k < n) {
-      const S t = st[src + k];
-      const uint16_t m = sm[src + k];
-      st[dst + k] = t;
-      sm[dst + k] = m;
-    }
-  }
-  WAVE_SYNC();
-}
-
-__device__ __forceinline__ int wave_max(int v) {
-  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
 __device__ __forceinline__ int wave_min(int v) {
   for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
   return v;
