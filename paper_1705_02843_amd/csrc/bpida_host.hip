@@ -445,18 +445,18 @@ struct BatchBufs {
 };
 
 // Queue slots, a power of two: the option, or what the seeds and the stacks'
-// overflow need and as much again as all waves may deal out at once.
-uint64_t queue_slots(const Options& O, uint64_t need, int64_t waves) {
-  const uint64_t want = O.queue_capacity > 0 ? (uint64_t)O.queue_capacity : need + 2 * kDealSlots * (uint64_t)waves;
+// overflow need.
+uint64_t queue_slots(const Options& O, uint64_t need) {
+  const uint64_t want = O.queue_capacity > 0 ? (uint64_t)O.queue_capacity : need;
   uint64_t q = 64;
   while (q < want) q <<= 1;
   return q;
 }
 
 // BatchArgs::deal: what is dealt leaves `need` slots free even if every wave
-// deals on the same look.  A smaller queue (an option, or the call without
-// allocation) is dealt into while it is a quarter full, if all waves' chunks
-// of one look fit at all.
+// deals on the same look.  A queue without that much more (`need` close below a
+// power of two, an option, the call without allocation) is dealt into while it
+// is a quarter full, if all waves' chunks of one look fit at all.
 int32_t deal_reserve(uint64_t need, int64_t waves, uint64_t slots) {
   const uint64_t look = kDealSlots * (uint64_t)waves;
   return slots < look ? 0 : (int32_t)std::min(need + look, slots - slots / 4);
@@ -512,7 +512,7 @@ int plan_batched(int n, int width, const int32_t* h_widths, const Options& O, in
   P->seed_chunks *= kQChunk / P->sc;
   const int64_t per_wg = P->any5 ? 64 : std::min<int64_t>(64, std::max<int64_t>(16, 32768 / P->cap));
   P->qneed = (uint64_t)(P->seed_chunks + P->grid * P->wpg * per_wg + 1024);
-  P->qcap = queue_slots(O, P->qneed, P->grid * P->wpg);
+  P->qcap = queue_slots(O, P->qneed);
   return BPIDA_OK;
 }
 
@@ -1064,7 +1064,7 @@ extern "C" int bpida_server_start(int32_t width, int32_t max_inflight, int32_t r
     // chunks its stack overflows into (smaller stacks spill more)
     const int64_t per_wg = std::min<int64_t>(64, std::max<int64_t>(16, 32768 / cap));
     const uint64_t need = (uint64_t)(S * ((max_roots + sc_srv - 1) / sc_srv) + grid * wpg * per_wg + 1024);
-    const uint64_t qcap = queue_slots(O, need, grid * wpg);
+    const uint64_t qcap = queue_slots(O, need);
     free_server_host(V);
     if (V.qctl.ensure(sizeof(QueueCtl)) != hipSuccess || V.qseq.ensure(sizeof(SlotCtl) * qcap) != hipSuccess ||
         V.qslots.ensure(sizeof(QChunk) * qcap) != hipSuccess ||
