@@ -505,9 +505,10 @@ int plan_batched(int n, int width, const int32_t* h_widths, const Options& O, in
   // Default queue size: the seeds plus, per wave, room for the chunks its
   // stack overflows into and for dealt ones (kDealSlots).  Smaller stacks spill
   // more, and a 5x5 subtree's stack runs deeper on a third of the entries
-  // (largest queue seen, chunks a wave: under 1 for 777 uneven 4x4 states on
-  // 1024 entries, 7 on 512; 5 for 61 5x5 states, 9 for 1088 of mixed widths).  Smaller seed chunks were measured not to help (the grid fills
-  // through donation within the first rounds), so 64 is the default.
+  // (largest queue seen, chunks a wave: 4096 uneven 4x4 states 1 on 1024
+  // entries, 5 on 640 and 27 on 512; 12 for 256 5x5 states).  Smaller seed chunks
+  // were measured not to help (the grid fills through donation within the first
+  // rounds), so 64 is the default.
   P->sc = (int)O.seed_chunk;
   P->seed_chunks *= kQChunk / P->sc;
   const int64_t per_wg = P->any5 ? 64 : std::min<int64_t>(64, std::max<int64_t>(16, 32768 / P->cap));
