@@ -325,9 +325,9 @@ constexpr int kDealRoots = 768;
 // for all chunks of 64 roots and for spills (BatchArgs::deal): a queue that
 // dealt chunks fill stops every wave that has to push, and the call can end in
 // BPIDA_ENOMEM.  (Dealing no more chunks than waves wait at each 64 roots costs
-// 4096 easy states 11 %: many small chunks even their ends out.)  Against one wave that donates from its 32nd round on: one hard
-// state 1.25 -> 1.14 ms, 64 easy ones 562 -> 525 us; at half these counts the
-// easy ones take 3 % longer.
+// 4096 easy states 11 %: many small chunks even their ends out.)  Against one
+// wave that donates from its 32nd round on: one hard state 1.25 -> 1.14 ms, 64
+// easy ones 562 -> 525 us; at half these counts the easy ones take 3 % longer.
 template <int W>
 __device__ __forceinline__ bool seed_limit(int i, int L, uint64_t nodes, uint64_t* stage, uint16_t* stage_m,
                                            Unit& mine, RunStats& wc) {
@@ -1204,9 +1204,9 @@ __device__ __forceinline__ bool run_unit(const Unit& u, ST& S, uint32_t top, Run
 // The persistent kernel.  A workgroup holds WPG independent waves (Sec. 5's
 // block = one warp, WPG times over): each wave has its own stack and takes
 // its own work, and no wave ever waits for another.  LDS per wave: 10 * CAP
-// bytes, i.e. CAP nodes of a 16-node round, about 4/5 CAP entries of the 3x3
-// and 4x4 64-node round, or a third of CAP of the 5x5 one; a chunk carries its
-// width.
+// bytes, i.e. CAP nodes of a 16-node round (56 fewer from 1024 on), about 4/5
+// CAP entries of the 3x3 and 4x4 64-node round, or a third of CAP of the 5x5
+// one; a chunk carries its width.
 //
 // Waves per SIMD a one-wave workgroup's stack allows (LDS: 160 KB per compute
 // unit).  The launch bound keeps the vector registers within that occupancy,
