@@ -1147,7 +1147,6 @@ __device__ __forceinline__ bool run_unit(const Unit& u, ST& S, uint32_t top, Run
     // past it would have overwritten entries (reported, never silent)
     if (top > (uint32_t)kCap) atomicOr(&q->err, 32);  // every lane: a uniform branch
     expanded += (uint64_t)kp;
-    wc.rounds += 1;
     if constexpr (FS) {
       // first-solution mode (Alg. 1 returns at its first goal): the unit that
       // expands a goal stops its instance; the others see the flag within 64
@@ -1183,7 +1182,6 @@ __device__ __forceinline__ bool run_unit(const Unit& u, ST& S, uint32_t top, Run
       if (gm != 0) goals += 1;
       tick += r;
       expanded += (uint64_t)kNpl * r;
-      wc.rounds += r;
       if constexpr (FS) {
         if (goals > 0) {
           if (lane == 0) __hip_atomic_store(&A.is[inst].stop, 1, __ATOMIC_RELAXED, AGENT);
@@ -1197,6 +1195,9 @@ __device__ __forceinline__ bool run_unit(const Unit& u, ST& S, uint32_t top, Run
   // of approaching moves from a slack-0 node cannot reach the goal, so it
   // ends at a node whose remaining moves all go away and are pruned
   if (kNpl == 64) fmin = u.limit + 2;
+  // (one round a tick: counted here, not in LDS every round; an abandoned
+  // unit's are left out, its call fails)
+  wc.rounds += tick - clk.tick;
   clk.tick = tick;
   return true;
 }
